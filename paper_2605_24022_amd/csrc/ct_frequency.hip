@@ -43,10 +43,15 @@ struct FftPlan {
   int32_t cutoff;     // bins k with min(k, n - k) >= cutoff are zeroed
   int32_t strips;     // strips per tensor = row_elems / (2 CP)
   int32_t groups;     // workgroups per tensor; workgroup g owns strips g * (strips / groups) ... in order
+  int cp() const { return 1 << lg_cp; }
 };
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
   return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+// a * conj(b)
+__device__ __forceinline__ float2 cmul_conj(float2 a, float2 b) {
+  return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
@@ -242,6 +247,207 @@ __device__ __forceinline__ void transform_fixed(float2* data, const float2* tw, 
   stockham_pass<R0, N, 1>(data, tw, 0, 0, 0, sgn);
   stockham_pass<R1, N, R0>(data, tw, 0, 0, 0, sgn);
   if constexpr (R2 > 1) stockham_pass<R2, N, R0 * R1>(data, tw, 0, 0, 0, sgn);
+}
+
+// ---- power-of-two lengths 256 ... 4096: plan compiled in ----------------------------------------
+// A forward transform by decimation in frequency leaves its bins in digit-reversed order, and an
+// inverse by decimation in time takes them in that order, so nothing is ever reordered: every pass
+// reads and writes the same places, each owned by one thread, and the last forward pass, the mask of
+// Eq. 3 and the first inverse pass are one step in registers, as are the global load with the first
+// pass and the squares with the last.  A strip crosses LDS four times with four barriers (Stockham
+// passes in both directions: eight crossings, sixteen barriers).
+// N = 16 x 16 x MID (N = 256: 16 x 16), 16 elements per thread and pass, bin = k0 + 16 k1 + 256 k2 in row
+// k0 N/16 + k1 MID + k2.  A thread's first twiddles do not depend on the strip: they are taken once
+// from a table of rounded values and stay in 30 registers, the second ones in a small LDS table (rows
+// of 17 against bank conflicts, 3 % of the launch), instead of products recomputed in every pass; the
+// next strip's values are fetched into registers meanwhile.
+// Bound by vector instructions (1290 per wave and strip against 2400 before, two thirds of the cycles;
+// the rest is LDS time right after the barriers).  32 x 2048 x 1024, K and V: 371 -> 205 us with the
+// Stockham kernel before.  Not kept: two workgroups of 512 threads per compute unit with half the
+// columns each (285 us: 16-byte row pieces), wave priorities against the common wait for LDS (+-0).
+
+// x + (x of the lane that the DPP control names)
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float keep, float send) {
+  return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), CTRL, 0xf, 0xf, true));
+}
+// One step of a reduce-scatter over lane groups: e[0 .. 2 H) -> e[0 .. H); a lane of the upper half of
+// its group keeps the upper half of the values.
+template <int CTRL, int H>
+__device__ __forceinline__ void halve(float* e, bool upper) {
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const float keep = upper ? e[i + H] : e[i], send = upper ? e[i] : e[i + H];
+    e[i] = add_dpp<CTRL>(keep, send);
+  }
+}
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppMirror = 0x140;   // lanes i and i ^ 1, i ^ 2, 7 - i, 15 - i
+// Sums of 16 values over the CP adjacent lanes of a group; lane `c` of the group ends up with the sums
+// of values first .. first + max(1, 16 / CP) - 1 in e[0 ..].
+template <int CP>
+__device__ __forceinline__ int reduce_scatter16(float (&e)[16], int c) {
+  int first = 0, h = 16;
+  if constexpr (CP >= 64) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) e[i] += __shfl_xor(e[i], 32);
+  }
+  if constexpr (CP >= 32) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) e[i] += __shfl_xor(e[i], 16);
+  }
+  if constexpr (CP >= 16) {
+    halve<kDppMirror, 8>(e, c & 8);
+    first += c & 8 ? 8 : 0;
+    halve<kDppHalfMirror, 4>(e, c & 4);
+    first += c & 4 ? 4 : 0;
+    halve<kDppXor2, 2>(e, c & 2);
+    first += c & 2 ? 2 : 0;
+    halve<kDppXor1, 1>(e, c & 1);
+    first += c & 1 ? 1 : 0;
+  } else if constexpr (CP == 8) {
+    halve<kDppHalfMirror, 8>(e, c & 4);
+    halve<kDppXor2, 4>(e, c & 2);
+    halve<kDppXor1, 2>(e, c & 1);
+    first = (c & 4 ? 8 : 0) + (c & 2 ? 4 : 0) + (c & 1 ? 2 : 0);
+  } else {
+    static_assert(CP == 4, "sequences per strip");
+    halve<kDppXor2, 8>(e, c & 2);
+    halve<kDppXor1, 4>(e, c & 1);
+    first = (c & 2 ? 8 : 0) + (c & 1 ? 4 : 0);
+  }
+  (void)h;
+  return first;
+}
+
+template <int N>
+struct FixedPlan {
+  static constexpr int CP = kFreqMaxElems / N;            // complex sequences per strip
+  static constexpr int MID = N == 256 ? 16 : N / 256;
+  static constexpr int M0 = N / 16;                       // distance of the elements of a first-pass butterfly
+  static constexpr int M1 = MID;                          // and of a second-pass one
+  // one spare row per 8 (16 when the middle pass owns 16 rows): the middle pass's accesses, MID rows
+  // apart, then fall on distinct banks
+  static constexpr int PAD = MID == 16 ? 4 : 3;
+  static constexpr int ROWS = N + (N >> PAD);
+  static constexpr __host__ __device__ int row(int n) { return n + (n >> PAD); }
+};
+
+// partial[tensor * groups * n + g * n + token] = sum over strip g of |N x~|^2
+template <int N>
+__global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                                                                  int64_t batch_stride, int32_t row_elems, int32_t n_work,
+                                                                  FftPlan p, float* __restrict__ partial) {
+  using P = FixedPlan<N>;
+  constexpr int CP = P::CP, MID = P::MID, M0 = P::M0, M1 = P::M1, T = kFreqThreads;
+  extern __shared__ float2 data[];
+  float2* const tab1 = data + P::ROWS * CP;      // [u % M1][j]
+  const int tid = threadIdx.x, c = tid % CP, u = tid / CP;
+  // first (and last) pass: rows u + j M0; second: rows (u / M1) M0 + j M1 + u % M1
+  float2* const d0 = data + P::row(u) * CP + c;
+  float2* const d1 = data + P::row(N == 256 ? 0 : (u / M1) * M0 + u % M1) * CP + c;
+  // twiddles exp(-2 pi i u j / N) and exp(-2 pi i (u % M1) j / M0), from a table that the strips then overwrite
+  for (int t = tid; t < N; t += T) {
+    float s, co;
+    sincospif(-2.f * ((float)t / (float)N), &s, &co);
+    data[t] = make_float2(co, s);
+  }
+  __syncthreads();
+  float2 w0[16];
+#pragma unroll
+  for (int j = 1; j < 16; ++j) w0[j] = data[(u * j) % N];
+  if (N > 256 && tid < M1 * 16) tab1[(tid >> 4) * 17 + (tid & 15)] = data[((tid >> 4) * (tid & 15) * 16) % N];
+  __syncthreads();
+  const float2* const w1 = tab1 + (u % M1) * 17;
+
+  const int gone_first = p.cutoff, gone_last = p.cutoff == 0 ? N - 1 : N - p.cutoff;   // Eq. 3: these bins go
+  const uint32_t gone = gone_last >= gone_first ? gone_last - gone_first + 1 : 0;
+  // workgroups that share 128-byte lines of the rows (adjacent strips) are given ids that differ
+  // by 8, which puts them on the same XCD (and its L2) at the same time
+  constexpr int per_line = CP >= 32 ? 1 : 32 / CP;
+  const bool swizzled = n_work % (8 * per_line) == 0 && p.groups % per_line == 0 && gridDim.x % 8 == 0;
+
+  // strip number `it` of this launch -> tensor (batch * 2 + kv) and strip of it
+  auto strip_of = [&](int it, int& strip) __attribute__((always_inline)) -> int {
+    int w = it;
+    if (swizzled) {
+      const int xcd = w & 7, slot = w >> 3;
+      w = (slot / per_line) * (8 * per_line) + xcd * per_line + slot % per_line;
+    }
+    const int tensor = w / p.groups;
+    strip = w - tensor * p.groups;
+    return tensor;
+  };
+  const uint32_t lane_off = (uint32_t)u * (row_elems / 2) + c;
+  uint32_t next[16];
+  auto fetch = [&](int it) __attribute__((always_inline)) {
+    int strip;
+    const int tensor = strip_of(it, strip);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(((tensor & 1) ? v : k) + (int64_t)(tensor >> 1) * batch_stride) + strip * CP;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) next[j] = __builtin_nontemporal_load(src + (int64_t)j * M0 * (row_elems / 2) + lane_off);
+  };
+  fetch(blockIdx.x);
+  for (int it = blockIdx.x; it < n_work; it += gridDim.x) {
+    float2 x[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] = make_float2(bf16_lo(next[j]), bf16_hi(next[j]));
+    if (it + (int)gridDim.x < n_work) fetch(it + gridDim.x);   // arrives while this strip is transformed
+    dft<16>(x, -1.f);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) d0[P::row(j * M0) * CP] = j == 0 ? x[0] : cmul(x[j], w0[j]);
+    __syncthreads();
+    if constexpr (N > 256) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] = d1[P::row(j * M1) * CP];
+      dft<16>(x, -1.f);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) d1[P::row(j * M1) * CP] = j == 0 ? x[0] : cmul(x[j], w1[j]);
+      __syncthreads();
+    }
+    // the last forward pass, the mask and the first inverse pass: MID neighbouring rows
+#pragma unroll
+    for (int i = 0; i < 16 / MID; ++i) {
+      const int q = u + i * (T / CP);
+      float2* const dm = data + P::row(q * MID) * CP + c;
+      float2 y[MID];
+#pragma unroll
+      for (int j = 0; j < MID; ++j) y[j] = dm[P::row(j) * CP];
+      dft<MID>(y, -1.f);
+      const int bin0 = N == 256 ? q : (q >> 4) + ((q & 15) << 4);
+      constexpr int BSTEP = N == 256 ? 16 : 256;
+#pragma unroll
+      for (int j = 0; j < MID; ++j)
+        if ((uint32_t)(bin0 + BSTEP * j - gone_first) < gone) y[j] = make_float2(0.f, 0.f);
+      dft<MID>(y, 1.f);
+#pragma unroll
+      for (int j = 0; j < MID; ++j) dm[P::row(j) * CP] = y[j];
+    }
+    __syncthreads();
+    if constexpr (N > 256) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] = j == 0 ? d1[0] : cmul_conj(d1[P::row(j * M1) * CP], w1[j]);
+      dft<16>(x, 1.f);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) d1[P::row(j * M1) * CP] = x[j];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] = j == 0 ? d0[0] : cmul_conj(d0[P::row(j * M0) * CP], w0[j]);
+    dft<16>(x, 1.f);
+    // Eq. 5: squares summed over the strip's sequences, which sit in CP adjacent lanes.  (The next strip's
+    // first pass writes the places that this thread has just read: no barrier.)
+    float e[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) e[j] = fmaf(x[j].x, x[j].x, x[j].y * x[j].y);
+    const int first = reduce_scatter16<CP>(e, c);
+    int strip;
+    const int tensor = strip_of(it, strip);
+    float* out = partial + ((int64_t)tensor * p.groups + strip) * N + u;
+    if (CP <= 16 || c < 16) {
+#pragma unroll
+      for (int j = 0; j < (CP >= 16 ? 1 : 16 / CP); ++j) out[(first + j) * M0] = e[j];
+    }
+  }
 }
 
 // partial[((b * 2 + kv) * groups + g) * n + token] = sum over the workgroup's strips of
@@ -460,18 +666,33 @@ __global__ __launch_bounds__(kFreqThreads) void freq_long_c_kernel(const float2*
   }
 }
 
-// Eq. 5-6: s_i = (||K~_i|| + ||V~_i||) / 2
+// Eq. 5-6: s_i = (||K~_i|| + ||V~_i||) / 2.  64 tokens per workgroup; its four waves each add a quarter of
+// the groups (group g by wave g mod 4), so that enough loads are in flight to read the partial sums at
+// memory speed (32 x 2048 tokens, 64 groups: 7 us against 19 us with a thread per token), and the
+// quarters are added in a fixed order.
 __global__ __launch_bounds__(256) void freq_finish_kernel(const float* __restrict__ partial, int32_t n, int32_t groups,
                                                           int32_t n_batch, float* __restrict__ scores) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)n_batch * n) return;
-  const int b = (int)(i / n), t = (int)(i - (int64_t)b * n);
+  __shared__ float part[2][4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int blocks = (n + 63) / 64;                 // workgroups per sequence
+  const int b = blockIdx.x / blocks, t = (blockIdx.x % blocks) * 64 + lane;
   float sk = 0.f, sv = 0.f;
-  for (int g = 0; g < groups; ++g) {
-    sk += partial[((int64_t)(b * 2 + 0) * groups + g) * n + t];
-    sv += partial[((int64_t)(b * 2 + 1) * groups + g) * n + t];
+  if (t < n) {
+    const float* pk = partial + (int64_t)(b * 2) * groups * n + t;
+    const float* pv = pk + (int64_t)groups * n;
+#pragma unroll 8
+    for (int g = wave; g < groups; g += 4) {
+      sk += pk[(int64_t)g * n];
+      sv += pv[(int64_t)g * n];
+    }
   }
-  scores[i] = 0.5f * (sqrtf(sk) + sqrtf(sv)) / (float)n;
+  part[0][wave][lane] = sk;
+  part[1][wave][lane] = sv;
+  __syncthreads();
+  if (wave != 0 || t >= n) return;
+  sk = (part[0][0][lane] + part[0][1][lane]) + (part[0][2][lane] + part[0][3][lane]);
+  sv = (part[1][0][lane] + part[1][1][lane]) + (part[1][2][lane] + part[1][3][lane]);
+  scores[(int64_t)b * n + t] = 0.5f * (sqrtf(sk) + sqrtf(sv)) / (float)n;
 }
 
 // ---- TopK ---------------------------------------------------------------------------------
@@ -642,8 +863,8 @@ static bool make_plan(int32_t n, int32_t row_elems, double alpha, int32_t n_batc
   return true;
 }
 
-static size_t freq_lds_bytes(const FftPlan& p, bool fixed) {
-  return ((size_t)((p.n + (p.n >> 4) + 1) << p.lg_cp) + (size_t)(fixed ? p.n / 8 : (p.n + 1) / 2)) * sizeof(float2);
+static size_t freq_lds_bytes(const FftPlan& p) {
+  return ((size_t)((p.n + (p.n >> 4) + 1) << p.lg_cp) + (size_t)(p.n + 1) / 2) * sizeof(float2);
 }
 
 }  // namespace ct
@@ -709,8 +930,7 @@ ct_status ct_frequency_scores(const void* k, const void* v, int32_t n_batch, int
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "long-sequence frequency score launch");
-    const int64_t total = (int64_t)n_batch * n_tokens;
-    launch_kernel(KC_FREQ, freq_finish_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
+    launch_kernel(KC_FREQ, freq_finish_kernel, dim3((unsigned)((int64_t)n_batch * ((n_tokens + 63) / 64))), dim3(256), 0, s,
                   (const float*)partial, n_tokens, groups, n_batch, scores);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "frequency score finish launch");
@@ -726,24 +946,29 @@ ct_status ct_frequency_scores(const void* k, const void* v, int32_t n_batch, int
   // with the plan compiled in; everything else the one that reads the plan at run time
   using Kernel = void (*)(const uint16_t*, const uint16_t*, int64_t, int32_t, int32_t, FftPlan, float*);
   Kernel kern = freq_energy_kernel<0>;
+  size_t lds = freq_lds_bytes(p);
+  const int n_work = n_batch * 2 * p.groups;
+  unsigned grid = n_work;
+  auto fixed = [&](Kernel f, int rows) {
+    kern = f;
+    lds = ((size_t)rows * p.cp() + 16 * 17) * sizeof(float2);
+    grid = n_work < kNumCUs ? n_work : kNumCUs;      // a workgroup fills a compute unit and goes on to further strips
+  };
   if ((int64_t)n_tokens << p.lg_cp == kFreqMaxElems) {
     switch (n_tokens) {
-      case 256: kern = freq_energy_kernel<256>; break;
-      case 512: kern = freq_energy_kernel<512>; break;
-      case 1024: kern = freq_energy_kernel<1024>; break;
-      case 2048: kern = freq_energy_kernel<2048>; break;
-      case 4096: kern = freq_energy_kernel<4096>; break;
+      case 256: fixed(freq_fixed_kernel<256>, FixedPlan<256>::ROWS); break;
+      case 512: fixed(freq_fixed_kernel<512>, FixedPlan<512>::ROWS); break;
+      case 1024: fixed(freq_fixed_kernel<1024>, FixedPlan<1024>::ROWS); break;
+      case 2048: fixed(freq_fixed_kernel<2048>, FixedPlan<2048>::ROWS); break;
+      case 4096: fixed(freq_fixed_kernel<4096>, FixedPlan<4096>::ROWS); break;
       default: break;
     }
   }
-  const size_t lds = freq_lds_bytes(p, kern != freq_energy_kernel<0>);
   hipError_t ea = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (ea != hipSuccess) return hip_fail(ea, "hipFuncSetAttribute(freq_energy_kernel)");
-  const int n_work = n_batch * 2 * p.groups;
-  launch_kernel(KC_FREQ, kern, dim3(n_work), dim3(kFreqThreads), (unsigned)lds, s, (const uint16_t*)k, (const uint16_t*)v,
+  if (ea != hipSuccess) return hip_fail(ea, "hipFuncSetAttribute(frequency score kernel)");
+  launch_kernel(KC_FREQ, kern, dim3(grid), dim3(kFreqThreads), (unsigned)lds, s, (const uint16_t*)k, (const uint16_t*)v,
                 batch_stride, row_elems, n_work, p, (float*)workspace);
-  const int64_t total = (int64_t)n_batch * n_tokens;
-  launch_kernel(KC_FREQ, freq_finish_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
+  launch_kernel(KC_FREQ, freq_finish_kernel, dim3((unsigned)((int64_t)n_batch * ((n_tokens + 63) / 64))), dim3(256), 0, s,
                 (const float*)workspace, n_tokens, p.groups, n_batch, scores);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "frequency score launch");
