@@ -16,12 +16,15 @@
 // staging): a wave-wide load fills 8 rows of 128 bytes, the 16-byte pieces of a row are
 // XOR-swizzled so that the 128-bit fragment reads of 16 consecutive rows hit distinct banks.
 //
-// Workgroup: 512 threads = 8 waves (2 feature halves x 4 token quarters), tile 256 features x
-// 256 tokens x 64 (K step), wave tile 128 x 64 = 4 x 2 MFMA tiles of
-// v_mfma_f32_32x32x16_bf16, three weight-tile and two token-tile LDS slots of 32 KiB (loads run
-// two and one K steps ahead), one barrier per K step, placed before the step's last MFMA group so
-// that it passes while the matrix core is busy.  Two waves share a SIMD, so one wave's other
-// waits hide behind the other's MFMAs.
+// Workgroup tile: 256 features x 256 (or 128) tokens x 64 (K step), 32 x 32 x 16 MFMAs.  Reading the
+// fragments from LDS takes about as long as multiplying them, so the wave tiles are as square as the
+// registers allow: 64 x 64 for eight waves on 128 tokens (128 x 32 read a quarter more: QKV of 1228 rows
+// 67 -> 63 us, of 153 rows 47 -> 39 us), 128 x 64 for eight waves on 256 tokens, 128 x 128 for four.
+// LDS holds three weight tiles and two (of 128 tokens: three) token tiles: loads run two and one
+// (two) K steps ahead.  One barrier per K step, placed inside the step's last MFMA group so
+// that it passes while the matrix core is busy; fragment reads and tile loads go out one by one between
+// the MFMAs where a wave has the matrix core to itself or the tile is small (sent in bursts ahead of each group
+// of MFMAs they held it up: gate/up, K = 4096, n = 1638: 400 -> 350 us together with the 64 x 64 tiles).
 // Workgroups are numbered so that the ones resident on one XCD (ids congruent mod 8) cover a
 // patch of neighbouring tiles and share their W and X tiles in that XCD's L2.
 #include <string.h>
@@ -38,7 +41,7 @@ constexpr int BF = 256;           // features per workgroup
 constexpr int BK = 64;            // reduction elements per stage
 constexpr int ROWB = BK * 2;      // LDS row in bytes (unpadded, swizzled)
 constexpr int A_BYTES = BF * ROWB;
-constexpr int A_SLOTS = 3, B_SLOTS = 2;   // LDS slots per operand tile
+constexpr int A_SLOTS = 3;        // LDS slots of weight tiles
 
 enum Epilogue { EPI_QKV_ROPE = 0, EPI_LINEAR = 1, EPI_SWIGLU = 2, EPI_PARTIAL = 3 };
 
@@ -99,12 +102,17 @@ __device__ __forceinline__ void tile_of(int v, int nF, int nT, int* f_tile, int*
 template <int EPI, int D, int STYLE, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void gemm_kernel(
     GemmArgs a, RopeTable rope, ChunkTable chunks) {
-  constexpr int NWAVES = NW;                 // 8: two waves per SIMD, wave tile 128 x 32 NB; 4: one, 128 x 64 NB
+  constexpr int NWAVES = NW;                 // 8: two waves per SIMD; 4: one
   constexpr int A_LOADS = BF / 8 / NWAVES;   // wave-wide loads (8 rows each) per wave and stage
-  constexpr int TW = 8 * NB / NW;            // 32-token MFMA tiles per wave
   constexpr int BT = 128 * NB;
+  constexpr int WF = NB == 1 ? 4 : 2, WT = NW / WF;   // waves along features and tokens
+  constexpr int FM = BF / 32 / WF, TW = BT / 32 / WT; // 32 x 32 MFMA tiles per wave
+  // tile row of feature tile m of wave wf: FM = 4 owns 128 consecutive rows; FM = 2 owns 32 rows and,
+  // where the epilogue pairs rows 64 apart (gate with up, halves of a 128-wide head), the 32 that go with them
+  constexpr bool PAIR64 = EPI == EPI_SWIGLU || (EPI == EPI_QKV_ROPE && D == 128);
   constexpr int B_BYTES = BT * ROWB;
   constexpr int B_LOADS = BT / 8 / NWAVES;
+  constexpr int B_SLOTS = NB == 1 ? 3 : 2;   // LDS slots of token tiles; they are loaded B_SLOTS - 1 steps ahead
   __shared__ __align__(1024) unsigned char lds[A_SLOTS * A_BYTES + B_SLOTS * B_BYTES];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -151,111 +159,146 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
   };
   // A (weight) tiles cycle through three LDS slots, B (token) tiles through two.  `half` selects
   // the first or second half of a tile's loads.
-  auto issue_a = [&](int k0, int slot, int half) __attribute__((always_inline)) {
-    const uint16_t* wk = a.wqkv + k0;      // scalar bases advanced to the K step
-    const uint16_t* uk = EPI == EPI_SWIGLU ? a.w_up + k0 : wk;
-    const uint32_t st = lds_addr0 + slot * A_BYTES;
-#pragma unroll
-    for (int j = half * (A_LOADS / 2); j < (half + 1) * (A_LOADS / 2); ++j) {
-      // a wave-wide load covers 8 consecutive tile rows: all gate or all up
-      const bool up = EPI == EPI_SWIGLU && ((((NWAVES * j + wave) * 8) >> 6) & 1);
-      dma16(up ? uk : wk, a_off[j], st + (NWAVES * j + wave) * 1024);
-    }
+  auto issue_a1 = [&](int k0, int slot, int j) __attribute__((always_inline)) {
+    // scalar bases advanced to the K step; a wave-wide load covers 8 consecutive tile rows: all gate or all up
+    const bool up = EPI == EPI_SWIGLU && ((((NWAVES * j + wave) * 8) >> 6) & 1);
+    dma16((up ? a.w_up : a.wqkv) + k0, a_off[j], lds_addr0 + slot * A_BYTES + (NWAVES * j + wave) * 1024);
   };
-  auto issue_b = [&](int k0, int slot, int half) __attribute__((always_inline)) {
-    const uint16_t* xk = a.hidden + k0;
-    const uint32_t st = lds_addr0 + A_SLOTS * A_BYTES + slot * B_BYTES;
+  auto issue_b1 = [&](int k0, int slot, int j) __attribute__((always_inline)) {
+    dma16(a.hidden + k0, b_off[j], lds_addr0 + A_SLOTS * A_BYTES + slot * B_BYTES + (NWAVES * j + wave) * 1024);
+  };
+  auto issue_a = [&](int k0, int slot) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = half * (B_LOADS / 2); j < (half + 1) * (B_LOADS / 2); ++j)
-      dma16(xk, b_off[j], st + (NWAVES * j + wave) * 1024);
+    for (int j = 0; j < A_LOADS; ++j) issue_a1(k0, slot, j);
+  };
+  auto issue_b = [&](int k0, int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < B_LOADS; ++j) issue_b1(k0, slot, j);
   };
 
-  const int wf = wave & 1, wt = wave >> 1;
+  const int wf = wave % WF, wt = wave / WF;
+  const int row0 = FM == 4 ? wf * 128 : PAIR64 ? (wf >> 1) * 128 + (wf & 1) * 32 : wf * 64;
+  constexpr int MROW = FM == 2 && PAIR64 ? 64 : 32;   // rows from one feature tile of the wave to the next
   // fragment read offsets inside a stage (bytes): row base + swizzled piece, per k-step
   int a_frag[BK / 16], b_frag[BK / 16];
 #pragma unroll
   for (int ks = 0; ks < BK / 16; ++ks) {
-    a_frag[ks] = (wf * 128 + l32) * ROWB + (((2 * ks + hi) ^ swz(l32)) * 16);
+    a_frag[ks] = (row0 + l32) * ROWB + (((2 * ks + hi) ^ swz(l32)) * 16);
     b_frag[ks] = (wt * 32 * TW + l32) * ROWB + (((2 * ks + hi) ^ swz(l32)) * 16);
   }
 
-  f32x16 acc[4][TW];
+  f32x16 acc[FM][TW];
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < FM; ++m)
 #pragma unroll
     for (int n = 0; n < TW; ++n)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[m][n][i] = 0.f;
 
   // Pipeline.  The weight tile of K step kt + 2 and the token tile of step kt + 1 are in flight
-  // while step kt is multiplied (all 160 KiB of LDS: 3 + 2 slots of 32 KiB); with one step in
+  // while step kt is multiplied (all 160 KiB of LDS: 3 + 2 slots of 32 KiB; a 128-token tile leaves room
+  // for a third token slot, and kt + 2 is in flight for both); with one step in
   // flight the load path alone (issue, L2 latency, barrier) takes as long as the MFMAs of a step.
   // Loads are issued in the order B(kt + 1), A(kt + 2), so when step kt + 1 is about to start
-  // everything but the newest A_LOADS loads - A(kt + 2) - is waited for.  Past the end the last
+  // everything but the newest loads - A(kt + 2), and B(kt + 2) with three slots - is waited for.  Past the end the last
   // step is loaded again into the free slots, which keeps the number of loads in flight, and the
   // wait, uniform.
-  // The workgroup barrier of a step sits before its last MFMA group, not after it: a wave waits
-  // for its loads of the next step, meets the others, issues the first fragment reads of the
-  // next step and only then issues the last 4 x TW MFMAs of this step, so the barrier and the
-  // LDS latency that follows it pass while the matrix core still has work queued.  (All waves of
+  // The workgroup barrier of a step sits near the start of its last MFMA group, not after it: a wave waits
+  // for its loads of the next step, meets the others, and the first fragment reads of the
+  // next step go out between the MFMAs left of this one, so the barrier and the
+  // LDS latency that follows it pass while the matrix core still has work.  (All waves of
   // a workgroup stand at the barrier together, so the other wave of the SIMD cannot cover it.)
   // this workgroup's part of the reduction: K steps kbeg .. kbeg + nk - 1
   const int nk_all = a.E / BK;
   const int kbeg = (int)((long)kp * nk_all / a.k_parts);
   const int nk = (int)((long)(kp + 1) * nk_all / a.k_parts) - kbeg;
   const int kbase = kbeg * BK;
-  constexpr int WAIT_STEP = (A_LOADS & 15) | 0x0f70;   // s_waitcnt vmcnt(A_LOADS)
+  constexpr int AHEAD = B_SLOTS == 3 ? A_LOADS + B_LOADS : A_LOADS;   // loads of a step that may stay in flight at its end
+  constexpr int WAIT_STEP = AHEAD | 0x0f70;                           // s_waitcnt vmcnt(AHEAD)
+  static_assert(AHEAD < 16, "vmcnt field");
   __builtin_amdgcn_s_waitcnt(0x0f70);   // ordinary loads so far (row indices) are complete
-  issue_a(kbase, 0, 0); issue_a(kbase, 0, 1);
-  issue_b(kbase, 0, 0); issue_b(kbase, 0, 1);
-  issue_a(kbase + min(1, nk - 1) * BK, 1, 0); issue_a(kbase + min(1, nk - 1) * BK, 1, 1);
+  const int k1 = kbase + min(1, nk - 1) * BK;
+  issue_a(kbase, 0);
+  issue_b(kbase, 0);
+  if (B_SLOTS == 3) issue_b(k1, 1);
+  issue_a(k1, 1);
   int sa = 0, sb = 0;
-  // The fragment reads of MFMA group ks + 1 are issued before the MFMAs of group ks (two register
-  // sets), so a wave waits for LDS once per K step instead of once per group.
-  bf16x8 fa[2][4], fb[2][TW];
-  auto read_frags = [&](const unsigned char* a_base, const unsigned char* b_base, int ks, int set) __attribute__((always_inline)) {
-#pragma unroll
-    for (int n = 0; n < TW; ++n) fb[set][n] = *reinterpret_cast<const bf16x8*>(b_base + b_frag[ks] + n * 32 * ROWB);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) fa[set][m] = *reinterpret_cast<const bf16x8*>(a_base + a_frag[ks] + m * 32 * ROWB);
+  // Two register sets of fragments: those of MFMA group ks + 1 are read while group ks runs, one read
+  // behind each MFMA, and the tile loads go out between them, so that no burst of memory instructions
+  // holds up the matrix core of a wave.
+  bf16x8 fa[2][FM], fb[2][TW];
+  constexpr int G = FM * TW, R = FM + TW;    // MFMAs and fragment reads of a group
+  constexpr int KG = BK / 16;
+  // Two waves per SIMD on 256-token tiles take turns instead: loads and reads ahead of a group of MFMAs
+  // (one by one: QKV of 1638 gathered rows in the layer 94 -> 104 us, of 16384 rows 670 -> 682 us).
+  constexpr bool AHEAD_OF_GROUP = NB == 2 && NW == 8;
+  constexpr int BAR_AT = AHEAD_OF_GROUP ? 0 : G / 8;              // MFMAs of a step's last group that go ahead of its barrier
+  static_assert(R <= G, "a read behind every MFMA");
+  auto read_frag = [&](const unsigned char* a_base, const unsigned char* b_base, int ks, int set, int r) __attribute__((always_inline)) {
+    if (r < TW) fb[set][r] = *reinterpret_cast<const bf16x8*>(b_base + b_frag[ks] + r * 32 * ROWB);
+    else fa[set][r - TW] = *reinterpret_cast<const bf16x8*>(a_base + a_frag[ks] + (r - TW) * MROW * ROWB);
   };
-  auto mfma_group = [&](int set) __attribute__((always_inline)) {
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int n = 0; n < TW; ++n)
-        acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][m], fb[set][n], acc[m][n], 0, 0, 0);
+  auto mfma = [&](int set, int i) __attribute__((always_inline)) {
+    const int m = i / TW, n = i % TW;
+    acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][m], fb[set][n], acc[m][n], 0, 0, 0);
   };
   __builtin_amdgcn_s_waitcnt(WAIT_STEP);   // this wave's loads of step 0 have landed
   __syncthreads();                         // everybody's have
-  read_frags(lds, lds + A_SLOTS * A_BYTES, 0, 0);
+#pragma unroll
+  for (int r = 0; r < R; ++r) read_frag(lds, lds + A_SLOTS * A_BYTES, 0, 0, r);
   for (int kt = 0; kt < nk; ++kt) {
     const unsigned char* a_base = lds + sa * A_BYTES;
     const unsigned char* b_base = lds + A_SLOTS * A_BYTES + sb * B_BYTES;
     const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slot of step kt - 1
-    const int sb_free = sb ^ 1;
-    const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1;
-    const int kb1 = kbase + min(kt + 1, nk - 1) * BK, ka2 = kbase + min(kt + 2, nk - 1) * BK;
+    const int sb_free = sb == 0 ? B_SLOTS - 1 : sb - 1;
+    const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1, sb_next = sb == B_SLOTS - 1 ? 0 : sb + 1;
+    const int kb1 = kbase + min(kt + B_SLOTS - 1, nk - 1) * BK, ka2 = kbase + min(kt + 2, nk - 1) * BK;
 #pragma unroll
-    for (int ks = 0; ks < BK / 16 - 1; ++ks) {
-      // the loads go out a part at a time, one part per MFMA group: a burst of all of them from
-      // all waves would queue at the texture addresser.  B first: it is needed a step earlier.
-      if (ks == 0) { issue_b(kb1, sb_free, 0); issue_b(kb1, sb_free, 1); }
-      else issue_a(ka2, sa_free, ks - 1);
-      read_frags(a_base, b_base, ks + 1, (ks + 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_group(ks & 1);
+    for (int ks = 0; ks < KG - 1; ++ks) {
+      constexpr int HALF = A_LOADS / 2;
+      static_assert(A_LOADS <= G && B_LOADS <= G, "a load behind every MFMA");
+      // tile loads, B first: it is needed a step earlier
+      auto load_tile = [&](int i) __attribute__((always_inline)) {
+        if (ks == 0 && i < B_LOADS) issue_b1(kb1, sb_free, i);
+        if (ks > 0 && i < HALF) issue_a1(ka2, sa_free, (ks - 1) * HALF + i);
+      };
+      if (AHEAD_OF_GROUP) {
+#pragma unroll
+        for (int i = 0; i < B_LOADS; ++i) load_tile(i);
+#pragma unroll
+        for (int r = 0; r < R; ++r) read_frag(a_base, b_base, ks + 1, (ks + 1) & 1, r);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        mfma(ks & 1, i);
+        if (AHEAD_OF_GROUP) continue;
+        if (i < R) read_frag(a_base, b_base, ks + 1, (ks + 1) & 1, i);
+        load_tile(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // vmcnt(A_LOADS): this wave's loads of step kt + 1 have
+#pragma unroll
+    for (int i = 0; i < BAR_AT; ++i) mfma((KG - 1) & 1, i);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // vmcnt(AHEAD): this wave's loads of step kt + 1 have
                                                         // landed; lgkmcnt(0): its fragment reads of step kt are done
     __syncthreads();                         // everybody's have; everybody is done reading step kt
-    read_frags(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_free * B_BYTES, 0, 0);
+#pragma unroll
+    for (int r = 0; r < (AHEAD_OF_GROUP ? R : 0); ++r) read_frag(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_next * B_BYTES, 0, 0, r);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_group((BK / 16 - 1) & 1);
-    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = BAR_AT; i < G; ++i) {
+      mfma((KG - 1) & 1, i);
+      if (AHEAD_OF_GROUP) continue;
+      if (i - BAR_AT < R) read_frag(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_next * B_BYTES, 0, 0, i - BAR_AT);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int r = AHEAD_OF_GROUP ? R : G - BAR_AT; r < R; ++r) read_frag(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_next * B_BYTES, 0, 0, r);
     sa = sa_next;
-    sb = sb_free;
+    sb = sb_next;
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);   // the repeated loads of the last steps have landed before the LDS is released
 
@@ -284,78 +327,84 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
     for (int n = 0; n < TW; ++n) {
       const int tl = wt * 32 * TW + n * 32 + l32;
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
+      for (int m = 0; m < FM; ++m)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 w = {acc[m][n][4 * g + 0], acc[m][n][4 * g + 1], acc[m][n][4 * g + 2], acc[m][n][4 * g + 3]};
-          *reinterpret_cast<f32x4*>(dst + (size_t)tl * BF + wf * 128 + m * 32 + 8 * g + 4 * hi) = w;
+          *reinterpret_cast<f32x4*>(dst + (size_t)tl * BF + row0 + m * MROW + 8 * g + 4 * hi) = w;
         }
     }
     return;
   } else if constexpr (EPI == EPI_LINEAR) {
-    const int f0 = f_blk + wf * 128;
+    const int f0 = f_blk + row0;
     // Residuals arrive the same way, as 16-byte loads of the lane's eight features, and are swapped
-    // back into the accumulator layout.  All residual values of the wave's tile are fetched before
-    // the first result is stored: `out` may be the residual buffer itself, so the compiler cannot
-    // move these loads above stores on its own, and with few loads in flight per lane the epilogue
-    // is bound by memory latency.
-    u32x4 res[TW][4][2];
-    if (a.residual != nullptr) {
+    // back into the accumulator layout.  Those of all the wave's token tiles (one tile at a time where four waves
+    // hold four each: registers) are fetched before the first result is stored: `out` may be the
+    // residual buffer itself, so the compiler cannot move these loads above stores on its own, and with
+    // few loads in flight per lane the epilogue is bound by memory latency.
+    constexpr int NG = TW > 2 ? 1 : TW;       // token tiles whose residuals are in flight together
+    u32x4 res[NG][FM][2];
 #pragma unroll
-      for (int n = 0; n < TW; ++n) {
-        const int t = min(t_blk + wt * 32 * TW + n * 32 + l32, a.n_sel - 1);
+    for (int n0 = 0; n0 < TW; n0 += NG) {
+      if (a.residual != nullptr) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const int fm = min(f0 + m * 32, a.O - 32);
-          const size_t row = (size_t)t * a.O + fm + 8 * hi;
+        for (int n = 0; n < NG; ++n) {
+          const int t = min(t_blk + wt * 32 * TW + (n0 + n) * 32 + l32, a.n_sel - 1);
 #pragma unroll
-          for (int q = 0; q < 2; ++q) res[n][m][q] = *reinterpret_cast<const u32x4*>(a.residual + row + 16 * q);
-        }
-      }
-    }
+          for (int m = 0; m < FM; ++m) {
+            const int fm = min(f0 + m * MROW, a.O - 32);
+            const size_t row = (size_t)t * a.O + fm + 8 * hi;
 #pragma unroll
-    for (int n = 0; n < TW; ++n) {
-      const int t = t_blk + wt * 32 * TW + n * 32 + l32;
-      const bool t_ok = t < a.n_sel;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int fm = f0 + m * 32;
-        if (fm >= a.O) continue;            // uniform for the wave
-        if (a.residual != nullptr) {
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            // r[0], r[1]: features +0..3 of the lane's eight, r[2], r[3]: +4..7
-            const u32x4 r = res[n][m][q];
-            const auto d0 = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);   // dword 0 of groups 2q, 2q + 1
-            const auto d1 = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);   // dword 1
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              const int i0 = 4 * (2 * q + e);
-              acc[m][n][i0 + 0] += bf16_lo(d0[e]);
-              acc[m][n][i0 + 1] += bf16_hi(d0[e]);
-              acc[m][n][i0 + 2] += bf16_lo(d1[e]);
-              acc[m][n][i0 + 3] += bf16_hi(d1[e]);
-            }
+            for (int q = 0; q < 2; ++q) res[n][m][q] = *reinterpret_cast<const u32x4*>(a.residual + row + 16 * q);
           }
         }
-        store_tile(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, acc[m][n], t_ok);
+      }
+      if (NG < TW) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int n = n0; n < n0 + NG; ++n) {
+        const int t = t_blk + wt * 32 * TW + n * 32 + l32;
+        const bool t_ok = t < a.n_sel;
+#pragma unroll
+        for (int m = 0; m < FM; ++m) {
+          const int fm = f0 + m * MROW;
+          if (fm >= a.O) continue;            // uniform for the wave
+          if (a.residual != nullptr) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+              // r[0], r[1]: features +0..3 of the lane's eight, r[2], r[3]: +4..7
+              const u32x4 r = res[n - n0][m][q];
+              const auto d0 = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);   // dword 0 of groups 2q, 2q + 1
+              const auto d1 = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);   // dword 1
+#pragma unroll
+              for (int e = 0; e < 2; ++e) {
+                const int i0 = 4 * (2 * q + e);
+                acc[m][n][i0 + 0] += bf16_lo(d0[e]);
+                acc[m][n][i0 + 1] += bf16_hi(d0[e]);
+                acc[m][n][i0 + 2] += bf16_lo(d1[e]);
+                acc[m][n][i0 + 3] += bf16_hi(d1[e]);
+              }
+            }
+          }
+          store_tile(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, acc[m][n], t_ok);
+          if (NG < TW) __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
     return;
   } else if constexpr (EPI == EPI_SWIGLU) {
-    const int f0 = f_blk + wf * 64;          // output features of this wave: f0 .. f0 + 63
+    const int f0 = f_blk + (row0 >> 7) * 64 + (row0 & 63);   // first output feature of this wave
 #pragma unroll
     for (int n = 0; n < TW; ++n) {
       const int t = t_blk + wt * 32 * TW + n * 32 + l32;
       const bool t_ok = t < a.n_sel;
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {          // gate tile m, up tile m + 2
+      for (int m = 0; m < FM / 2; ++m) {     // gate tile m, up tile m + FM / 2
         const int fm = f0 + m * 32;
         if (fm >= a.O) continue;             // uniform for the wave
         f32x16 y;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const float gate = acc[m][n][i], up = acc[m + 2][n][i];
+          const float gate = acc[m][n][i], up = acc[m + FM / 2][n][i];
           y[i] = gate / (1.0f + __builtin_amdgcn_exp2f(-gate * 1.4426950408889634f)) * up;   // silu(gate) * up
         }
         store_tile(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, y, t_ok);
@@ -363,8 +412,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
     }
     return;
   } else {
-    // accumulator element i of tile (m, n): feature f0 + m*32 + 8*(i/4) + 4*hi + i%4, token = column l32
-    const int f0 = f_blk + wf * 128;
+    // accumulator element i of tile (m, n): feature f0 + m*MROW + 8*(i/4) + 4*hi + i%4, token = column l32
+    const int f0 = f_blk + row0;
     const int rope_end = (a.Hq + a.Hkv) * D;   // features below this are q or k heads
     const int q_end = a.Hq * D;
   #pragma unroll
@@ -377,21 +426,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 
       if (a.bias != nullptr) {
   #pragma unroll
-        for (int m = 0; m < 4; ++m)
+        for (int m = 0; m < FM; ++m)
   #pragma unroll
           for (int i = 0; i < 16; ++i) {
-            const int f = min(f0 + m * 32 + 8 * (i >> 2) + 4 * hi + (i & 3), a.O - 1);
+            const int f = min(f0 + m * MROW + 8 * (i >> 2) + 4 * hi + (i & 3), a.O - 1);
             acc[m][n][i] += bf16_lo((uint32_t)a.bias[f]);
           }
       }
 
       if (STYLE == 0) {
-        // pairs (j, j + D/2): D = 128 couples tiles (m, m+2); D = 64 couples (m, m+1) for m even
-        constexpr int STEP = D / 64;          // tile distance between the two halves of a pair
+        // pairs (j, j + D/2), D/2 rows apart
+        constexpr int STEP = D / 2 / MROW;    // tile distance between the two halves of a pair
   #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          if ((D == 128 && m >= 2) || (D == 64 && (m & 1))) continue;
-          const int fa0 = f0 + m * 32;        // first feature of the "a" half tile
+        for (int m = 0; m < FM; ++m) {
+          if (m & STEP) continue;
+          const int fa0 = f0 + m * MROW;        // first feature of the "a" half tile
           if (fa0 >= rope_end) continue;      // v heads are not rotated
   #pragma unroll
           for (int i = 0; i < 16; ++i) {
@@ -405,8 +454,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
         }
       } else {
   #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const int fa0 = f0 + m * 32;
+        for (int m = 0; m < FM; ++m) {
+          const int fa0 = f0 + m * MROW;
           if (fa0 >= rope_end) continue;
   #pragma unroll
           for (int i = 0; i < 16; i += 2) {
@@ -421,8 +470,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
       }
 
   #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int fm = f0 + m * 32;
+      for (int m = 0; m < FM; ++m) {
+        const int fm = f0 + m * MROW;
         if (fm >= a.O) continue;             // uniform for the wave
         uint16_t* dst;
         if (fm < q_end)
@@ -503,9 +552,12 @@ static ct_status launch_gemm(Kernel kernel, int threads, const GemmArgs& a, cons
 template <int EPI, int D, int STYLE, int NB>
 static ct_status launch_variant(const GemmArgs& a, const RopeTable& rope, const ChunkTable& tab, KernelClass kc,
                                 hipStream_t s) {
-  // Eight waves.  Four (one per SIMD, 128 x 128 wave tiles, half the LDS reads per MFMA) compile
-  // from the same source and were measured: no faster on any layer shape.
-  return launch_gemm(gemm_kernel<EPI, D, STYLE, NB, 8>, 512, a, rope, tab, kc, s);
+  // Eight waves, or four (one per SIMD, 128 x 128 wave tiles), which read a third less from LDS per MFMA
+  // and so leave the power-limited clock higher, but run an epilogue with less overlap.  Four for
+  // 256-token tiles (K = 4096, n = 4915: gate/up 903 us, 936 us with eight; down projection 465 and 501)
+  // unless the rotation is in the epilogue (QKV at n = 4915: 218 us with four, 214 with eight).
+  constexpr int NW = NB == 2 && EPI != EPI_QKV_ROPE ? 4 : 8;
+  return launch_gemm(gemm_kernel<EPI, D, STYLE, NB, NW>, 64 * NW, a, rope, tab, kc, s);
 }
 
 ct_status launch_qkv(const ct_layer_cfg* cfg, const void* hidden, const int32_t* hidden_rows, const int32_t* sel_pos,
