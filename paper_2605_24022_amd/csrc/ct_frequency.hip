@@ -5,12 +5,9 @@
 // of 2*CP adjacent columns and all N tokens: two real columns ride as the real and imaginary
 // part of one complex sequence (the mask is symmetric in +-frequency, so it commutes with that
 // packing), which leaves CP complex sequences of length N.  They live in LDS for the whole
-// transform; every pass is a Stockham (auto-sorting) radix-R step with R in {16, 8, 5, 4, 3, 2}:
-// each thread pulls the R inputs of its butterflies into registers, the workgroup meets at a
-// barrier, and the thread writes its R outputs to their natural-order places, so one LDS array
-// serves as source and destination.  After the inverse passes the squared magnitudes of a
-// token's row are summed over the strip (Eq. 5 needs the norm over all heads and dims) and
-// accumulated over the strips a workgroup owns; a second small kernel adds the workgroups'
+// transform, in place (see below).  After the inverse passes the squared magnitudes of a
+// token's row are summed over the strip (Eq. 5 needs the norm over all heads and dims);
+// a second small kernel adds the strips'
 // partial sums in a fixed order, so the scores are reproducible bit for bit.
 //
 // Sequences longer than kFreqMaxTokens do not fit one workgroup's LDS: their transform is split as
@@ -34,17 +31,6 @@ namespace ct {
 constexpr int kFreqThreads = 1024;
 constexpr int kFreqMaxElems = 16384;   // complex values of a strip held in LDS (16 per thread)
 constexpr int kFreqMaxTokens = 4096;
-
-struct FftPlan {
-  int32_t n;          // tokens
-  int32_t lg_cp;      // log2 of the complex sequences per strip
-  int32_t n_pass;
-  int32_t radix[12];
-  int32_t cutoff;     // bins k with min(k, n - k) >= cutoff are zeroed
-  int32_t strips;     // strips per tensor = row_elems / (2 CP)
-  int32_t groups;     // workgroups per tensor; workgroup g owns strips g * (strips / groups) ... in order
-  int cp() const { return 1 << lg_cp; }
-};
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
   return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -139,122 +125,12 @@ __device__ __forceinline__ void dft<8>(float2 (&v)[8], float sgn) { dft_by4<2>(v
 template <>
 __device__ __forceinline__ void dft<16>(float2 (&v)[16], float sgn) { dft_by4<4>(v, sgn); }
 
-// Place of element (token or bin n, sequence c) in LDS: one spare row per 16 rows keeps the
-// first pass's strided writes off a common bank.
-__device__ __forceinline__ int phys(int n, int c, int lg_cp) { return ((n + (n >> 4)) << lg_cp) + c; }
-
-// One Stockham pass of radix R over all CP sequences.  ns = product of the radices of the
-// passes before this one.  tw[t] = exp(-2 pi i t / n) for t < n / 2.
-// N_CT > 0: the length (a power of two, with CP = kFreqMaxElems / N sequences per strip) and ns are known
-// at compile time, which turns the index arithmetic into shifts and immediate offsets; N_CT = 0
-// takes them at run time.
-template <int R, int N_CT, int NS_CT>
-__device__ __forceinline__ void stockham_pass(float2* data, const float2* tw, int n_rt, int lg_cp_rt, int ns_rt,
-                                              float sgn) {
-  constexpr bool FIXED = N_CT > 0;
-  constexpr int ITER = (kFreqMaxElems / kFreqThreads + R - 1) / R;
-  const int n = FIXED ? N_CT : n_rt;
-  const int lg_cp = FIXED ? __builtin_ctz(kFreqMaxElems / (FIXED ? N_CT : 1)) : lg_cp_rt;
-  const int ns = FIXED ? NS_CT : ns_rt;
-  const int m = n / R;                 // butterflies per sequence
-  const int nb = m << lg_cp;
-  const int cmask = (1 << lg_cp) - 1;
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));        // addresses are computed here, not hoisted out of the strip loop
-  float2 v[ITER][R];
-#pragma unroll
-  for (int i = 0; i < ITER; ++i) {
-    const int b = tid + i * kFreqThreads;
-    if (FIXED || b < nb) {
-      const int j = b >> lg_cp, c = b & cmask;
-      if (FIXED && (N_CT / R) % 16 == 0) {      // the stride is whole groups of 16 rows: constant offsets
-        const float2* src = data + phys(j, c, lg_cp);
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[i][r] = src[(r * (m + m / 16)) << lg_cp];
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[i][r] = data[phys(j + r * m, c, lg_cp)];
-      }
-    }
-  }
-  __syncthreads();
-  const int tstep = n / (ns * R);
-#pragma unroll
-  for (int i = 0; i < ITER; ++i) {
-    const int b = tid + i * kFreqThreads;
-    if (FIXED || b < nb) {
-      const int j = b >> lg_cp, c = b & cmask;
-      const int hi = j / ns, k = j - hi * ns;
-      if (ns > 1) {
-        float2 w1 = tw[k * tstep];
-        w1.y *= -sgn;                 // the table holds the forward (sgn = -1) twiddles
-        float2 cur = w1, pw = w1;     // cur = w1^r; restarted from a repeated square at every power of two
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-          if (r > 1) {
-            if ((r & (r - 1)) == 0) {
-              pw = cmul(pw, pw);
-              cur = pw;
-            } else {
-              cur = cmul(cur, w1);
-            }
-          }
-          v[i][r] = cmul(v[i][r], cur);
-        }
-      }
-      dft<R>(v[i], sgn);
-      const int j0 = hi * ns * R + k;
-      if (FIXED && (NS_CT % 16 == 0 || (NS_CT == 1 && 16 % R == 0))) {
-        // rows j0 + r ns: whole groups of 16 rows apart, or (ns = 1) inside one group
-        float2* dst = data + phys(j0, c, lg_cp);
-        const int stride = NS_CT == 1 ? 1 : ns + ns / 16;
-#pragma unroll
-        for (int r = 0; r < R; ++r) dst[(r * stride) << lg_cp] = v[i][r];
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) data[phys(j0 + r * ns, c, lg_cp)] = v[i][r];
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Run-time plan: any length of the form 2^a 3^b 5^c.
-__device__ __forceinline__ void transform(float2* data, const float2* tw, const FftPlan& p, int n, int lg_cp,
-                                          float sgn) {
-  int ns = 1;
-  for (int s = 0; s < p.n_pass; ++s) {
-    const int r = p.radix[s];
-    asm volatile("" : "+s"(n), "+s"(lg_cp));
-    switch (r) {
-      case 16: stockham_pass<16, 0, 0>(data, tw, n, lg_cp, ns, sgn); break;
-      case 8: stockham_pass<8, 0, 0>(data, tw, n, lg_cp, ns, sgn); break;
-      case 5: stockham_pass<5, 0, 0>(data, tw, n, lg_cp, ns, sgn); break;
-      case 4: stockham_pass<4, 0, 0>(data, tw, n, lg_cp, ns, sgn); break;
-      case 3: stockham_pass<3, 0, 0>(data, tw, n, lg_cp, ns, sgn); break;
-      default: stockham_pass<2, 0, 0>(data, tw, n, lg_cp, ns, sgn); break;
-    }
-    ns *= r;
-  }
-}
-
-// Compile-time plans for the power-of-two lengths 256 ... 4096 (three passes at most).
-template <int N>
-__device__ __forceinline__ void transform_fixed(float2* data, const float2* tw, float sgn) {
-  constexpr int R0 = N == 512 ? 8 : 16;
-  constexpr int R1 = (N == 512 || N == 1024) ? 8 : 16;
-  constexpr int R2 = N / (R0 * R1);     // 1 (N = 256), 8 or 16
-  stockham_pass<R0, N, 1>(data, tw, 0, 0, 0, sgn);
-  stockham_pass<R1, N, R0>(data, tw, 0, 0, 0, sgn);
-  if constexpr (R2 > 1) stockham_pass<R2, N, R0 * R1>(data, tw, 0, 0, 0, sgn);
-}
-
 // ---- power-of-two lengths 256 ... 4096: plan compiled in ----------------------------------------
 // A forward transform by decimation in frequency leaves its bins in digit-reversed order, and an
 // inverse by decimation in time takes them in that order, so nothing is ever reordered: every pass
 // reads and writes the same places, each owned by one thread, and the last forward pass, the mask of
 // Eq. 3 and the first inverse pass are one step in registers, as are the global load with the first
-// pass and the squares with the last.  A strip crosses LDS four times with four barriers (Stockham
+// pass and the squares with the last.  A strip crosses LDS four times with four barriers (sorting Stockham
 // passes in both directions: eight crossings, sixteen barriers).
 // N = 16 x 16 x MID (N = 256: 16 x 16), 16 elements per thread and pass, bin = k0 + 16 k1 + 256 k2 in row
 // k0 N/16 + k1 MID + k2.  A thread's first twiddles do not depend on the strip: they are taken once
@@ -336,7 +212,7 @@ struct FixedPlan {
 template <int N>
 __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                                   int64_t batch_stride, int32_t row_elems, int32_t n_work,
-                                                                  FftPlan p, float* __restrict__ partial) {
+                                                                  int32_t groups, int32_t cutoff, float* __restrict__ partial) {
   using P = FixedPlan<N>;
   constexpr int CP = P::CP, MID = P::MID, M0 = P::M0, M1 = P::M1, T = kFreqThreads;
   extern __shared__ float2 data[];
@@ -359,12 +235,12 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
   __syncthreads();
   const float2* const w1 = tab1 + (u % M1) * 17;
 
-  const int gone_first = p.cutoff, gone_last = p.cutoff == 0 ? N - 1 : N - p.cutoff;   // Eq. 3: these bins go
+  const int gone_first = cutoff, gone_last = cutoff == 0 ? N - 1 : N - cutoff;   // Eq. 3: these bins go
   const uint32_t gone = gone_last >= gone_first ? gone_last - gone_first + 1 : 0;
   // workgroups that share 128-byte lines of the rows (adjacent strips) are given ids that differ
   // by 8, which puts them on the same XCD (and its L2) at the same time
   constexpr int per_line = CP >= 32 ? 1 : 32 / CP;
-  const bool swizzled = n_work % (8 * per_line) == 0 && p.groups % per_line == 0 && gridDim.x % 8 == 0;
+  const bool swizzled = n_work % (8 * per_line) == 0 && groups % per_line == 0 && gridDim.x % 8 == 0;
 
   // strip number `it` of this launch -> tensor (batch * 2 + kv) and strip of it
   auto strip_of = [&](int it, int& strip) __attribute__((always_inline)) -> int {
@@ -373,8 +249,8 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
       const int xcd = w & 7, slot = w >> 3;
       w = (slot / per_line) * (8 * per_line) + xcd * per_line + slot % per_line;
     }
-    const int tensor = w / p.groups;
-    strip = w - tensor * p.groups;
+    const int tensor = w / groups;
+    strip = w - tensor * groups;
     return tensor;
   };
   const uint32_t lane_off = (uint32_t)u * (row_elems / 2) + c;
@@ -442,7 +318,7 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
     const int first = reduce_scatter16<CP>(e, c);
     int strip;
     const int tensor = strip_of(it, strip);
-    float* out = partial + ((int64_t)tensor * p.groups + strip) * N + u;
+    float* out = partial + ((int64_t)tensor * groups + strip) * N + u;
     if (CP <= 16 || c < 16) {
 #pragma unroll
       for (int j = 0; j < (CP >= 16 ? 1 : 16 / CP); ++j) out[(first + j) * M0] = e[j];
@@ -450,219 +326,487 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
   }
 }
 
-// partial[((b * 2 + kv) * groups + g) * n + token] = sum over the workgroup's strips of
-// |N x~|^2 (the 1/N of the inverse transform is applied by the finishing kernel).
-template <int N_CT>
-__global__ __launch_bounds__(kFreqThreads) void freq_energy_kernel(const uint16_t* __restrict__ k,
-                                                                   const uint16_t* __restrict__ v,
-                                                                   int64_t batch_stride, int32_t row_elems, int32_t n_work,
-                                                                   FftPlan p, float* __restrict__ partial) {
-  extern __shared__ float2 lds[];
-  int n = N_CT > 0 ? N_CT : p.n, lg_cp = N_CT > 0 ? __builtin_ctz(kFreqMaxElems / (N_CT > 0 ? N_CT : 1)) : p.lg_cp;
-  const int cp = 1 << lg_cp;
-  float2* data = lds;
-  float2* tw = lds + ((n + (n >> 4) + 1) << lg_cp);
-  // workgroups that share 128-byte lines of the rows (adjacent strips) are given ids that differ
-  // by 8, which puts them on the same XCD (and its L2) in the same wave of launches
-  int w = blockIdx.x;
-  const int own = p.strips / p.groups;                       // strips per workgroup
-  const int per_line = cp * own >= 32 ? 1 : 32 / (cp * own);
-  if (n_work % (8 * per_line) == 0 && p.groups % per_line == 0) {
-    const int xcd = w & 7, slot = w >> 3;
-    w = (slot / per_line) * (8 * per_line) + xcd * per_line + slot % per_line;
-  }
-  const int tensor = w / p.groups, g = w - tensor * p.groups;   // tensor = batch * 2 + kv
-  const uint16_t* src = ((tensor & 1) ? v : k) + (int64_t)(tensor >> 1) * batch_stride;
+// ---- other lengths: the same in-place transforms with the plan taken at run time -----------------
+// N = R0 R1 R2 with radices up to 27, which reaches every 2^a 3^b 5^c up to 4096; bin = k0 + R0 k1 + R0 R1 k2
+// in row (k0 R1 + k1) R2 + k2.  Blocks of R2 rows are `pitch` apart (one spare row when R2 is even and
+// sequences are few), so that the middle pass's accesses fall on distinct banks.
+struct MixPlan {
+  int32_t n, lg_cp, r0, r1, r2, pitch;
+  uint32_t mg1, mg2;       // floor(2^32 / r1) + 1 and the same of r2: quotients by multiplication
+  int32_t cutoff;
+  __host__ __device__ int rows() const { return r0 * r1 * pitch; }
+  __host__ __device__ int tables() const { return 5 * (r1 * r2 + r2); }      // twiddles of the first two stages, powers 1, 2, 4, 8, 16
+  size_t lds_bytes(int extra) const { return (((size_t)rows() << lg_cp) + tables() + extra) * sizeof(float2); }
+};
 
-  // only radices 8 and 16 occur in the compiled-in plans, so their first-power twiddles stop at n / 8
-  const int tw_len = N_CT > 0 ? N_CT / 8 : (n + 1) / 2;
-  for (int t = threadIdx.x; t < tw_len; t += kFreqThreads) {
-    float s, c;
-    const float turns = (float)t / (float)n;           // in [0, 1/2)
-    sincospif(-2.f * turns, &s, &c);
-    tw[t] = make_float2(c, s);
-  }
-  const int elems = n << lg_cp;
-  constexpr int PER = kFreqMaxElems / kFreqThreads;
-  // energy of the rows this thread owns (rows tid, tid + kFreqThreads, ...), summed over the strips
-  constexpr int ROWS = kFreqMaxTokens / kFreqThreads;
-  float acc[ROWS];
+// R = R1 R2 with coprime factors (Good-Thomas: index maps instead of twiddles): input
+// n = (R2 n1 + R1 n2) mod R, output k with k = k1 mod R1 and k = k2 mod R2.
+template <int R1, int R2>
+__device__ __forceinline__ void dft_coprime(float2 (&v)[R1 * R2], float sgn) {
+  constexpr int R = R1 * R2;
+  float2 y[R1][R2];
 #pragma unroll
-  for (int i = 0; i < ROWS; ++i) acc[i] = 0.f;
+  for (int n2 = 0; n2 < R2; ++n2) {
+    float2 col[R1];
+#pragma unroll
+    for (int n1 = 0; n1 < R1; ++n1) col[n1] = v[(R2 * n1 + R1 * n2) % R];
+    dft<R1>(col, sgn);
+#pragma unroll
+    for (int k1 = 0; k1 < R1; ++k1) y[k1][n2] = col[k1];
+  }
+  // with n = R2 n1 + R1 n2 the kernel is exp(i 2 pi (n1 k1 / R1 + n2 k2 / R2)), k1 = k mod R1, k2 = k mod R2
+#pragma unroll
+  for (int k1 = 0; k1 < R1; ++k1) dft<R2>(y[k1], sgn);
+#pragma unroll
+  for (int k = 0; k < R; ++k) v[k] = y[k % R1][k % R2];
+}
+template <> __device__ __forceinline__ void dft<6>(float2 (&v)[6], float sgn) { dft_coprime<2, 3>(v, sgn); }
+template <> __device__ __forceinline__ void dft<10>(float2 (&v)[10], float sgn) { dft_coprime<2, 5>(v, sgn); }
+template <> __device__ __forceinline__ void dft<12>(float2 (&v)[12], float sgn) { dft_coprime<4, 3>(v, sgn); }
+template <> __device__ __forceinline__ void dft<15>(float2 (&v)[15], float sgn) { dft_coprime<3, 5>(v, sgn); }
+// exp(2 pi i m / R), m constant after unrolling
+template <int R>
+__device__ __forceinline__ float2 root(int m, float sgn);
+template <>
+__device__ __forceinline__ float2 root<9>(int m, float sgn) {
+  constexpr float co[9] = {1.f, 0.766044443f, 0.173648178f, -0.5f, -0.939692621f, -0.939692621f, -0.5f, 0.173648178f, 0.766044443f};
+  constexpr float si[9] = {0.f, 0.64278761f, 0.984807753f, 0.866025404f, 0.342020143f, -0.342020143f, -0.866025404f, -0.984807753f,
+      -0.64278761f};
+  return make_float2(co[m], sgn * si[m]);
+}
+template <>
+__device__ __forceinline__ float2 root<25>(int m, float sgn) {
+  constexpr float co[25] = {1.f, 0.968583161f, 0.87630668f, 0.728968627f, 0.535826795f, 0.309016994f, 0.0627905195f, -0.187381315f,
+      -0.425779292f, -0.63742399f, -0.809016994f, -0.929776486f, -0.992114701f, -0.992114701f, -0.929776486f,
+      -0.809016994f, -0.63742399f, -0.425779292f, -0.187381315f, 0.0627905195f, 0.309016994f, 0.535826795f,
+      0.728968627f, 0.87630668f, 0.968583161f};
+  constexpr float si[25] = {0.f, 0.248689887f, 0.481753674f, 0.684547106f, 0.844327926f, 0.951056516f, 0.998026728f, 0.982287251f,
+      0.904827052f, 0.770513243f, 0.587785252f, 0.368124553f, 0.125333234f, -0.125333234f, -0.368124553f,
+      -0.587785252f, -0.770513243f, -0.904827052f, -0.982287251f, -0.998026728f, -0.951056516f, -0.844327926f,
+      -0.684547106f, -0.481753674f, -0.248689887f};
+  return make_float2(co[m], sgn * si[m]);
+}
+template <>
+__device__ __forceinline__ float2 root<27>(int m, float sgn) {
+  constexpr float co[27] = {1.f, 0.973044871f, 0.89363264f, 0.766044443f, 0.597158592f, 0.396079766f, 0.173648178f, -0.0581448289f,
+      -0.286803233f, -0.5f, -0.686241638f, -0.835487811f, -0.939692621f, -0.993238358f, -0.993238358f,
+      -0.939692621f, -0.835487811f, -0.686241638f, -0.5f, -0.286803233f, -0.0581448289f, 0.173648178f, 0.396079766f,
+      0.597158592f, 0.766044443f, 0.89363264f, 0.973044871f};
+  constexpr float si[27] = {0.f, 0.230615871f, 0.44879918f, 0.64278761f, 0.802123193f, 0.918216107f, 0.984807753f, 0.998308158f,
+      0.957989512f, 0.866025404f, 0.727373642f, 0.549508978f, 0.342020143f, 0.116092914f, -0.116092914f,
+      -0.342020143f, -0.549508978f, -0.727373642f, -0.866025404f, -0.957989512f, -0.998308158f, -0.984807753f,
+      -0.918216107f, -0.802123193f, -0.64278761f, -0.44879918f, -0.230615871f};
+  return make_float2(co[m], sgn * si[m]);
+}
+// R = R1 R2, input n = R2 n1 + n2, output k = k1 + R1 k2, twiddles exp(sgn 2 pi i n2 k1 / R)
+template <int R1, int R2>
+__device__ __forceinline__ void dft_split(float2 (&v)[R1 * R2], float sgn) {
+  float2 y[R1][R2];
+#pragma unroll
+  for (int n2 = 0; n2 < R2; ++n2) {
+    float2 col[R1];
+#pragma unroll
+    for (int n1 = 0; n1 < R1; ++n1) col[n1] = v[R2 * n1 + n2];
+    dft<R1>(col, sgn);
+#pragma unroll
+    for (int k1 = 0; k1 < R1; ++k1) y[k1][n2] = n2 * k1 == 0 ? col[k1] : cmul(col[k1], root<R1 * R2>(n2 * k1, sgn));
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < R1; ++k1) {
+    dft<R2>(y[k1], sgn);
+#pragma unroll
+    for (int k2 = 0; k2 < R2; ++k2) v[k1 + R1 * k2] = y[k1][k2];
+  }
+}
+template <> __device__ __forceinline__ void dft<1>(float2 (&)[1], float) {}
+template <> __device__ __forceinline__ void dft<9>(float2 (&v)[9], float sgn) { dft_split<3, 3>(v, sgn); }
+template <> __device__ __forceinline__ void dft<18>(float2 (&v)[18], float sgn) { dft_coprime<2, 9>(v, sgn); }
+template <> __device__ __forceinline__ void dft<25>(float2 (&v)[25], float sgn) { dft_split<5, 5>(v, sgn); }
+template <> __device__ __forceinline__ void dft<27>(float2 (&v)[27], float sgn) { dft_split<3, 9>(v, sgn); }
 
-  for (int strip = g * own; strip < (g + 1) * own; ++strip) {
-    // the sizes are made opaque once per strip, and once more before each stage, so that the
-    // addresses of every stage are computed where they are used instead of being hoisted out of
-    // the loop together (which overflows the 128 registers a 1024-thread workgroup leaves a lane)
-    if (N_CT == 0) asm volatile("" : "+s"(n), "+s"(lg_cp));
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    const uint32_t* base = reinterpret_cast<const uint32_t*>(src) + (int64_t)strip * cp;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = tid + i * kFreqThreads;
-      if (e < elems) {
-        const int row = e >> lg_cp, c = e & (cp - 1);
-        const uint32_t pair = __builtin_nontemporal_load(base + (int64_t)row * (row_elems / 2) + c);
-        data[phys(row, c, lg_cp)] = make_float2(bf16_lo(pair), bf16_hi(pair));
-      }
-    }
-    __syncthreads();
-    if constexpr (N_CT > 0) {
-      transform_fixed<N_CT>(data, tw, -1.f);
-    } else {
-      asm volatile("" : "+s"(n), "+s"(lg_cp));
-      transform(data, tw, p, n, lg_cp, -1.f);
-      asm volatile("" : "+s"(n), "+s"(lg_cp));
-    }
-    // Eq. 3: bins from the cutoff on (and their mirror images) are zeroed
-    {
-      const int first = p.cutoff, last = p.cutoff == 0 ? n - 1 : n - p.cutoff;   // bins first..last go
-      const int gone = last >= first ? last - first + 1 : 0;
-      for (int e = threadIdx.x; e < (gone << lg_cp); e += kFreqThreads) {
-        const int bin = first + (e >> lg_cp), c = e & (cp - 1);
-        data[phys(bin, c, lg_cp)] = make_float2(0.f, 0.f);
-      }
-    }
-    __syncthreads();
-    if constexpr (N_CT > 0) {
-      transform_fixed<N_CT>(data, tw, 1.f);
-    } else {
-      asm volatile("" : "+s"(n), "+s"(lg_cp));
-      transform(data, tw, p, n, lg_cp, 1.f);
-      asm volatile("" : "+s"(n), "+s"(lg_cp));
-    }
-    asm volatile("" : "+v"(tid));
-    // Eq. 5: each thread adds up the squares of whole rows (all CP sequences of a token), the
-    // sequences visited in an order rotated by the lane so that neighbours start on other banks
-#pragma unroll
-    for (int i = 0; i < ROWS; ++i) {
-      const int row = tid + i * kFreqThreads;
-      if (row < n) {
-        const float2* line = data + phys(row, 0, lg_cp);
-        float sq = 0.f;
-        for (int q = 0; q < cp; ++q) {
-          const float2 x = line[(q + tid) & (cp - 1)];
-          sq = fmaf(x.x, x.x, fmaf(x.y, x.y, sq));
-        }
-        acc[i] += sq;
-      }
-    }
-    __syncthreads();
+template <int R> struct Radix { static constexpr int value = R; };
+template <class F>
+__device__ __forceinline__ void by_radix(int r, F&& f) {
+  switch (r) {
+    case 27: f(Radix<27>{}); break;
+    case 25: f(Radix<25>{}); break;
+    case 18: f(Radix<18>{}); break;
+    case 16: f(Radix<16>{}); break;
+    case 15: f(Radix<15>{}); break;
+    case 12: f(Radix<12>{}); break;
+    case 10: f(Radix<10>{}); break;
+    case 9: f(Radix<9>{}); break;
+    case 8: f(Radix<8>{}); break;
+    case 6: f(Radix<6>{}); break;
+    case 5: f(Radix<5>{}); break;
+    case 4: f(Radix<4>{}); break;
+    case 3: f(Radix<3>{}); break;
+    case 2: f(Radix<2>{}); break;
+    default: f(Radix<1>{}); break;
   }
-  float* out = partial + ((int64_t)tensor * p.groups + g) * n;
+}
+// The thread's number, opaque: what a pass derives from it is computed there instead of being hoisted out of the
+// loop over the strips, together for every radix of every pass (which overflows the registers).
+__device__ __forceinline__ int pass_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+__device__ __forceinline__ int quotient(int x, int d, uint32_t magic) { return d == 1 ? x : (int)__umulhi((uint32_t)x, magic); }
+
+// v[r] *= w^r (conjugated: SGN = -1), the powers 1, 2, 4, 8 and 16 of w from a table, `stride` apart, the others as
+// products of at most five of those: a power taken by repeated products of w alone carries r times the rounding
+// of w (scores of 4 x 1500 x 1024 were off by 4.4e-7 that way, 2-norm; so: 0.9e-7).
+template <int R, int SGN>
+__device__ __forceinline__ void times_powers(float2 (&v)[R], const float2* w, int stride) {
+  auto base = [&](int k) __attribute__((always_inline)) {
+    const float2 x = w[k * stride];
+    return make_float2(x.x, SGN * x.y);
+  };
+  // pre[k]: product of the bits of r from bit k on
+  float2 b[5], pre[5];
 #pragma unroll
-  for (int i = 0; i < ROWS; ++i) {
-    const int row = threadIdx.x + i * kFreqThreads;
-    if (row < n) out[row] = acc[i];
+  for (int k = 0; k < 5; ++k)
+    if ((1 << k) < R) b[k] = base(k);
+#pragma unroll
+  for (int r = 1; r < R; ++r) {
+#pragma unroll
+    for (int k = 4; k >= 0; --k) {
+      if ((r & ((1 << k) - 1)) != 0 && k > 0) continue;     // pre[k] stands since r last was a multiple of 2^k
+      const bool above = (r >> (k + 1)) != 0, bit = (r >> k) & 1;
+      if (bit) pre[k] = above ? cmul(pre[k + 1], b[k]) : b[k];
+      else if (above) pre[k] = pre[k + 1];
+    }
+    v[r] = cmul(v[r], pre[0]);
+  }
+}
+
+// exp(-2 pi i u 2^k / n) for u < R1 R2 at tw[k R1 R2 + u], and behind them exp(-2 pi i u 2^k / (R1 R2)) for
+// u < R2 at [k R2 + u], k < 5
+__device__ __forceinline__ void mix_tables(float2* tw, const MixPlan& p, int threads) {
+  const int m0 = p.r1 * p.r2;
+  for (int t = threadIdx.x; t < 5 * (m0 + p.r2); t += threads) {
+    const bool second = t >= 5 * m0;
+    const int x = second ? t - 5 * m0 : t, m = second ? p.r2 : m0, len = second ? m0 : p.n;
+    const int k = x / m, u = x - k * m;
+    double s, c;
+    sincospi(-2.0 * (double)((u << k) % len) / (double)len, &s, &c);
+    tw[t] = make_float2((float)c, (float)s);
+  }
+}
+
+// The passes.  A butterfly is (place, sequence c); `fn` bodies see registers only.
+// First stage: rows u + i R1 R2 (i < R0), u = b1 R2 + r2, in LDS at ((i R1 + b1) pitch + r2).
+template <int R, int T, class Load>
+__device__ __forceinline__ void mix_first(float2* data, const float2* tw, const MixPlan& p, Load&& load) {
+  const int m0 = p.r1 * p.r2, nb = m0 << p.lg_cp, step = (p.r1 * p.pitch) << p.lg_cp;
+  constexpr int ITER = (kFreqMaxElems / kFreqThreads + R - 1) / R;   // 16 elements per thread at most
+  const int tid = pass_thread();
+#pragma unroll
+  for (int it = 0; it < ITER; ++it) {
+    const int b = tid + it * T;
+    if (b < nb) {
+      const int u = b >> p.lg_cp, c = b & ((1 << p.lg_cp) - 1);
+      float2 v[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) v[i] = load(it * R + i, u + i * m0, c);
+      dft<R>(v, -1.f);
+      times_powers<R, 1>(v, tw + u, m0);
+      const int b1 = quotient(u, p.r2, p.mg2);
+      float2* d = data + ((b1 * p.pitch + u - b1 * p.r2) << p.lg_cp) + c;
+#pragma unroll
+      for (int i = 0; i < R; ++i) d[i * step] = v[i];
+    }
+  }
+}
+// Its inverse: `store(i, row, c, value)` takes the results.
+template <int R, int T, class Done>
+__device__ __forceinline__ void mix_last(const float2* data, const float2* tw, const MixPlan& p, Done&& done) {
+  const int m0 = p.r1 * p.r2, nb = m0 << p.lg_cp, step = (p.r1 * p.pitch) << p.lg_cp;
+  for (int b = pass_thread(); b < nb; b += T) {
+    const int u = b >> p.lg_cp, c = b & ((1 << p.lg_cp) - 1);
+    const int b1 = quotient(u, p.r2, p.mg2);
+    const float2* d = data + ((b1 * p.pitch + u - b1 * p.r2) << p.lg_cp) + c;
+    float2 v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = d[i * step];
+    times_powers<R, -1>(v, tw + u, m0);
+    dft<R>(v, 1.f);
+    done(v, u, m0, c);
+  }
+}
+// Second stage and its inverse, in place: rows (a R1 + i) R2 + r2 (i < R1).
+template <int R, int T, bool INV>
+__device__ __forceinline__ void mix_second(float2* data, const float2* tw1, const MixPlan& p) {
+  const int nb = (p.r0 * p.r2) << p.lg_cp, step = p.pitch << p.lg_cp;
+  for (int b = pass_thread(); b < nb; b += T) {
+    const int j = b >> p.lg_cp, c = b & ((1 << p.lg_cp) - 1);
+    const int a = quotient(j, p.r2, p.mg2), r = j - a * p.r2;
+    float2* d = data + ((a * R * p.pitch + r) << p.lg_cp) + c;
+    float2 v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = d[i * step];
+    if (INV) {
+      times_powers<R, -1>(v, tw1 + r, p.r2);
+      dft<R>(v, 1.f);
+    } else {
+      dft<R>(v, -1.f);
+      times_powers<R, 1>(v, tw1 + r, p.r2);
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) d[i * step] = v[i];
+  }
+}
+// Third stage: rows j R2 + i (i < R2), j = k0 R1 + k1, bins bin0 + i R0 R1 with bin0 = k0 + R0 k1.
+// `mid(v, bin0, bin_step, c, place)` does what belongs between the two transforms, from and to registers;
+// LOAD / STORE: the values come from, and go back to, LDS.
+template <int R, int T, bool LOAD, bool STORE, class Mid>
+__device__ __forceinline__ void mix_third(float2* data, const MixPlan& p, Mid&& mid) {
+  const int nb = (p.r0 * p.r1) << p.lg_cp;
+  for (int b = pass_thread(); b < nb; b += T) {
+    const int j = b >> p.lg_cp, c = b & ((1 << p.lg_cp) - 1);
+    const int k0 = quotient(j, p.r1, p.mg1), k1 = j - k0 * p.r1;
+    float2* d = data + ((j * p.pitch) << p.lg_cp) + c;
+    float2 v[R];
+    if (LOAD) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) v[i] = d[i << p.lg_cp];
+      dft<R>(v, -1.f);
+    }
+    mid(v, k0 + p.r0 * k1, p.r0 * p.r1, c);
+    if (STORE) {
+      dft<R>(v, 1.f);
+#pragma unroll
+      for (int i = 0; i < R; ++i) d[i << p.lg_cp] = v[i];
+    }
+  }
+}
+
+// x + (x of the other lanes of its group of 2^lg adjacent lanes); every lane gets the sum
+__device__ __forceinline__ float group_sum(float x, int lg) {
+  if (lg > 0) x = add_dpp<kDppXor1>(x, x);
+  if (lg > 1) x = add_dpp<kDppXor2>(x, x);
+  if (lg > 2) x = add_dpp<kDppHalfMirror>(x, x);
+  if (lg > 3) x = add_dpp<kDppMirror>(x, x);
+  if (lg > 4) x += __shfl_xor(x, 16);
+  if (lg > 5) x += __shfl_xor(x, 32);
+  return x;
+}
+// Eq. 5 for the rows of a last-stage butterfly: squares summed over the strip's sequences, written (or added) once per row.
+template <int R>
+__device__ __forceinline__ void write_energy(const float2 (&v)[R], int lg, int c, float* out, int64_t step, bool add) {
+  const int cmask = (1 << lg) - 1;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const float e = group_sum(fmaf(v[i].x, v[i].x, v[i].y * v[i].y), lg);
+    if (c == (i & cmask)) out[i * step] = add ? out[i * step] + e : e;
+  }
+}
+
+// Sequences that fit: as freq_fixed_kernel, a persistent workgroup per compute unit.  Bound by vector instructions
+// and LDS accesses.  K and V, against sorting Stockham passes (one per radix up to 16, two barriers each):
+// 4 x 1500 x 1024 75 -> 35 us, 4 x 3072 x 1024 158 -> 80 us, 4 x 4050 x 1000 303 -> 144 us; errors are smaller.
+__global__ __launch_bounds__(kFreqThreads) void freq_mixed_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                                                                  int64_t batch_stride, int32_t row_elems, int32_t n_work,
+                                                                  int32_t groups, MixPlan p, float* __restrict__ partial) {
+  constexpr int T = kFreqThreads;
+  extern __shared__ float2 data[];
+  float2* const tw = data + ((size_t)p.rows() << p.lg_cp);
+  const float2* const tw1 = tw + 5 * p.r1 * p.r2;   // (no restrict: written by mix_tables below)
+  mix_tables(tw, p, T);
+  __syncthreads();
+  const int cp = 1 << p.lg_cp, width = row_elems / 2, n = p.n;
+  const int gone_first = p.cutoff, gone_last = p.cutoff == 0 ? n - 1 : n - p.cutoff;   // Eq. 3: these bins go
+  const uint32_t gone = gone_last >= gone_first ? gone_last - gone_first + 1 : 0;
+  const int per_line = cp >= 32 ? 1 : 32 / cp;      // strips that share 128-byte lines: see freq_fixed_kernel
+  const bool swizzled = n_work % (8 * per_line) == 0 && groups % per_line == 0 && gridDim.x % 8 == 0;
+  auto strip_of = [&](int it, int& strip) __attribute__((always_inline)) -> int {
+    int w = it;
+    if (swizzled) {
+      const int xcd = w & 7, slot = w >> 3;
+      w = (slot / per_line) * (8 * per_line) + xcd * per_line + slot % per_line;
+    }
+    const int tensor = w / groups;
+    strip = w - tensor * groups;
+    return tensor;
+  };
+  for (int it = blockIdx.x; it < n_work; it += gridDim.x) {
+    int strip;
+    const int tensor = strip_of(it, strip);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(((tensor & 1) ? v : k) + (int64_t)(tensor >> 1) * batch_stride) + ((int64_t)strip << p.lg_cp);
+    by_radix(p.r0, [&](auto r) __attribute__((always_inline)) {
+      mix_first<decltype(r)::value, T>(data, tw, p, [&](int, int row, int c) __attribute__((always_inline)) {
+        const uint32_t pair = __builtin_nontemporal_load(src + (int64_t)row * width + c);
+        return make_float2(bf16_lo(pair), bf16_hi(pair));
+      });
+    });
+    __syncthreads();
+    if (p.r1 > 1) {
+      by_radix(p.r1, [&](auto r) __attribute__((always_inline)) { mix_second<decltype(r)::value, T, false>(data, tw1, p); });
+      __syncthreads();
+    }
+    by_radix(p.r2, [&](auto r) __attribute__((always_inline)) {
+      constexpr int R = decltype(r)::value;
+      mix_third<R, T, true, true>(data, p, [&](float2 (&y)[R], int bin0, int step, int) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+          if ((uint32_t)(bin0 + step * i - gone_first) < gone) y[i] = make_float2(0.f, 0.f);
+      });
+    });
+    __syncthreads();
+    if (p.r1 > 1) {
+      by_radix(p.r1, [&](auto r) __attribute__((always_inline)) { mix_second<decltype(r)::value, T, true>(data, tw1, p); });
+      __syncthreads();
+    }
+    float* out = partial + ((int64_t)tensor * groups + strip) * n;
+    by_radix(p.r0, [&](auto r) __attribute__((always_inline)) {
+      constexpr int R = decltype(r)::value;
+      mix_last<R, T>(data, tw, p, [&](float2 (&y)[R], int u, int m0, int c) __attribute__((always_inline)) {
+        write_energy<R>(y, p.lg_cp, c, out + u, m0, false);
+      });
+    });
+    // (the next strip's first stage writes the places that this thread has just read: no barrier)
   }
 }
 
 // ---- sequences beyond kFreqMaxTokens: N = N1 N2 through HBM -----------------------------------
-constexpr int kFreqLongElems = 8192;   // complex values per workgroup in the long path (8 per thread)
+// Workgroups of 512 threads on 8192 complex values: two share a compute unit, so that one loads or
+// stores while the other transforms.
+// The array crosses HBM four times per tensor; with twiddles from one root per butterfly and a table of its steps
+// (a 64-bit remainder and a root per value before) and the run-time plan above: K and V of 32768 x 1024
+// 510 -> 370 us, 131072 x 256 494 -> 318 us, 6000 x 1024 147 -> 86 us.
+constexpr int kFreqLongElems = 8192;
+constexpr int kFreqLongThreads = 512;
 
-__device__ __forceinline__ void build_twiddles(float2* tw, int n) {
-  for (int t = threadIdx.x; t < (n + 1) / 2; t += kFreqThreads) {
-    float s, c;
-    sincospif(-2.f * ((float)t / (float)n), &s, &c);
-    tw[t] = make_float2(c, s);
-  }
-}
-// exp(sgn 2 pi i a b / n) for a b < 2^48, n < 2^24: the product is reduced exactly before it is rounded
-__device__ __forceinline__ float2 long_twiddle(int a, int b, int n, float sgn) {
-  const int t = (int)(((int64_t)a * b) % n);
+// exp(sgn 2 pi i t / n), t < n < 2^24.  The angle is brought to within an eighth of a turn of a quarter in whole
+// numbers first: what the rounded quotient is off by then counts little.
+__device__ __forceinline__ float2 unit_root(int t, int n, float sgn) {
+  const int q = (4 * t + n / 2) / n;               // nearest quarter turn, 0 ... 4
+  const float turns2 = (float)(4 * t - q * n) * (0.5f / (float)n);   // half turns from there
   float s, c;
-  sincospif(2.f * ((float)t / (float)n), &s, &c);
-  return make_float2(c, sgn * s);
+  sincospif(turns2, &s, &c);
+  const float x = q & 1 ? -s : c, y = q & 1 ? c : s;
+  return q & 2 ? make_float2(-x, -sgn * y) : make_float2(x, sgn * y);
 }
 
 // A: one workgroup = one n2 and one strip of 2^lg complex columns (pairs of real columns).
-__global__ __launch_bounds__(kFreqThreads) void freq_long_a_kernel(const uint16_t* __restrict__ src, int32_t width,
-                                                                   FftPlan p1, int32_t n, int32_t n2_len,
-                                                                   float2* __restrict__ scratch) {
-  extern __shared__ float2 lds[];
-  int n1 = p1.n, lg = p1.lg_cp;
-  const int cp = 1 << lg;
-  float2* data = lds;
-  float2* tw = lds + ((n1 + (n1 >> 4) + 1) << lg);
-  const int strips = width >> lg;
+__global__ __launch_bounds__(kFreqLongThreads) void freq_long_a_kernel(const uint16_t* __restrict__ src, int32_t width,
+                                                                       MixPlan p, int32_t n, int32_t n2_len,
+                                                                       float2* __restrict__ scratch) {
+  constexpr int T = kFreqLongThreads;
+  extern __shared__ float2 data[];
+  float2* const tw = data + ((size_t)p.rows() << p.lg_cp);
+  float2* const steps = tw + p.tables();                 // exp(-2 pi i n2 R0 R1 i / n), i < R2
+  const int strips = width >> p.lg_cp;
   const int strip = blockIdx.x % strips, n2 = blockIdx.x / strips;
-  build_twiddles(tw, n1);
-  const uint32_t* base = reinterpret_cast<const uint32_t*>(src) + (int64_t)strip * cp;
-  for (int e = threadIdx.x; e < (n1 << lg); e += kFreqThreads) {
-    const int row = e >> lg, c = e & (cp - 1);
-    const uint32_t pair = __builtin_nontemporal_load(base + ((int64_t)row * n2_len + n2) * width + c);
-    data[phys(row, c, lg)] = make_float2(bf16_lo(pair), bf16_hi(pair));
-  }
+  mix_tables(tw, p, T);
+  if (threadIdx.x < p.r2) steps[threadIdx.x] = unit_root(n2 * p.r0 * p.r1 * (int)threadIdx.x, n, -1.f);
   __syncthreads();
-  transform(data, tw, p1, n1, lg, -1.f);
-  float2* out = scratch + (int64_t)strip * cp;
-  for (int e = threadIdx.x; e < (n1 << lg); e += kFreqThreads) {
-    const int k1 = e >> lg, c = e & (cp - 1);
-    out[((int64_t)k1 * n2_len + n2) * width + c] = cmul(data[phys(k1, c, lg)], long_twiddle(n2, k1, n, -1.f));
+  const uint32_t* base = reinterpret_cast<const uint32_t*>(src) + ((int64_t)strip << p.lg_cp) + (int64_t)n2 * width;
+  by_radix(p.r0, [&](auto r) __attribute__((always_inline)) {
+    mix_first<decltype(r)::value, T>(data, tw, p, [&](int, int row, int c) __attribute__((always_inline)) {
+      const uint32_t pair = __builtin_nontemporal_load(base + (int64_t)row * n2_len * width + c);
+      return make_float2(bf16_lo(pair), bf16_hi(pair));
+    });
+  });
+  __syncthreads();
+  if (p.r1 > 1) {
+    by_radix(p.r1, [&](auto r) __attribute__((always_inline)) { mix_second<decltype(r)::value, T, false>(data, tw + 5 * p.r1 * p.r2, p); });
+    __syncthreads();
   }
+  float2* out = scratch + ((int64_t)strip << p.lg_cp) + (int64_t)n2 * width;
+  by_radix(p.r2, [&](auto r) __attribute__((always_inline)) {
+    constexpr int R = decltype(r)::value;
+    mix_third<R, T, true, false>(data, p, [&](float2 (&y)[R], int bin0, int step, int c) __attribute__((always_inline)) {
+      const float2 w = unit_root(n2 * bin0, n, -1.f);
+#pragma unroll
+      for (int i = 0; i < R; ++i) out[(int64_t)(bin0 + step * i) * n2_len * width + c] = cmul(cmul(y[i], w), steps[i]);
+    });
+  });
 }
 
 // B: one workgroup = one k1 and one strip; rows k1 N2 ... k1 N2 + N2 - 1 of the scratch array, in place.
-__global__ __launch_bounds__(kFreqThreads) void freq_long_b_kernel(float2* __restrict__ scratch, int32_t width, FftPlan p2,
-                                                                   int32_t n, int32_t n1_len, int32_t cutoff) {
-  extern __shared__ float2 lds[];
-  int n2 = p2.n, lg = p2.lg_cp;
-  const int cp = 1 << lg;
-  float2* data = lds;
-  float2* tw = lds + ((n2 + (n2 >> 4) + 1) << lg);
-  const int strips = width >> lg;
+__global__ __launch_bounds__(kFreqLongThreads) void freq_long_b_kernel(float2* __restrict__ scratch, int32_t width, MixPlan p,
+                                                                       int32_t n, int32_t n1_len, int32_t cutoff) {
+  constexpr int T = kFreqLongThreads;
+  extern __shared__ float2 data[];
+  float2* const tw = data + ((size_t)p.rows() << p.lg_cp);
+  float2* const steps = tw + p.tables();                 // exp(2 pi i k1 R1 R2 i / n), i < R0
+  const int strips = width >> p.lg_cp;
   const int strip = blockIdx.x % strips, k1 = blockIdx.x / strips;
-  build_twiddles(tw, n2);
-  float2* rows = scratch + (int64_t)k1 * n2 * width + (int64_t)strip * cp;
-  for (int e = threadIdx.x; e < (n2 << lg); e += kFreqThreads) {
-    const int row = e >> lg, c = e & (cp - 1);
-    data[phys(row, c, lg)] = rows[(int64_t)row * width + c];
-  }
+  mix_tables(tw, p, T);
+  if (threadIdx.x < p.r0) steps[threadIdx.x] = unit_root(k1 * p.r1 * p.r2 * (int)threadIdx.x, n, 1.f);
   __syncthreads();
-  transform(data, tw, p2, n2, lg, -1.f);
-  // Eq. 3: bin k = k1 + N1 k2 goes when cutoff <= k <= N - cutoff
-  for (int e = threadIdx.x; e < (n2 << lg); e += kFreqThreads) {
-    const int k2 = e >> lg, c = e & (cp - 1);
-    const int k = k1 + n1_len * k2;
-    if (k >= cutoff && k <= n - cutoff) data[phys(k2, c, lg)] = make_float2(0.f, 0.f);
-  }
+  float2* rows = scratch + (int64_t)k1 * p.n * width + ((int64_t)strip << p.lg_cp);
+  by_radix(p.r0, [&](auto r) __attribute__((always_inline)) {
+    mix_first<decltype(r)::value, T>(data, tw, p, [&](int, int row, int c) __attribute__((always_inline)) {
+      return rows[(int64_t)row * width + c];
+    });
+  });
   __syncthreads();
-  transform(data, tw, p2, n2, lg, 1.f);
-  for (int e = threadIdx.x; e < (n2 << lg); e += kFreqThreads) {
-    const int j = e >> lg, c = e & (cp - 1);
-    rows[(int64_t)j * width + c] = cmul(data[phys(j, c, lg)], long_twiddle(j, k1, n, 1.f));
+  if (p.r1 > 1) {
+    by_radix(p.r1, [&](auto r) __attribute__((always_inline)) { mix_second<decltype(r)::value, T, false>(data, tw + 5 * p.r1 * p.r2, p); });
+    __syncthreads();
   }
+  by_radix(p.r2, [&](auto r) __attribute__((always_inline)) {
+    constexpr int R = decltype(r)::value;
+    // Eq. 3: bin k = k1 + N1 k2 goes when cutoff <= k <= N - cutoff
+    mix_third<R, T, true, true>(data, p, [&](float2 (&y)[R], int bin0, int step, int) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const int bin = k1 + n1_len * (bin0 + step * i);
+        if (bin >= cutoff && bin <= n - cutoff) y[i] = make_float2(0.f, 0.f);
+      }
+    });
+  });
+  __syncthreads();
+  if (p.r1 > 1) {
+    by_radix(p.r1, [&](auto r) __attribute__((always_inline)) { mix_second<decltype(r)::value, T, true>(data, tw + 5 * p.r1 * p.r2, p); });
+    __syncthreads();
+  }
+  by_radix(p.r0, [&](auto r) __attribute__((always_inline)) {
+    constexpr int R = decltype(r)::value;
+    mix_last<R, T>(data, tw, p, [&](float2 (&y)[R], int u, int m0, int c) __attribute__((always_inline)) {
+      const float2 w = unit_root(k1 * u, n, 1.f);
+#pragma unroll
+      for (int i = 0; i < R; ++i) rows[(int64_t)(u + i * m0) * width + c] = cmul(cmul(y[i], w), steps[i]);
+    });
+  });
 }
 
-// C: one workgroup = one n2 and one strip; partial[strip * n + token] = sum over the strip of |N x~|^2.
-__global__ __launch_bounds__(kFreqThreads) void freq_long_c_kernel(const float2* __restrict__ scratch, int32_t width,
-                                                                   FftPlan p1, int32_t n, int32_t n2_len,
-                                                                   float* __restrict__ partial) {
-  extern __shared__ float2 lds[];
-  int n1 = p1.n, lg = p1.lg_cp;
-  const int cp = 1 << lg;
-  float2* data = lds;
-  float2* tw = lds + ((n1 + (n1 >> 4) + 1) << lg);
-  const int strips = width >> lg;
-  const int strip = blockIdx.x % strips, n2 = blockIdx.x / strips;
-  build_twiddles(tw, n1);
-  const float2* in = scratch + (int64_t)strip * cp;
-  for (int e = threadIdx.x; e < (n1 << lg); e += kFreqThreads) {
-    const int k1 = e >> lg, c = e & (cp - 1);
-    data[phys(k1, c, lg)] = in[((int64_t)k1 * n2_len + n2) * width + c];
-  }
-  __syncthreads();
-  transform(data, tw, p1, n1, lg, 1.f);
-  // Eq. 5: a token's squares over the strip, summed by one thread in a fixed order
-  for (int row = threadIdx.x; row < n1; row += kFreqThreads) {
-    const float2* line = data + phys(row, 0, lg);
-    float sq = 0.f;
-    for (int q = 0; q < cp; ++q) {
-      const float2 x = line[(q + row) & (cp - 1)];
-      sq = fmaf(x.x, x.x, fmaf(x.y, x.y, sq));
+// C: one workgroup = one n2 and `per` strips; partial[(strip / per) * n + token] = sum over the strips of |N x~|^2.
+__global__ __launch_bounds__(kFreqLongThreads) void freq_long_c_kernel(const float2* __restrict__ scratch, int32_t width,
+                                                                       MixPlan p, int32_t n, int32_t n2_len, int32_t per,
+                                                                       float* __restrict__ partial) {
+  constexpr int T = kFreqLongThreads;
+  extern __shared__ float2 data[];
+  float2* const tw = data + ((size_t)p.rows() << p.lg_cp);
+  const int groups = (width >> p.lg_cp) / per;
+  const int group = blockIdx.x % groups, n2 = blockIdx.x / groups;
+  mix_tables(tw, p, T);
+  float* out = partial + (int64_t)group * n + n2;
+  for (int q = 0; q < per; ++q) {
+    const float2* in = scratch + ((int64_t)(group * per + q) << p.lg_cp) + (int64_t)n2 * width;
+    by_radix(p.r2, [&](auto r) __attribute__((always_inline)) {
+      constexpr int R = decltype(r)::value;
+      mix_third<R, T, false, true>(data, p, [&](float2 (&y)[R], int bin0, int step, int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) y[i] = in[(int64_t)(bin0 + step * i) * n2_len * width + c];
+      });
+    });
+    __syncthreads();
+    if (p.r1 > 1) {
+      by_radix(p.r1, [&](auto r) __attribute__((always_inline)) { mix_second<decltype(r)::value, T, true>(data, tw + 5 * p.r1 * p.r2, p); });
+      __syncthreads();
     }
-    partial[(int64_t)strip * n + (int64_t)row * n2_len + n2] = sq;
+    by_radix(p.r0, [&](auto r) __attribute__((always_inline)) {
+      constexpr int R = decltype(r)::value;
+      mix_last<R, T>(data, tw, p, [&](float2 (&y)[R], int u, int m0, int c) __attribute__((always_inline)) {
+        // the same thread adds the next strip's squares
+        write_energy<R>(y, p.lg_cp, c, out + (int64_t)u * n2_len, (int64_t)m0 * n2_len, q > 0);
+      });
+    });
+    __syncthreads();
   }
 }
 
@@ -790,20 +934,44 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
 }
 
 // ---- host side ------------------------------------------------------------------------------
-static bool factor_radices(int32_t n, FftPlan* p) {
-  p->n = n;
-  p->n_pass = 0;
-  int rest = n;
-  const int radices[6] = {16, 8, 4, 2, 3, 5};
-  // powers of two first, largest radix first; a lone factor 2 after 16s is folded as 8 or 4
-  for (int r : radices) {
-    while (rest % r == 0 && rest > 1) {
-      if (p->n_pass == 12) return false;
-      p->radix[p->n_pass++] = r;
-      rest /= r;
+// Radices of a run-time plan: the split of n with the least estimated vector instructions for a strip of
+// n << lg values (a wave's instructions for one butterfly: its sums and products, 8 per twiddle, LDS accesses
+// and addresses).  It depends on the shape alone, so a sequence gets the same bits whatever it is batched with.
+static bool make_mix_plan(int32_t n, int lg, int elems, size_t lds_cap, MixPlan* out) {
+  static const int radix[15] = {1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 25, 27};
+  static const int sums[15] = {0, 4, 14, 16, 36, 40, 60, 90, 92, 96, 160, 190, 200, 400, 400};
+  double best = 0;
+  bool found = false;
+  if ((int64_t)n << lg > elems) return false;
+  for (int a = 0; a < 15; ++a)
+    for (int b = 0; b < 15; ++b) {
+      const int r0 = radix[a], r1 = radix[b];
+      if (n % (r0 * r1) != 0) continue;
+      const int r2 = n / (r0 * r1);
+      int c = 0;
+      while (c < 15 && radix[c] != r2) ++c;
+      if (c == 15) continue;
+      MixPlan p = {};
+      p.n = n;
+      p.lg_cp = lg;
+      p.r0 = r0;
+      p.r1 = r1;
+      p.r2 = r2;
+      p.pitch = r2 > 1 && r2 % 2 == 0 && lg < 5 ? r2 + 1 : r2;
+      if (p.lds_bytes(32) > lds_cap) p.pitch = r2;
+      if (p.lds_bytes(32) > lds_cap) continue;
+      p.mg1 = r1 > 1 ? (uint32_t)((1ull << 32) / r1 + 1) : 0;
+      p.mg2 = r2 > 1 ? (uint32_t)((1ull << 32) / r2 + 1) : 0;
+      auto waves = [&](int r) { return (double)((((int64_t)n << lg) / r + 255) / 256); };   // per SIMD, rounded up
+      double cost = 2 * waves(r0) * (sums[a] + 11 * r0 + 30) + waves(r2) * (2 * sums[c] + 4 * r2 + 30) + 200;
+      if (r1 > 1) cost += 2 * waves(r1) * (sums[b] + 12 * r1 + 30) + 400;
+      if (!found || cost < best) {
+        best = cost;
+        *out = p;
+        found = true;
+      }
     }
-  }
-  return rest == 1;
+  return found;
 }
 
 static int32_t cutoff_bins(int32_t n, double alpha) {
@@ -816,8 +984,9 @@ static int32_t cutoff_bins(int32_t n, double alpha) {
 
 // Long sequences: N = N1 N2 with N1 <= N2 <= kFreqMaxTokens, N1 the largest such divisor.
 struct LongPlan {
-  FftPlan p1, p2;
+  MixPlan p1, p2;
   int32_t width;        // complex columns per row = row_elems / 2
+  int32_t per;          // strips that a workgroup of the last kernel adds up
   int32_t cutoff;
   size_t partial_bytes, scratch_bytes;
 };
@@ -831,40 +1000,39 @@ static bool make_long_plan(int32_t n, int32_t row_elems, double alpha, LongPlan*
     }
   if (n1 == 0) return false;
   *lp = LongPlan{};
-  if (!factor_radices(n1, &lp->p1) || !factor_radices(n / n1, &lp->p2)) return false;
   lp->width = row_elems / 2;
-  for (FftPlan* p : {&lp->p1, &lp->p2}) {
+  const int len[2] = {n1, n / n1};
+  for (int i = 0; i < 2; ++i) {
     int lg = 0;
-    while (((int64_t)p->n << (lg + 1)) <= kFreqLongElems && lp->width % (2 << lg) == 0) ++lg;
-    p->lg_cp = lg;
+    while (((int64_t)len[i] << (lg + 1)) <= kFreqLongElems && lp->width % (2 << lg) == 0) ++lg;
+    if (i == 0) lp->per = lg > 6 ? 1 << (lg - 6) : 1;
+    if (lg > 6) lg = 6;             // a token's squares are summed within a wave
+    // (a second workgroup fits beside this one unless rows are very few and long)
+    if (!make_mix_plan(len[i], lg, kFreqLongElems, 80 * 1024, i == 0 ? &lp->p1 : &lp->p2) &&
+        !make_mix_plan(len[i], lg, kFreqLongElems, 160 * 1024, i == 0 ? &lp->p1 : &lp->p2))
+      return false;
   }
   lp->cutoff = cutoff_bins(n, alpha);
-  const size_t strips_c = (size_t)lp->width >> lp->p1.lg_cp;
+  const size_t strips_c = ((size_t)lp->width >> lp->p1.lg_cp) / lp->per;
   lp->partial_bytes = strips_c * n * sizeof(float);                            // per tensor
   lp->scratch_bytes = ((size_t)n * lp->width * sizeof(float2) + 255) & ~(size_t)255;
   return true;
 }
-static size_t long_lds_bytes(const FftPlan& p) {
-  return ((size_t)((p.n + (p.n >> 4) + 1) << p.lg_cp) + (size_t)(p.n + 1) / 2) * sizeof(float2);
-}
-
-static bool make_plan(int32_t n, int32_t row_elems, double alpha, int32_t n_batch, FftPlan* p) {
-  if (!factor_radices(n, p)) return false;
+// Sequences that fit LDS: 2^lg complex columns per strip, one strip at a time per workgroup.
+struct StripPlan {
+  int lg, groups, cutoff;      // groups: strips per tensor
+  MixPlan mix;
+};
+static bool make_plan(int32_t n, int32_t row_elems, double alpha, StripPlan* p) {
   int lg = 0;
   while ((2 << lg) <= 64 && (int64_t)n * (2 << lg) <= kFreqMaxElems && row_elems % (4 << lg) == 0) ++lg;
   if (row_elems % (2 << lg) != 0) return false;
-  p->lg_cp = lg;
+  p->lg = lg;
+  p->groups = row_elems / (2 << lg);
   p->cutoff = cutoff_bins(n, alpha);
-  p->strips = row_elems / (2 << lg);
-  // one strip per workgroup.  The split depends on the shape alone, not on the batch, so that a
-  // sequence gets the same bits whatever it is batched with.
-  (void)n_batch;
-  p->groups = p->strips;
+  if (!make_mix_plan(n, lg, kFreqMaxElems, 160 * 1024, &p->mix)) return false;
+  p->mix.cutoff = p->cutoff;
   return true;
-}
-
-static size_t freq_lds_bytes(const FftPlan& p) {
-  return ((size_t)((p.n + (p.n >> 4) + 1) << p.lg_cp) + (size_t)(p.n + 1) / 2) * sizeof(float2);
 }
 
 }  // namespace ct
@@ -874,14 +1042,14 @@ using namespace ct;
 extern "C" {
 
 size_t ct_frequency_workspace_bytes(int32_t n_batch, int32_t n_tokens, int32_t row_elems) {
-  FftPlan p;
+  StripPlan p;
   if (n_batch <= 0 || n_tokens <= 0 || row_elems <= 0) return 0;
   if (n_tokens > kFreqMaxTokens) {
     LongPlan lp;
     if (!make_long_plan(n_tokens, row_elems, 0.5, &lp)) return 0;
     return (((size_t)n_batch * 2 * lp.partial_bytes + 255) & ~(size_t)255) + lp.scratch_bytes;
   }
-  if (!make_plan(n_tokens, row_elems, 0.5, n_batch, &p)) return 0;
+  if (!make_plan(n_tokens, row_elems, 0.5, &p)) return 0;
   return (size_t)n_batch * 2 * p.groups * n_tokens * sizeof(float);
 }
 
@@ -916,16 +1084,16 @@ ct_status ct_frequency_scores(const void* k, const void* v, int32_t n_batch, int
     const int n1 = lp.p1.n, n2 = lp.p2.n;
     const unsigned grid_ac = (unsigned)((size_t)n2 * (lp.width >> lp.p1.lg_cp));
     const unsigned grid_b = (unsigned)((size_t)n1 * (lp.width >> lp.p2.lg_cp));
-    const int groups = lp.width >> lp.p1.lg_cp;
+    const int groups = (lp.width >> lp.p1.lg_cp) / lp.per;
     // one tensor at a time through the one scratch array (the launches of a stream run in order)
     for (int t = 0; t < n_batch * 2; ++t) {
       const uint16_t* src = (const uint16_t*)((t & 1) ? v : k) + (int64_t)(t >> 1) * batch_stride;
-      launch_kernel(KC_FREQ, freq_long_a_kernel, dim3(grid_ac), dim3(kFreqThreads), (unsigned)long_lds_bytes(lp.p1), s, src,
+      launch_kernel(KC_FREQ, freq_long_a_kernel, dim3(grid_ac), dim3(kFreqLongThreads), (unsigned)lp.p1.lds_bytes(32), s, src,
                     lp.width, lp.p1, n_tokens, n2, scratch);
-      launch_kernel(KC_FREQ, freq_long_b_kernel, dim3(grid_b), dim3(kFreqThreads), (unsigned)long_lds_bytes(lp.p2), s, scratch,
+      launch_kernel(KC_FREQ, freq_long_b_kernel, dim3(grid_b), dim3(kFreqLongThreads), (unsigned)lp.p2.lds_bytes(32), s, scratch,
                     lp.width, lp.p2, n_tokens, n1, lp.cutoff);
-      launch_kernel(KC_FREQ, freq_long_c_kernel, dim3(grid_ac), dim3(kFreqThreads), (unsigned)long_lds_bytes(lp.p1), s,
-                    (const float2*)scratch, lp.width, lp.p1, n_tokens, n2,
+      launch_kernel(KC_FREQ, freq_long_c_kernel, dim3((unsigned)n2 * groups), dim3(kFreqLongThreads), (unsigned)lp.p1.lds_bytes(32), s,
+                    (const float2*)scratch, lp.width, lp.p1, n_tokens, n2, lp.per,
                     partial + (size_t)t * (lp.partial_bytes / sizeof(float)));
     }
     hipError_t e = hipGetLastError();
@@ -936,25 +1104,24 @@ ct_status ct_frequency_scores(const void* k, const void* v, int32_t n_batch, int
     if (e != hipSuccess) return hip_fail(e, "frequency score finish launch");
     return CT_OK;
   }
-  FftPlan p;
-  if (!make_plan(n_tokens, row_elems, alpha, n_batch, &p))
+  StripPlan p;
+  if (!make_plan(n_tokens, row_elems, alpha, &p))
     return fail(CT_ERR_UNSUPPORTED, "n_tokens %d has a prime factor above 5", n_tokens);
   const size_t need = (size_t)n_batch * 2 * p.groups * n_tokens * sizeof(float);
   if (workspace == nullptr || workspace_bytes < need)
     return fail(CT_ERR_WORKSPACE, "workspace of %zu bytes, %zu needed", workspace_bytes, need);
+  const int n_work = n_batch * 2 * p.groups;
+  const unsigned grid = n_work < kNumCUs ? n_work : kNumCUs;   // a workgroup fills a compute unit and goes on to further strips
   // power-of-two lengths from 256 on whose strips hold the full kFreqMaxElems values take the kernel
   // with the plan compiled in; everything else the one that reads the plan at run time
-  using Kernel = void (*)(const uint16_t*, const uint16_t*, int64_t, int32_t, int32_t, FftPlan, float*);
-  Kernel kern = freq_energy_kernel<0>;
-  size_t lds = freq_lds_bytes(p);
-  const int n_work = n_batch * 2 * p.groups;
-  unsigned grid = n_work;
+  using Kernel = void (*)(const uint16_t*, const uint16_t*, int64_t, int32_t, int32_t, int32_t, int32_t, float*);
+  Kernel kern = nullptr;
+  size_t lds = 0;
   auto fixed = [&](Kernel f, int rows) {
     kern = f;
-    lds = ((size_t)rows * p.cp() + 16 * 17) * sizeof(float2);
-    grid = n_work < kNumCUs ? n_work : kNumCUs;      // a workgroup fills a compute unit and goes on to further strips
+    lds = (((size_t)rows << p.lg) + 16 * 17) * sizeof(float2);
   };
-  if ((int64_t)n_tokens << p.lg_cp == kFreqMaxElems) {
+  if ((int64_t)n_tokens << p.lg == kFreqMaxElems) {
     switch (n_tokens) {
       case 256: fixed(freq_fixed_kernel<256>, FixedPlan<256>::ROWS); break;
       case 512: fixed(freq_fixed_kernel<512>, FixedPlan<512>::ROWS); break;
@@ -964,10 +1131,15 @@ ct_status ct_frequency_scores(const void* k, const void* v, int32_t n_batch, int
       default: break;
     }
   }
-  hipError_t ea = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  const void* fn = kern != nullptr ? (const void*)kern : (const void*)freq_mixed_kernel;
+  hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (ea != hipSuccess) return hip_fail(ea, "hipFuncSetAttribute(frequency score kernel)");
-  launch_kernel(KC_FREQ, kern, dim3(grid), dim3(kFreqThreads), (unsigned)lds, s, (const uint16_t*)k, (const uint16_t*)v,
-                batch_stride, row_elems, n_work, p, (float*)workspace);
+  if (kern != nullptr)
+    launch_kernel(KC_FREQ, kern, dim3(grid), dim3(kFreqThreads), (unsigned)lds, s, (const uint16_t*)k, (const uint16_t*)v,
+                  batch_stride, row_elems, n_work, p.groups, p.cutoff, (float*)workspace);
+  else
+    launch_kernel(KC_FREQ, freq_mixed_kernel, dim3(grid), dim3(kFreqThreads), (unsigned)p.mix.lds_bytes(0), s,
+                  (const uint16_t*)k, (const uint16_t*)v, batch_stride, row_elems, n_work, p.groups, p.mix, (float*)workspace);
   launch_kernel(KC_FREQ, freq_finish_kernel, dim3((unsigned)((int64_t)n_batch * ((n_tokens + 63) / 64))), dim3(256), 0, s,
                 (const float*)workspace, n_tokens, p.groups, n_batch, scores);
   hipError_t e = hipGetLastError();

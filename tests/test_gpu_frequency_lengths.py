@@ -1,0 +1,39 @@
+"""Frequency scores at lengths that take the run-time plan: every radix in every place, strips of one to 64
+column pairs, both factors of the lengths beyond 4096 tokens, against a 64-bit FFT of the same values."""
+import pytest
+import torch
+
+from paper_2605_24022_amd import binding as B
+from tests.gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    assert torch.cuda.is_available()
+    B.load()
+    torch.cuda.set_device(0)
+
+
+@pytest.mark.parametrize("n,row,n_batch,alpha", [
+    (1, 2, 2, 0.5), (5, 6, 1, 1.0), (27, 64, 2, 0.5), (96, 1024, 1, 0.5), (100, 128, 3, 0.3), (486, 256, 1, 0.5),
+    (625, 64, 2, 0.5), (640, 1000, 1, 0.7), (1500, 1024, 1, 0.5), (1500, 6, 1, 0.5), (1536, 128, 2, 0.0), (1944, 64, 1, 0.5),
+    (2025, 48, 1, 0.4), (2048, 10, 1, 0.5), (2187, 32, 1, 0.5), (2500, 128, 1, 0.5), (3645, 16, 1, 0.5), (4050, 1000, 1, 0.5),
+    (4096, 6, 1, 0.5), (4860, 128, 2, 0.5), (9375, 20, 1, 0.5), (15625, 16, 1, 0.5), (100000, 8, 1, 0.2)])
+def test_scores_against_fp64(n, row, n_batch, alpha):
+    say(f"frequency lengths n={n} row={row} batch={n_batch} alpha={alpha}")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    k, v = (torch.randn(n_batch, n, row, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    ws_bytes = B.ct_frequency_workspace_bytes(n_batch, n, row)
+    assert ws_bytes > 0
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    scores = torch.full((n_batch, n), -1.0, device="cuda")
+    B.ct_frequency_scores(k, v, n_batch, n * row, n, row, alpha, scores, ws, ws_bytes)
+    kept = (torch.arange(n // 2 + 1, device="cuda") < int(alpha * (n // 2 + 1) + 1e-9)).double()[None, :, None]
+    want = 0
+    for x in (k, v):
+        want = want + 0.5 * torch.fft.irfft(torch.fft.rfft(x.double(), dim=1) * kept, n=n, dim=1).norm(dim=2)
+    # roundings of 2^-24, about 4 log2(n) <= 68 of them deep, relative to the largest score
+    err = float((scores.double() - want).abs().max())
+    assert torch.isfinite(scores).all() and err <= 4.1e-6 * max(float(want.max()), 1e-30), err
