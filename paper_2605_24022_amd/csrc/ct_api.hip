@@ -305,6 +305,25 @@ ct_status stream_in_host_chunks(const ct_layer_cfg* cfg, const ct_chunk* chunks,
   return CT_OK;
 }
 
+bool move_beside_projection(const ReropeChunks& m, const void* k_buf, const void* v_buf, size_t row_bytes, int32_t n_ctx,
+                            const void* workspace, size_t workspace_bytes) {
+  auto meets = [](const void* a, size_t an, const void* b, size_t bn) {
+    return (uintptr_t)a < (uintptr_t)b + bn && (uintptr_t)b < (uintptr_t)a + an;
+  };
+  const size_t buf = (size_t)n_ctx * row_bytes;
+  for (int c = 0; c < m.n; ++c) {
+    const size_t bytes = (size_t)(m.tok_start[c + 1] - m.tok_start[c]) * row_bytes;
+    const size_t place = (size_t)m.row_start[c] * row_bytes;
+    const void* src[2] = {m.k_src[c], m.v_src[c]};
+    const void* own[2] = {static_cast<const char*>(k_buf) + place, static_cast<const char*>(v_buf) + place};
+    for (int i = 0; i < 2; ++i)
+      if (src[i] != nullptr && src[i] != own[i] &&
+          (meets(src[i], bytes, k_buf, buf) || meets(src[i], bytes, v_buf, buf) || meets(src[i], bytes, workspace, workspace_bytes)))
+        return false;
+  }
+  return true;
+}
+
 }  // namespace ct
 
 using namespace ct;
@@ -710,22 +729,27 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
   // Device-resident chunks: rotated (and their values copied) into place in as few launches
   // as the table size allows; they do not wait for any copy.  Rows of the recompute set are left
   // out: the projection's epilogue (or the scatter) writes them next.
+  // What fits one table rides on the projection's launch where that leaves compute units free.
+  ReropeChunks rc;
   {
-    ReropeChunks rc;
-    auto flush = [&]() -> ct_status {
-      if (rc.n == 0) return CT_OK;
+    auto close = [&]() {
       rc.tok_start[rc.n] = rc.total_tokens;
       rc.skip_rows = n_sel > 0 ? sel_idx : nullptr;
       rc.n_skip = n_sel;
+    };
+    auto flush = [&]() -> ct_status {
+      if (rc.n == 0) return CT_OK;
+      close();
       ct_status r = launch_rerope_chunks(cfg, k_buf, v_buf, &rc, 0, cs);
       rc.n = 0;
       rc.total_tokens = 0;
       return r;
     };
     memset(&rc, 0, sizeof(rc));
-    for (int c = 0; c < n_chunks; ++c) {
+    for (int c = 0; c < n_chunks && n_sel < n_ctx; ++c) {   // (n_sel == n_ctx: every row is recomputed)
       const ct_chunk& ch = chunks[c];
       if (ch.location != 0) continue;
+      if (rc.n == 32 && (st = flush()) != CT_OK) return st;
       const char* vd = static_cast<const char*>(v_buf) + (size_t)tab.row_start[c] * row_bytes;
       const int i = rc.n++;
       rc.tok_start[i] = rc.total_tokens;
@@ -735,15 +759,19 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
       rc.row_start[i] = tab.row_start[c];
       rc.delta0[i] = ch.raw_keys ? ch.new_pos_start : ch.new_pos_start - ch.old_pos_start;
       rc.delta_step[i] = ch.raw_keys ? 1 : 0;
-      if (rc.n == 32 && (st = flush()) != CT_OK) return st;
     }
-    if ((st = flush()) != CT_OK) return st;
+    close();
+    if ((n_sel == 0 || !projection_leaves_units(cfg, n_sel) || !move_beside_projection(rc, k_buf, v_buf, row_bytes, n_ctx, workspace, workspace_bytes)) &&
+        (st = flush()) != CT_OK)
+      return st;
   }
+  const ReropeChunks* move = rc.n > 0 ? &rc : nullptr;
   // Recompute stream: projection of the selected rows runs while the copies are in flight.
   if (n_sel > 0) {
     st = direct ? launch_qkv(cfg, hidden, hidden_rows, nullptr, sel_idx, &tab, n_sel, wqkv, bias, q_rows, k_buf, v_buf, cs,
-                             sel_idx)
-                : launch_qkv(cfg, hidden, hidden_rows, nullptr, sel_idx, &tab, n_sel, wqkv, bias, q_rows, k_rows, v_rows, cs);
+                             sel_idx, move, k_buf, v_buf)
+                : launch_qkv(cfg, hidden, hidden_rows, nullptr, sel_idx, &tab, n_sel, wqkv, bias, q_rows, k_rows, v_rows, cs,
+                             nullptr, move, k_buf, v_buf);
     if (st != CT_OK) return st;
   }
   // Pinned-host chunks: already rotated by the stream-in kernel, or rotated in place chunk by

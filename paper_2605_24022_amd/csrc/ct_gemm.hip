@@ -29,7 +29,10 @@
 // patch of neighbouring tiles and share their W and X tiles in that XCD's L2.
 #include <string.h>
 
+#include <type_traits>
+
 #include "ct_internal.h"
+#include "ct_rerope.h"
 
 namespace ct {
 
@@ -42,6 +45,9 @@ constexpr int BK = 64;            // reduction elements per stage
 constexpr int ROWB = BK * 2;      // LDS row in bytes (unpadded, swizzled)
 constexpr int A_BYTES = BF * ROWB;
 constexpr int A_SLOTS = 3;        // LDS slots of weight tiles
+// LDS slots of token tiles of 128 * nb rows; they are loaded b_slots - 1 steps ahead
+constexpr int b_slots(int nb) { return nb == 1 ? 3 : 2; }
+constexpr int gemm_lds_bytes(int nb) { return A_SLOTS * A_BYTES + b_slots(nb) * 128 * nb * ROWB; }
 
 enum Epilogue { EPI_QKV_ROPE = 0, EPI_LINEAR = 1, EPI_SWIGLU = 2, EPI_PARTIAL = 3 };
 
@@ -100,8 +106,8 @@ __device__ __forceinline__ void tile_of(int v, int nF, int nT, int* f_tile, int*
 // output features, so gate and up of one (feature, token) land in the same lane and register
 // index of accumulator tiles (m, m + 2) - the same pairing the half-split RoPE uses.
 template <int EPI, int D, int STYLE, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void gemm_kernel(
-    GemmArgs a, RopeTable rope, ChunkTable chunks) {
+__device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTable& rope, const ChunkTable& chunks,
+                                               unsigned char* lds) {
   constexpr int NWAVES = NW;                 // 8: two waves per SIMD; 4: one
   constexpr int A_LOADS = BF / 8 / NWAVES;   // wave-wide loads (8 rows each) per wave and stage
   constexpr int BT = 128 * NB;
@@ -112,8 +118,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
   constexpr bool PAIR64 = EPI == EPI_SWIGLU || (EPI == EPI_QKV_ROPE && D == 128);
   constexpr int B_BYTES = BT * ROWB;
   constexpr int B_LOADS = BT / 8 / NWAVES;
-  constexpr int B_SLOTS = NB == 1 ? 3 : 2;   // LDS slots of token tiles; they are loaded B_SLOTS - 1 steps ahead
-  __shared__ __align__(1024) unsigned char lds[A_SLOTS * A_BYTES + B_SLOTS * B_BYTES];
+  constexpr int B_SLOTS = b_slots(NB);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
@@ -486,6 +491,33 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
   }
 }
 
+template <int EPI, int D, int STYLE, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void gemm_kernel(
+    GemmArgs a, RopeTable rope, ChunkTable chunks) {
+  __shared__ __align__(1024) unsigned char lds[gemm_lds_bytes(NB)];
+  gemm_workgroup<EPI, D, STYLE, NB, NW>(a, rope, chunks, lds);
+}
+
+// The projection with the rotation of the device-resident chunks in the same launch: workgroups from
+// move_after on bring reused rows into the layer buffers.  The two touch different rows (the recompute set
+// is what `move` skips) and different limits (matrix cores, memory), and the rotation runs on the compute units that
+// the projection's last round leaves idle instead of in a launch of its own before it.  Few tokens per workgroup:
+// with four times as many, fetched all heads at once, one waits for the last of them (8192 tokens, 1228 rows 208 -> 215 us).
+constexpr int kMoveThreads = 512;
+template <int D, int STYLE, int NB>
+__global__ __launch_bounds__(kMoveThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void qkv_move_kernel(
+    GemmArgs a, RopeTable rope, ChunkTable chunks, ReropeChunks move, uint16_t* k_buf, uint16_t* v_buf, int32_t move_after) {
+  __shared__ __align__(1024) unsigned char lds[gemm_lds_bytes(NB)];
+  if ((int)blockIdx.x >= move_after) {
+    const int block = blockIdx.x - move_after, blocks = gridDim.x - move_after;
+    if (a.Hkv == 8) rerope_chunk_tokens<D, STYLE, 8, true>(k_buf, v_buf, 8, rope, move, kMoveThreads, block, blocks);
+    else if (a.Hkv == 2) rerope_chunk_tokens<D, STYLE, 2, true>(k_buf, v_buf, 2, rope, move, kMoveThreads, block, blocks);
+    else rerope_chunk_tokens<D, STYLE, 0, true>(k_buf, v_buf, a.Hkv, rope, move, kMoveThreads, block, blocks);
+    return;
+  }
+  gemm_workgroup<EPI_QKV_ROPE, D, STYLE, NB, 8>(a, rope, chunks, lds);
+}
+
 // Sum of the k_parts partial tiles of EPI_PARTIAL (+ residual), rounded to bf16 and written to
 // out[t, f].  One thread per token and four consecutive features; a workgroup covers 4 tokens.
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a) {
@@ -560,10 +592,37 @@ static ct_status launch_variant(const GemmArgs& a, const RopeTable& rope, const 
   return launch_gemm(gemm_kernel<EPI, D, STYLE, NB, NW>, 64 * NW, a, rope, tab, kc, s);
 }
 
+template <int D, int STYLE, int NB>
+static ct_status launch_qkv_variant(const GemmArgs& a, const RopeTable& rope, const ChunkTable& tab, const ReropeChunks* move,
+                                    void* k_buf, void* v_buf, hipStream_t s) {
+  if (move == nullptr) return launch_variant<EPI_QKV_ROPE, D, STYLE, NB>(a, rope, tab, KC_QKV, s);
+  const int gemm_blocks = (a.v_count + kNumXCDs - 1) / kNumXCDs * kNumXCDs;
+  const int64_t move_blocks = (move->total_tokens * (D / 16) + kMoveThreads - 1) / kMoveThreads;
+  launch_kernel(KC_QKV, qkv_move_kernel<D, STYLE, NB>, dim3((unsigned)(gemm_blocks + move_blocks)), dim3(kMoveThreads), 0, s, a,
+                rope, tab, *move, static_cast<uint16_t*>(k_buf), static_cast<uint16_t*>(v_buf), gemm_blocks);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e, "projection kernel launch");
+  return CT_OK;
+}
+
+// The rotation beside the projection costs it some of its memory bandwidth, which pays as long as idle compute
+// units take most of the work.  Llama-3-8B layer, fused against a launch of its own before: 2048 tokens,
+// 307 rows 88 us against 99 us, 8192 tokens, 983 rows 154 / 163 us, 32768 tokens, 1638 rows 546 / 561 us; with
+// 240 tiles on 256 units 206 / 205 us (8192 tokens, 1228 rows) and 529 / 529 us (16384 tokens, 2457 rows).
+bool projection_leaves_units(const ct_layer_cfg* cfg, int32_t n_sel) {
+  GemmArgs a;
+  memset(&a, 0, sizeof(a));
+  a.n_sel = n_sel;
+  a.O = (cfg->n_q_heads + 2 * cfg->n_kv_heads) * cfg->head_dim;
+  fill_tiles(&a, false, pick_nb(a, false));
+  const int last = a.v_count % kNumCUs;
+  return last > 0 && last <= kNumCUs - kNumCUs / 8;
+}
+
 ct_status launch_qkv(const ct_layer_cfg* cfg, const void* hidden, const int32_t* hidden_rows, const int32_t* sel_pos,
                      const int32_t* sel_idx, const ChunkTable* chunks, int32_t n_sel, const void* wqkv,
                      const void* bias, void* q_out, void* k_out, void* v_out, hipStream_t s,
-                     const int32_t* kv_rows) {
+                     const int32_t* kv_rows, const ReropeChunks* move, void* k_buf, void* v_buf) {
   if (n_sel == 0) return CT_OK;
   GemmArgs a;
   memset(&a, 0, sizeof(a));
@@ -595,18 +654,17 @@ ct_status launch_qkv(const ct_layer_cfg* cfg, const void* hidden, const int32_t*
     tab.row_start[1] = 0x7fffffff;
     tab.new_start[0] = 0;
   }
-  if (nb == 2) {
-    if (cfg->head_dim == 128)
-      return cfg->rope_style == 0 ? launch_variant<EPI_QKV_ROPE, 128, 0, 2>(a, rope, tab, KC_QKV, s)
-                                  : launch_variant<EPI_QKV_ROPE, 128, 1, 2>(a, rope, tab, KC_QKV, s);
-    return cfg->rope_style == 0 ? launch_variant<EPI_QKV_ROPE, 64, 0, 2>(a, rope, tab, KC_QKV, s)
-                                : launch_variant<EPI_QKV_ROPE, 64, 1, 2>(a, rope, tab, KC_QKV, s);
-  }
-  if (cfg->head_dim == 128)
-    return cfg->rope_style == 0 ? launch_variant<EPI_QKV_ROPE, 128, 0, 1>(a, rope, tab, KC_QKV, s)
-                                : launch_variant<EPI_QKV_ROPE, 128, 1, 1>(a, rope, tab, KC_QKV, s);
-  return cfg->rope_style == 0 ? launch_variant<EPI_QKV_ROPE, 64, 0, 1>(a, rope, tab, KC_QKV, s)
-                              : launch_variant<EPI_QKV_ROPE, 64, 1, 1>(a, rope, tab, KC_QKV, s);
+  auto launch = [&](auto d, auto style) -> ct_status {
+    constexpr int D = decltype(d)::value, STYLE = decltype(style)::value;
+    return nb == 2 ? launch_qkv_variant<D, STYLE, 2>(a, rope, tab, move, k_buf, v_buf, s)
+                   : launch_qkv_variant<D, STYLE, 1>(a, rope, tab, move, k_buf, v_buf, s);
+  };
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  using C64 = std::integral_constant<int, 64>;
+  using C128 = std::integral_constant<int, 128>;
+  if (cfg->head_dim == 128) return cfg->rope_style == 0 ? launch(C128{}, C0{}) : launch(C128{}, C1{});
+  return cfg->rope_style == 0 ? launch(C64{}, C0{}) : launch(C64{}, C1{});
 }
 
 // The last round of 256-token tiles of a linear launch, when it would leave most compute units

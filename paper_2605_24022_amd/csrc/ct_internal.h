@@ -122,6 +122,12 @@ ct_status stream_in_host_chunks(const ct_layer_cfg* cfg, const ct_chunk* chunks,
                                 stream_in_group_fn after_group = nullptr, void* ctx = nullptr);
 // Whether the stream-in kernel leaves the rows of the recompute set alone (it does unless switched off).
 bool stream_in_skips_selected();
+// Whether the last round of the projection's workgroups leaves an eighth of the compute units or more to others.
+bool projection_leaves_units(const ct_layer_cfg* cfg, int32_t n_sel);
+// Whether the projection may run beside the rotation of these chunks: no source lies in what the projection
+// writes - the layer buffers of n_ctx rows, except a chunk that stands in its own place, and the workspace.
+bool move_beside_projection(const ReropeChunks& m, const void* k_buf, const void* v_buf, size_t row_bytes, int32_t n_ctx,
+                            const void* workspace, size_t workspace_bytes);
 ct_status launch_scatter(const ct_layer_cfg* cfg, void* k_buf, void* v_buf, const void* k_sel, const void* v_sel,
                          const int32_t* sel_idx, int32_t n_sel, hipStream_t s);
 // pos_of_row != NULL: position of selected token s is pos_of_row[s]; otherwise it is looked up
@@ -134,8 +140,10 @@ struct ChunkTable {
 ct_status launch_qkv(const ct_layer_cfg* cfg, const void* hidden, const int32_t* hidden_rows, const int32_t* sel_pos,
                      const int32_t* sel_idx, const ChunkTable* chunks, int32_t n_sel, const void* wqkv,
                      const void* bias, void* q_out, void* k_out, void* v_out, hipStream_t s,
-                     const int32_t* kv_rows = nullptr);   // kv_rows != NULL: keys and values of selected row t go
+                     const int32_t* kv_rows = nullptr,    // kv_rows != NULL: keys and values of selected row t go
                                                           // to row kv_rows[t] of k_out / v_out (the layer buffers)
+                     // move != NULL: device chunks brought into k_buf / v_buf by the same launch
+                     const ReropeChunks* move = nullptr, void* k_buf = nullptr, void* v_buf = nullptr);
 // out[t, :] = x[t, :] * w^T (+ residual[t, :]);  x [n_tok, k_len], w [n_out, k_len], bf16
 // ws (optional, linear_workspace_bytes() bytes): scratch that lets a launch whose last round of
 // workgroups would leave most compute units idle split the reduction of those tiles.  n_cu: the

@@ -331,14 +331,16 @@ ct_status ct_partial_prefill_stack_tap(const ct_layer_cfg* cfg, int32_t ffn_dim,
     bool host_here = false;
     for (int c = 0; c < n_chunks && !full; ++c) host_here |= lw.chunks[c].location != 0;
     const bool direct = full || !host_here || (streamed[l & 1] && stream_in_skips_selected());
+    ReropeChunks rc;   // what fits one table rides on the projection's launch
+    memset(&rc, 0, sizeof(rc));
     if (!full) {
-      ReropeChunks rc;
-      memset(&rc, 0, sizeof(rc));
-      auto flush = [&]() -> ct_status {
-        if (rc.n == 0) return CT_OK;
+      auto close = [&]() {
         rc.tok_start[rc.n] = rc.total_tokens;
-        rc.skip_rows = sel_idx;   // the projection's epilogue (or the scatter) overwrites these rows next
+        rc.skip_rows = sel_idx;   // the projection's epilogue (or the scatter) writes these rows
         rc.n_skip = n_sel;
+      };
+      auto flush = [&]() -> ct_status {
+        close();
         ct_status r = launch_rerope_chunks(cfg, kb, vb, &rc, 0, cs);
         rc.n = 0;
         rc.total_tokens = 0;
@@ -347,6 +349,7 @@ ct_status ct_partial_prefill_stack_tap(const ct_layer_cfg* cfg, int32_t ffn_dim,
       for (int c = 0; c < n_chunks; ++c) {
         const ct_chunk& ch = lw.chunks[c];
         if (ch.location != 0) continue;
+        if (rc.n == 32 && (st = flush()) != CT_OK) return st;
         const int i = rc.n++;
         rc.tok_start[i] = rc.total_tokens;
         rc.total_tokens += ch.n_tokens;
@@ -355,14 +358,17 @@ ct_status ct_partial_prefill_stack_tap(const ct_layer_cfg* cfg, int32_t ffn_dim,
         rc.row_start[i] = tab.row_start[c];
         rc.delta0[i] = ch.raw_keys ? ch.new_pos_start : ch.new_pos_start - ch.old_pos_start;
         rc.delta_step[i] = ch.raw_keys ? 1 : 0;
-        if (rc.n == 32 && (st = flush()) != CT_OK) return st;
       }
-      if ((st = flush()) != CT_OK) return st;
+      close();
+      if (rc.n > 0 && (!projection_leaves_units(cfg, n_sel) || !move_beside_projection(rc, kb, vb, row_bytes, n_ctx, workspace, workspace_bytes)) &&
+          (st = flush()) != CT_OK)
+        return st;
     }
+    const ReropeChunks* move = rc.n > 0 ? &rc : nullptr;
     if ((st = direct ? launch_qkv(cfg, ws + L.x_norm, nullptr, nullptr, sel_idx, &tab, n_sel, lw.wqkv, nullptr, ws + L.q, kb, vb,
-                                  cs, sel_idx)
+                                  cs, sel_idx, move, kb, vb)
                      : launch_qkv(cfg, ws + L.x_norm, nullptr, nullptr, sel_idx, &tab, n_sel, lw.wqkv, nullptr, ws + L.q,
-                                  ws + L.k, ws + L.v, cs)) != CT_OK)
+                                  ws + L.k, ws + L.v, cs, nullptr, move, kb, vb)) != CT_OK)
       return st;
     if (!full) {
       if (streamed[l & 1] && (e = hipStreamWaitEvent(cs, landed(l, 0), 0)) != hipSuccess)
