@@ -211,7 +211,9 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
                                    size_t workspace_bytes, void* compute_stream, void* copy_stream);
 
 /* Scratch bytes ct_selected_attention / ct_partial_prefill_layer need for this problem
- * size (0 on invalid arguments). */
+ * size (0 on invalid arguments).  For few selected rows the amount includes room for splitting
+ * the key range over more workgroups; a call with less, down to what it cannot do without, splits
+ * less and takes longer. */
 size_t ct_workspace_bytes(const ct_layer_cfg* cfg, int32_t n_ctx, int32_t n_sel);
 
 /* Optional extra workspace of ct_partial_prefill_layer for layers whose chunks come from host

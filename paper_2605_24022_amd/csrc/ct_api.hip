@@ -142,6 +142,31 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
   return p;
 }
 
+// With few (tile, head) pairs a launch lasts as long as one workgroup takes to walk its keys, 1.4 us per 64 of
+// them.  Up to half a round of pairs is split further, into one round of workgroups over at least 256 keys
+// each, as far as the scratch goes; from there on a second round costs what the shorter walk gains.
+// (A partial result also goes through memory: contexts up to 512 keys stay whole.)  Layer calls, split against
+// whole: tiny model, 1024 tokens, 153 rows 28.7 / 34.3 us, 2048 tokens, 102 rows 32 / 54 us; Llama-3-8B 2048 tokens,
+// 20 rows 62 / 89 us, 1024 rows (128 pairs) 92 / 100 us, 8192 tokens, 81 rows 88 / 103 us.
+AttnPlan plan_attention_within(const ct_layer_cfg* cfg, int n_ctx, int n_sel, size_t scratch_bytes) {
+  AttnPlan p = plan_attention(cfg, n_ctx, n_sel);
+  const long pairs = (long)p.n_tiles * cfg->n_kv_heads;
+  if (pairs <= 0 || pairs > kNumCUs / 2 || n_ctx <= 512) return p;
+  const size_t per_split = (size_t)pairs * 256 * (size_t)(cfg->head_dim + 2) * sizeof(float);
+  long want = kNumCUs / pairs;
+  if (want > (long)(scratch_bytes / per_split)) want = (long)(scratch_bytes / per_split);
+  if (want < 2) return p;
+  int keys = (int)((n_ctx + want - 1) / want);
+  keys = (keys + 63) / 64 * 64;
+  if (keys < 256) keys = 256;
+  const int ns = (n_ctx + keys - 1) / keys;
+  if (ns <= p.n_splits) return p;
+  p.n_splits = ns;
+  p.split_keys = keys;
+  p.ws_bytes = ns * per_split;
+  return p;
+}
+
 size_t attention_scratch_bytes(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
   return plan_attention(cfg, n_ctx, n_sel).ws_bytes;
 }
@@ -399,15 +424,19 @@ ct_status ct_validate_indices(const int32_t* host_idx, int32_t n_sel, int32_t n_
   return check_indices_host(host_idx, n_sel, n_ctx);
 }
 
-size_t ct_workspace_bytes(const ct_layer_cfg* cfg, int32_t n_ctx, int32_t n_sel) {
-  if (check_cfg(cfg) != CT_OK || n_ctx <= 0 || n_sel < 0 || n_sel > n_ctx) return 0;
-  // selected-row attention partials (if the key range is split) + the layer call's staging of
-  // recomputed q, k, v rows, each region 256-byte aligned
-  AttnPlan p = plan_attention(cfg, n_ctx, n_sel);
+// selected-row attention partials (if the key range is split) + the layer call's staging of
+// recomputed q, k, v rows, each region 256-byte aligned
+static size_t staging_bytes(const ct_layer_cfg* cfg, int32_t n_sel) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t q = up((size_t)n_sel * cfg->n_q_heads * cfg->head_dim * 2);
   const size_t kv = up((size_t)n_sel * cfg->n_kv_heads * cfg->head_dim * 2);
-  return up(p.ws_bytes) + q + 2 * kv + 256;
+  return q + 2 * kv + 256;
+}
+
+size_t ct_workspace_bytes(const ct_layer_cfg* cfg, int32_t n_ctx, int32_t n_sel) {
+  if (check_cfg(cfg) != CT_OK || n_ctx <= 0 || n_sel < 0 || n_sel > n_ctx) return 0;
+  const AttnPlan p = plan_attention_within(cfg, n_ctx, n_sel, ~(size_t)0);
+  return ((p.ws_bytes + 255) & ~(size_t)255) + staging_bytes(cfg, n_sel);
 }
 
 size_t ct_attention_state_bytes(const ct_layer_cfg* cfg, int32_t n_ctx, int32_t n_sel) {
@@ -515,7 +544,8 @@ ct_status ct_selected_attention(const ct_layer_cfg* cfg, const void* q_sel, cons
       return fail(CT_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, p.ws_bytes);
     if (((uintptr_t)workspace & 255) != 0) return fail(CT_ERR_WORKSPACE, "workspace is not 256-byte aligned");
   }
-  return launch_attention(cfg, q_sel, k_buf, v_buf, n_ctx, sel_idx, n_sel, out, lse, workspace,
+  if (workspace != nullptr && ((uintptr_t)workspace & 255) == 0) p = plan_attention_within(cfg, n_ctx, n_sel, workspace_bytes);
+  return launch_attention(cfg, p, q_sel, k_buf, v_buf, n_ctx, sel_idx, n_sel, out, lse, workspace,
                           static_cast<hipStream_t>(stream));
 }
 
@@ -572,7 +602,8 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
   if (n_sel > 0) {
     if (!hidden || !sel_idx || !wqkv || !attn_out)
       return fail(CT_ERR_NULL, "hidden, sel_idx, wqkv and attn_out must be non-NULL when n_sel > 0");
-    const size_t need = ct_workspace_bytes(cfg, n_ctx, n_sel);
+    // (less than ct_workspace_bytes() will do where that asks for further splits of the key range)
+    const size_t need = ((plan_attention(cfg, n_ctx, n_sel).ws_bytes + 255) & ~(size_t)255) + staging_bytes(cfg, n_sel);
     if (workspace == nullptr) return fail(CT_ERR_WORKSPACE, "workspace is NULL but %zu bytes are needed", need);
     if (workspace_bytes < need) return fail(CT_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     if (((uintptr_t)workspace & 255) != 0) return fail(CT_ERR_WORKSPACE, "workspace is not 256-byte aligned");
@@ -589,8 +620,12 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
   char* ws = static_cast<char*>(workspace);
   void *q_rows = nullptr, *k_rows = nullptr, *v_rows = nullptr;
   float* attn_state = nullptr;
+  AttnPlan plan = {};
   if (n_sel > 0) {
-    AttnPlan p = plan_attention(cfg, n_ctx, n_sel);
+    // the attention of host-pool layers follows the chunk groups, whose launches want whole key ranges
+    plan = any_host ? plan_attention(cfg, n_ctx, n_sel)
+                    : plan_attention_within(cfg, n_ctx, n_sel, (workspace_bytes - staging_bytes(cfg, n_sel)) & ~(size_t)255);
+    const AttnPlan& p = plan;
     size_t off = up(p.ws_bytes);
     q_rows = ws + off;
     off += up((size_t)n_sel * cfg->n_q_heads * cfg->head_dim * 2);
@@ -643,7 +678,7 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
     int host_chunks = 0;
     for (int c = 0; c < n_chunks; ++c) host_chunks += chunks[c].location != 0;
     pipelined = n_sel > 0 && host_chunks >= 2 && stream_in_skips_selected() &&
-                plan_attention(cfg, n_ctx, n_sel).n_splits == 1;
+                plan.n_splits == 1;
     groups.xs = xs;
     groups.ev = ev_pool + 1;
     // Equal groups of chunks.  Without room for the attention state: as many as leave every
@@ -656,7 +691,6 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
     int sizes[8];
     int n_groups = 0;
     if (pipelined) {
-      const AttnPlan plan = plan_attention(cfg, n_ctx, n_sel);
       int G = (int)((int64_t)plan.n_tiles * cfg->n_kv_heads / 200);
       // With room for the attention state a launch takes all unfinished tiles through the keys of
       // one group, so the launches are full whatever the number of groups, and what is left when
@@ -785,7 +819,7 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
       if ((e = hipStreamWaitEvent(cs, groups.ev[j], 0)) != hipSuccess)
         return hip_fail(e, "hipStreamWaitEvent (chunk group streamed in)");
       const int32_t upto = j + 1 == groups.n ? 0x7fffffff : tab.row_start[groups.last_chunk[j] + 1];
-      st = launch_attention(cfg, q_rows, k_buf, v_buf, n_ctx, sel_idx, n_sel, attn_out, nullptr, workspace, cs, seen, upto,
+      st = launch_attention(cfg, plan, q_rows, k_buf, v_buf, n_ctx, sel_idx, n_sel, attn_out, nullptr, workspace, cs, seen, upto,
                             attn_state);
       if (st != CT_OK) return st;
       seen = upto;
@@ -806,7 +840,7 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
   }
   if (n_sel == 0) return CT_OK;
   if (!direct && (st = launch_scatter(cfg, k_buf, v_buf, k_rows, v_rows, sel_idx, n_sel, cs)) != CT_OK) return st;
-  return launch_attention(cfg, q_rows, k_buf, v_buf, n_ctx, sel_idx, n_sel, attn_out, nullptr, workspace, cs);
+  return launch_attention(cfg, plan, q_rows, k_buf, v_buf, n_ctx, sel_idx, n_sel, attn_out, nullptr, workspace, cs);
 }
 
 }  // extern "C"

@@ -506,11 +506,10 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 
 }  // namespace
 
-ct_status launch_attention(const ct_layer_cfg* cfg, const void* q_sel, const void* k_buf, const void* v_buf,
+ct_status launch_attention(const ct_layer_cfg* cfg, const AttnPlan& p, const void* q_sel, const void* k_buf, const void* v_buf,
                            int32_t n_ctx, const int32_t* sel_idx, int32_t n_sel, void* out, float* lse,
                            void* workspace, hipStream_t s, int32_t key_after, int32_t key_upto, float* state) {
   if (n_sel == 0) return CT_OK;
-  const AttnPlan p = plan_attention(cfg, n_ctx, n_sel);
   AttnArgs a;
   a.q = static_cast<const uint16_t*>(q_sel);
   a.k = static_cast<const uint16_t*>(k_buf);

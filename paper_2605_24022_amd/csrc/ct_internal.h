@@ -68,11 +68,13 @@ struct AttnPlan {
   size_t ws_bytes;   // workspace bytes needed
 };
 AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel);
+// The same, with the key range split further where that shortens the launch and scratch_bytes have room for it.
+AttnPlan plan_attention_within(const ct_layer_cfg* cfg, int n_ctx, int n_sel, size_t scratch_bytes);
 // Lowest and highest key row the attention launch over keys [key_after, key_upto) reads (host replay).
 ct_status attention_rows_read(const ct_layer_cfg* cfg, const int32_t* sel_idx_host, int32_t n_sel, int32_t n_ctx,
                               int32_t key_after, int32_t key_upto, bool resumable, int32_t* first_row,
                               int32_t* last_row);
-// Scratch bytes launch_attention needs behind its `workspace` pointer for this problem size.
+// Scratch bytes that plan_attention's plan needs behind launch_attention's `workspace` pointer.
 size_t attention_scratch_bytes(const ct_layer_cfg* cfg, int n_ctx, int n_sel);
 
 // ---- launchers implemented next to their kernels ---------------------------------------
@@ -163,7 +165,7 @@ ct_status launch_rmsnorm(const void* x, const void* w, float eps, int32_t n_tok,
 // state != NULL (attention_state_bytes() bytes): the launch takes every tile that sees keys past
 // key_after through the keys [key_after, key_upto) alone; tiles that need later keys leave their
 // fp32 (O, m, l) in `state`, where the launch for the next key range picks them up.
-ct_status launch_attention(const ct_layer_cfg* cfg, const void* q_sel, const void* k_buf, const void* v_buf,
+ct_status launch_attention(const ct_layer_cfg* cfg, const AttnPlan& plan, const void* q_sel, const void* k_buf, const void* v_buf,
                            int32_t n_ctx, const int32_t* sel_idx, int32_t n_sel, void* out, float* lse,
                            void* workspace, hipStream_t s, int32_t key_after = 0, int32_t key_upto = 0x7fffffff,
                            float* state = nullptr);

@@ -255,6 +255,10 @@ ct_status ct_partial_prefill_stack_tap(const ct_layer_cfg* cfg, int32_t ffn_dim,
   if (workspace == nullptr) return fail(CT_ERR_WORKSPACE, "workspace is NULL but %zu bytes are needed", L.total);
   if (workspace_bytes < L.total) return fail(CT_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, L.total);
   if (((uintptr_t)workspace & 255) != 0) return fail(CT_ERR_WORKSPACE, "workspace is not 256-byte aligned");
+  // the FFN's regions lie idle during the attention: partial results of further splits of its key range go there
+  const AttnPlan base_plan = plan_attention(cfg, n_ctx, n_sel);
+  const AttnPlan plan = plan_attention_within(cfg, n_ctx, n_sel, L.total - 256 - L.act);
+  const size_t attn_ws = plan.n_splits > base_plan.n_splits ? L.act : L.attn_ws;
   if (any_host && !full && compute_stream == copy_stream)
     return fail(CT_ERR_SHAPE, "pinned-host chunks need a copy_stream different from compute_stream");
 
@@ -384,7 +388,7 @@ ct_status ct_partial_prefill_stack_tap(const ct_layer_cfg* cfg, int32_t ffn_dim,
       }
     }
     if (!direct && (st = launch_scatter(cfg, kb, vb, ws + L.k, ws + L.v, sel_idx, n_sel, cs)) != CT_OK) return st;
-    if ((st = launch_attention(cfg, ws + L.q, kb, vb, n_ctx, sel_idx, n_sel, ws + L.attn_out, nullptr, ws + L.attn_ws, cs)) != CT_OK)
+    if ((st = launch_attention(cfg, plan, ws + L.q, kb, vb, n_ctx, sel_idx, n_sel, ws + L.attn_out, nullptr, ws + attn_ws, cs)) != CT_OK)
       return st;
     if ((e = hipEventRecord(attn_done(l), cs)) != hipSuccess) return hip_fail(e, "hipEventRecord (attention done)");
     // output projection + residual, FFN + residual (the residual stream is updated in place).

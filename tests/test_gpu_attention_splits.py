@@ -1,0 +1,59 @@
+"""Attention of few selected rows: the key range is split as far as the workspace goes.  Every amount of scratch,
+from what a call needs at least to what ct_workspace_bytes asks for, gives the same rows, against a plain 64-bit
+softmax; lengths around the limits of the rule, rows that see one key, and rows whose splits are empty."""
+import pytest
+import torch
+
+from paper_2605_24022_amd import binding as B
+from tests.gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    assert torch.cuda.is_available()
+    B.load()
+    torch.cuda.set_device(0)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_ctx,n_sel", [
+    (8, 2, 64, 512, 9), (8, 2, 64, 513, 1), (8, 2, 64, 1024, 153), (32, 8, 128, 1025, 65), (16, 16, 64, 4097, 3),
+    (16, 1, 128, 3000, 200), (32, 8, 128, 8192, 81), (4, 4, 128, 2049, 2000), (32, 2, 128, 700, 700)])
+def test_any_scratch_gives_the_same_rows(hq, hkv, d, n_ctx, n_sel):
+    say(f"attention splits heads={hq}/{hkv} d={d} n_ctx={n_ctx} n_sel={n_sel}")
+    g = torch.Generator(device="cuda").manual_seed(n_ctx + n_sel)
+    cfg = B.make_cfg(64, hq, hkv, d, 1.0e4)
+    q, k, v = (torch.randn(n, h, d, generator=g, device="cuda").to(torch.bfloat16) for n, h in ((n_sel, hq), (n_ctx, hkv), (n_ctx, hkv)))
+    sel = torch.randperm(n_ctx, generator=g, device="cuda")[:n_sel]
+    sel[0] = 0                                   # one key
+    sel = torch.unique(sel).to(torch.int32)      # ascending
+    n_sel = sel.numel()
+    q = q[:n_sel].contiguous()
+    want, size = (torch.empty(n_sel, hq, d, device="cuda", dtype=torch.float64) for _ in range(2))
+    want_lse = torch.empty(n_sel, hq, device="cuda", dtype=torch.float64)
+    hidden = torch.arange(n_ctx, device="cuda")[None, :] > sel[:, None]
+    for h in range(hq):
+        kv = h // (hq // hkv)
+        s = (q[:, h].double() @ k[:, kv].double().T.contiguous() * d ** -0.5).masked_fill(hidden, float("-inf"))
+        want[:, h] = torch.softmax(s, 1) @ v[:, kv].double()
+        size[:, h] = torch.softmax(s, 1) @ v[:, kv].double().abs()
+        want_lse[:, h] = torch.logsumexp(s, 1)
+    most = B.ct_workspace_bytes(cfg, n_ctx, n_sel)
+    ws = torch.empty(most, dtype=torch.uint8, device="cuda")
+    ran = 0
+    for share in (0.0, 0.1, 0.4, 0.7, 1.0):
+        out = torch.full((n_sel, hq, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+        lse = torch.full((n_sel, hq), float("nan"), device="cuda")
+        try:
+            B.ct_selected_attention(cfg, q, k, v, n_ctx, sel, n_sel, out, lse, ws, int(most * share))
+        except B.CacheTuneError:                 # less than the call needs at least
+            assert share < 1.0 and n_ctx > 2048
+            continue
+        ran += 1
+        # probabilities are rounded to bf16 (8 significant bits: by up to 2^-8 of each; their sum is not) and so is the
+        # result; fp32 sums and exponents take the rest
+        err = (out.double() - want).abs()
+        assert (err <= 2.0 ** -8 * (size + want.abs()) + 1e-4 * size).all(), (share, float(err.max()))
+        assert ((lse.double() - want_lse).abs() <= 1e-4).all()
+    assert ran >= 1

@@ -22,7 +22,7 @@ def _rand(g, *shape):
 
 
 def _check(got, want, scale):
-    """One rounding to bf16 (2^-9 of the value) and fp32 sums in another order (K <= 4096 products of
+    """One rounding to bf16 (up to 2^-8 of the value) and fp32 sums in another order (K <= 4096 products of
     size `scale`: 4096 * 2^-24, with a factor of four)."""
     err = (got.float() - want).abs()
     assert torch.isfinite(got).all()
