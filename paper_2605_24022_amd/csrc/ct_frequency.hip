@@ -846,15 +846,18 @@ __device__ __forceinline__ uint32_t score_key(float s) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);             // larger score <=> larger key
 }
 
+// One workgroup per sequence; scores stay in L2, so what counts is the chain of loads, atomics and barriers: loads
+// go out kTopkBatch at a time, scores that share the first byte (nearly all do) are added by one lane, and each
+// wave sweeps a stretch of its own without barriers.  15 % of 32768 scores: 92 -> 38 us, of 4 x 1500 8.4 -> 7.2 us.
+constexpr int kTopkBatch = 8;
 __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ scores, int32_t n, int32_t k,
                                                     int32_t* __restrict__ idx_out) {
   __shared__ uint32_t hist[256];
   __shared__ uint32_t sh_prefix, sh_need;
-  __shared__ uint32_t wave_sum[2][16];
-  __shared__ uint32_t carry[2];
+  __shared__ uint32_t n_above[16], n_tie[16];
   const float* s = scores + (int64_t)blockIdx.x * n;
   int32_t* out = idx_out + (int64_t)blockIdx.x * k;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (k <= 0) return;
   // radix select, most significant byte first: after the loop `prefix` is the key of the k-th
   // largest score and `need` the number of tokens with exactly that key that are still taken
@@ -863,9 +866,27 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
     if (tid < 256) hist[tid] = 0;
     __syncthreads();
     const uint32_t himask = shift == 24 ? 0u : (0xffffffffu << (shift + 8));
-    for (int i = tid; i < n; i += 1024) {
-      const uint32_t key = score_key(s[i]);
-      if ((key & himask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+    for (int i0 = tid; i0 - tid < n; i0 += 1024 * kTopkBatch) {
+      float x[kTopkBatch];
+#pragma unroll
+      for (int b = 0; b < kTopkBatch; ++b) x[b] = i0 + b * 1024 < n ? s[i0 + b * 1024] : 0.f;
+#pragma unroll
+      for (int b = 0; b < kTopkBatch; ++b) {
+        if (i0 - tid + b * 1024 >= n) break;
+        const uint32_t key = score_key(x[b]), bin = (key >> shift) & 255u;
+        bool left = i0 + b * 1024 < n && (key & himask) == prefix;
+        if (shift == 24) {     // the first byte is the same for most: added by one lane for all that share it
+          const uint64_t live = __ballot(left);
+          if (live != 0) {
+            const int first = __ffsll((unsigned long long)live) - 1;
+            const bool same = left && bin == (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
+            const uint64_t who = __ballot(same);
+            if (lane == first) atomicAdd(&hist[bin], (uint32_t)__popcll(who));
+            left = left && !same;
+          }
+        }
+        if (left) atomicAdd(&hist[bin], 1u);
+      }
     }
     __syncthreads();
     if (tid < 64) {
@@ -896,41 +917,48 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
     need = sh_need;
     __syncthreads();
   }
-  // ordered sweep: tokens above the threshold, and the first `need` tokens on it
-  if (tid < 2) carry[tid] = 0;
-  __syncthreads();
-  const int lane = tid & 63, wv = tid >> 6;
-  for (int i0 = 0; i0 < n; i0 += 1024) {
-    const int i = i0 + tid;
-    const uint32_t key = i < n ? score_key(s[i]) : 0u;
-    const bool above = i < n && key > prefix;
-    const bool tie = i < n && key == prefix;
-    const uint64_t tie_ballot = __ballot(tie);
-    const uint32_t tie_before = __popcll(tie_ballot & ((1ull << lane) - 1ull));
-    if (lane == 0) wave_sum[0][wv] = __popcll(tie_ballot);
-    __syncthreads();
-    uint32_t tie_off = carry[0];
-    for (int q = 0; q < wv; ++q) tie_off += wave_sum[0][q];
-    const bool take = above || (tie && tie_off + tie_before < need);
-    const uint64_t take_ballot = __ballot(take);
-    const uint32_t take_before = __popcll(take_ballot & ((1ull << lane) - 1ull));
-    if (lane == 0) wave_sum[1][wv] = __popcll(take_ballot);
-    __syncthreads();
-    uint32_t take_off = carry[1];
-    for (int q = 0; q < wv; ++q) take_off += wave_sum[1][q];
-    if (take) out[take_off + take_before] = i;
-    __syncthreads();
-    if (tid == 0) {
-      uint32_t a = 0, b = 0;
-      for (int q = 0; q < 16; ++q) {
-        a += wave_sum[0][q];
-        b += wave_sum[1][q];
+  // ordered sweep: tokens above the threshold, and the first `need` tokens on it.  Wave w owns one
+  // stretch of tokens; it counts both kinds, and what the waves before it hold says where it writes.
+  const int stretch = (n + 1023) / 1024 * 64, begin = wv * stretch, end = min(n, begin + stretch);
+  auto sweep = [&](auto&& body) __attribute__((always_inline)) {
+    for (int i0 = begin; i0 < end; i0 += 64 * kTopkBatch) {
+      float x[kTopkBatch];
+#pragma unroll
+      for (int b = 0; b < kTopkBatch; ++b) x[b] = i0 + b * 64 + lane < end ? s[i0 + b * 64 + lane] : 0.f;
+#pragma unroll
+      for (int b = 0; b < kTopkBatch; ++b) {
+        if (i0 + b * 64 >= end) break;
+        const int i = i0 + b * 64 + lane;
+        const uint32_t key = score_key(x[b]);
+        body(i, i < end && key > prefix, i < end && key == prefix);
       }
-      carry[0] += a;
-      carry[1] += b;
     }
-    __syncthreads();
+  };
+  uint32_t above_here = 0, ties_here = 0;
+  sweep([&](int, bool above, bool tie) __attribute__((always_inline)) {
+    above_here += __popcll(__ballot(above));
+    ties_here += __popcll(__ballot(tie));
+  });
+  if (lane == 0) {
+    n_above[wv] = above_here;
+    n_tie[wv] = ties_here;
   }
+  __syncthreads();
+  uint32_t ties = 0, at = 0;
+  for (int q = 0; q < wv; ++q) {
+    ties += n_tie[q];
+    at += n_above[q];
+  }
+  at += min(ties, need);
+  const uint64_t before = (1ull << lane) - 1ull;
+  sweep([&](int i, bool above, bool tie) __attribute__((always_inline)) {
+    const uint64_t tie_lanes = __ballot(tie);
+    const bool take = above || (tie && ties + __popcll(tie_lanes & before) < need);
+    const uint64_t take_lanes = __ballot(take);
+    if (take) out[at + __popcll(take_lanes & before)] = i;
+    ties += __popcll(tie_lanes);
+    at += __popcll(take_lanes);
+  });
 }
 
 // ---- host side ------------------------------------------------------------------------------
