@@ -102,9 +102,9 @@ __device__ __forceinline__ void tile_of(int v, int nF, int nT, int* f_tile, int*
   *t_tile = tp * PT + r2 / fw;
 }
 
-// EPI_SWIGLU: the 128 A rows of a wave are 64 gate rows followed by the 64 up rows of the same
-// output features, so gate and up of one (feature, token) land in the same lane and register
-// index of accumulator tiles (m, m + 2) - the same pairing the half-split RoPE uses.
+// EPI_SWIGLU: 128 A rows are 64 gate rows followed by the 64 up rows of the same
+// output features, and a wave owns both, so gate and up of one (feature, token) land in the same lane and register
+// index of accumulator tiles 64 rows apart - the same pairing the half-split RoPE uses.
 template <int EPI, int D, int STYLE, int NB, int NW>
 __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTable& rope, const ChunkTable& chunks,
                                                unsigned char* lds) {
