@@ -10,21 +10,25 @@
 // a lane holds one token (column) and groups of four consecutive features (rows):
 //   - both elements of every RoPE pair of a token sit in the same lane (no cross-lane
 //     traffic in the epilogue), and the token's position is a per-lane scalar;
-//   - results leave as 8-byte stores of four consecutive bf16 features.
+//   - results leave as 16-byte stores of eight consecutive bf16 features (two half waves swap halves).
 // Both operands are K-contiguous in memory (W is out-features major, X is token major).
 // Tiles go from global memory straight into LDS (global_load_lds_dwordx4, no register
 // staging): a wave-wide load fills 8 rows of 128 bytes, the 16-byte pieces of a row are
 // XOR-swizzled so that the 128-bit fragment reads of 16 consecutive rows hit distinct banks.
 //
-// Workgroup tile: 256 features x 256 (or 128) tokens x 64 (K step), 32 x 32 x 16 MFMAs.  Reading the
-// fragments from LDS takes about as long as multiplying them, so the wave tiles are as square as the
-// registers allow: 64 x 64 for eight waves on 128 tokens (128 x 32 read a quarter more: QKV of 1228 rows
-// 67 -> 63 us, of 153 rows 47 -> 39 us), 128 x 64 for eight waves on 256 tokens, 128 x 128 for four.
+// Workgroup: 512 threads = 8 waves, two to a SIMD; tile 256 features x 256 (or 128) tokens x 64 (K step),
+// 32 x 32 x 16 MFMAs.  Reading the fragments from LDS takes about as long as multiplying them, so the wave tiles are
+// as square as the registers of two waves allow: 64 x 64 on 128 tokens (128 x 32 read a quarter more: QKV of 1228 rows
+// 67 -> 63 us, of 153 rows 47 -> 39 us), 128 x 64 on 256 tokens.
 // LDS holds three weight tiles and two (of 128 tokens: three) token tiles: loads run two and one
-// (two) K steps ahead.  One barrier per K step, placed inside the step's last MFMA group so
-// that it passes while the matrix core is busy; fragment reads and tile loads go out one by one between
-// the MFMAs where a wave has the matrix core to itself or the tile is small (sent in bursts ahead of each group
-// of MFMAs they held it up: gate/up, K = 4096, n = 1638: 400 -> 350 us together with the 64 x 64 tiles).
+// (two) K steps ahead.  One barrier per K step, ahead of the step's last MFMA group so
+// that it passes while the matrix core is busy.  On 128-token tiles fragment reads and tile loads go out one by one
+// between the MFMAs (sent in bursts ahead of each group of MFMAs they held it up: gate/up, K = 4096, n = 1638:
+// 400 -> 350 us together with the 64 x 64 tiles); on 256-token tiles they stay in bursts.
+// Not kept on 256-token tiles: four waves with 128 x 128 each, which read a third less from LDS but have one wave to
+// hide an epilogue behind (and with a residual spill): linear 2458 x 4096 x 4096 with weights from memory 107 us against
+// 101, 4915 x 2048 x 2048 71 / 63, gate/up 4915 x 4096 x 14336 924 / 919; only from reductions of 8192 on are they ahead
+// (4915 x 8192 x 28672 3594 / 3636).  Read-behind-MFMA there: linear 2458 x 4096 x 4096 107 against 101 us as well.
 // Workgroups are numbered so that the ones resident on one XCD (ids congruent mod 8) cover a
 // patch of neighbouring tiles and share their W and X tiles in that XCD's L2.
 #include <string.h>
@@ -38,9 +42,10 @@ namespace ct {
 
 namespace {
 
+constexpr int kGemmThreads = 512;
 constexpr int BF = 256;           // features per workgroup
-// tokens per workgroup: 128 * NB, NB = MFMA column tiles per wave (template parameter; 2 unless the
-// grid would otherwise end in a mostly empty last round of workgroups)
+// tokens per workgroup: 128 * NB (template parameter; 2 unless the grid would otherwise end in a mostly empty last
+// round of workgroups)
 constexpr int BK = 64;            // reduction elements per stage
 constexpr int ROWB = BK * 2;      // LDS row in bytes (unpadded, swizzled)
 constexpr int A_BYTES = BF * ROWB;
@@ -105,13 +110,13 @@ __device__ __forceinline__ void tile_of(int v, int nF, int nT, int* f_tile, int*
 // EPI_SWIGLU: 128 A rows are 64 gate rows followed by the 64 up rows of the same
 // output features, and a wave owns both, so gate and up of one (feature, token) land in the same lane and register
 // index of accumulator tiles 64 rows apart - the same pairing the half-split RoPE uses.
-template <int EPI, int D, int STYLE, int NB, int NW>
+template <int EPI, int D, int STYLE, int NB>
 __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTable& rope, const ChunkTable& chunks,
                                                unsigned char* lds) {
-  constexpr int NWAVES = NW;                 // 8: two waves per SIMD; 4: one
+  constexpr int NWAVES = kGemmThreads / 64;  // two per SIMD
   constexpr int A_LOADS = BF / 8 / NWAVES;   // wave-wide loads (8 rows each) per wave and stage
   constexpr int BT = 128 * NB;
-  constexpr int WF = NB == 1 ? 4 : 2, WT = NW / WF;   // waves along features and tokens
+  constexpr int WF = NB == 1 ? 4 : 2, WT = NWAVES / WF;   // waves along features and tokens
   constexpr int FM = BF / 32 / WF, TW = BT / 32 / WT; // 32 x 32 MFMA tiles per wave
   // tile row of feature tile m of wave wf: FM = 4 owns 128 consecutive rows; FM = 2 owns 32 rows and,
   // where the epilogue pairs rows 64 apart (gate with up, halves of a 128-wide head), the 32 that go with them
@@ -162,8 +167,7 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0), "v"(byte_off), "s"(base) : "memory", "m0");
   };
-  // A (weight) tiles cycle through three LDS slots, B (token) tiles through two.  `half` selects
-  // the first or second half of a tile's loads.
+  // A (weight) tiles cycle through A_SLOTS LDS slots, B (token) tiles through B_SLOTS; j is one of a tile's loads.
   auto issue_a1 = [&](int k0, int slot, int j) __attribute__((always_inline)) {
     // scalar bases advanced to the K step; a wave-wide load covers 8 consecutive tile rows: all gate or all up
     const bool up = EPI == EPI_SWIGLU && ((((NWAVES * j + wave) * 8) >> 6) & 1);
@@ -208,9 +212,9 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
   // everything but the newest loads - A(kt + 2), and B(kt + 2) with three slots - is waited for.  Past the end the last
   // step is loaded again into the free slots, which keeps the number of loads in flight, and the
   // wait, uniform.
-  // The workgroup barrier of a step sits near the start of its last MFMA group, not after it: a wave waits
+  // The workgroup barrier of a step sits ahead of its last MFMA group, not after it: a wave waits
   // for its loads of the next step, meets the others, and the first fragment reads of the
-  // next step go out between the MFMAs left of this one, so the barrier and the
+  // next step go out ahead of that group (or between its MFMAs), so the barrier and the
   // LDS latency that follows it pass while the matrix core still has work.  (All waves of
   // a workgroup stand at the barrier together, so the other wave of the SIMD cannot cover it.)
   // this workgroup's part of the reduction: K steps kbeg .. kbeg + nk - 1
@@ -228,17 +232,11 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
   if (B_SLOTS == 3) issue_b(k1, 1);
   issue_a(k1, 1);
   int sa = 0, sb = 0;
-  // Two register sets of fragments: those of MFMA group ks + 1 are read while group ks runs, one read
-  // behind each MFMA, and the tile loads go out between them, so that no burst of memory instructions
-  // holds up the matrix core of a wave.
+  // Two register sets of fragments: those of MFMA group ks + 1 are read while group ks runs.
   bf16x8 fa[2][FM], fb[2][TW];
   constexpr int G = FM * TW, R = FM + TW;    // MFMAs and fragment reads of a group
   constexpr int KG = BK / 16;
-  // Two waves per SIMD on 256-token tiles take turns instead: loads and reads ahead of a group of MFMAs
-  // (one by one: QKV of 1638 gathered rows in the layer 94 -> 104 us, of 16384 rows 670 -> 682 us).
-  constexpr bool AHEAD_OF_GROUP = NB == 2 && NW == 8;
-  constexpr int BAR_AT = AHEAD_OF_GROUP ? 0 : G / 8;              // MFMAs of a step's last group that go ahead of its barrier
-  static_assert(R <= G, "a read behind every MFMA");
+  constexpr int HALF = A_LOADS / 2;
   auto read_frag = [&](const unsigned char* a_base, const unsigned char* b_base, int ks, int set, int r) __attribute__((always_inline)) {
     if (r < TW) fb[set][r] = *reinterpret_cast<const bf16x8*>(b_base + b_frag[ks] + r * 32 * ROWB);
     else fa[set][r - TW] = *reinterpret_cast<const bf16x8*>(a_base + a_frag[ks] + (r - TW) * MROW * ROWB);
@@ -251,59 +249,81 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
   __syncthreads();                         // everybody's have
 #pragma unroll
   for (int r = 0; r < R; ++r) read_frag(lds, lds + A_SLOTS * A_BYTES, 0, 0, r);
-  for (int kt = 0; kt < nk; ++kt) {
-    const unsigned char* a_base = lds + sa * A_BYTES;
-    const unsigned char* b_base = lds + A_SLOTS * A_BYTES + sb * B_BYTES;
-    const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slot of step kt - 1
-    const int sb_free = sb == 0 ? B_SLOTS - 1 : sb - 1;
-    const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1, sb_next = sb == B_SLOTS - 1 ? 0 : sb + 1;
-    const int kb1 = kbase + min(kt + B_SLOTS - 1, nk - 1) * BK, ka2 = kbase + min(kt + 2, nk - 1) * BK;
+  if constexpr (NB == 2) {
+    // The two waves of a SIMD take turns: one sends a group's loads and reads while the other multiplies (one by one
+    // between the MFMAs: QKV of 1638 gathered rows in the layer 94 -> 104 us, of 16384 rows 670 -> 682 us).  This loop
+    // and the one for 128-token tiles stay apart: written as one, with the order chosen by a constant, the compiler
+    // formed the LDS addresses of the loads one from the other and reads of cold weights took 3 to 10 % longer (QKV of
+    // 1638 rows 93 -> 96 us, linear 2458 x 14336 x 4096 287 -> 318 us).
+    auto read_group = [&](const unsigned char* a_base, const unsigned char* b_base, int ks, int set) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < KG - 1; ++ks) {
-      constexpr int HALF = A_LOADS / 2;
-      static_assert(A_LOADS <= G && B_LOADS <= G, "a load behind every MFMA");
-      // tile loads, B first: it is needed a step earlier
-      auto load_tile = [&](int i) __attribute__((always_inline)) {
-        if (ks == 0 && i < B_LOADS) issue_b1(kb1, sb_free, i);
-        if (ks > 0 && i < HALF) issue_a1(ka2, sa_free, (ks - 1) * HALF + i);
-      };
-      if (AHEAD_OF_GROUP) {
+      for (int r = 0; r < R; ++r) read_frag(a_base, b_base, ks, set, r);
+    };
+    auto mfma_group = [&](int set) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < B_LOADS; ++i) load_tile(i);
+      for (int i = 0; i < G; ++i) mfma(set, i);
+    };
+    for (int kt = 0; kt < nk; ++kt) {
+      const unsigned char* a_base = lds + sa * A_BYTES;
+      const unsigned char* b_base = lds + A_SLOTS * A_BYTES + sb * B_BYTES;
+      const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slot of step kt - 1
+      const int sb_free = sb ^ 1;
+      const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1;
+      const int kb1 = kbase + min(kt + 1, nk - 1) * BK, ka2 = kbase + min(kt + 2, nk - 1) * BK;
 #pragma unroll
-        for (int r = 0; r < R; ++r) read_frag(a_base, b_base, ks + 1, (ks + 1) & 1, r);
+      for (int ks = 0; ks < KG - 1; ++ks) {
+        if (ks == 0) issue_b(kb1, sb_free);     // B first: it is needed a step earlier
+#pragma unroll
+        for (int j = 0; j < HALF; ++j)
+          if (ks > 0) issue_a1(ka2, sa_free, (ks - 1) * HALF + j);
+        read_group(a_base, b_base, ks + 1, (ks + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_group(ks & 1);
         __builtin_amdgcn_sched_barrier(0);
       }
+      __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // vmcnt(AHEAD): this wave's loads of step kt + 1 have
+                                                          // landed; lgkmcnt(0): its fragment reads of step kt are done
+      __syncthreads();                         // everybody's have; everybody is done reading step kt
+      read_group(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_free * B_BYTES, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_group((KG - 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
+      sa = sa_next;
+      sb = sb_free;
+    }
+  } else {
+    // a read behind each MFMA, and the tile loads between them, so that no burst of memory instructions holds up
+    // the matrix core of a wave
+    static_assert(R <= G && HALF <= G && B_LOADS <= G, "a read and a load behind every MFMA");
+    for (int kt = 0; kt < nk; ++kt) {
+      const unsigned char* a_base = lds + sa * A_BYTES;
+      const unsigned char* b_base = lds + A_SLOTS * A_BYTES + sb * B_BYTES;
+      const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slots of step kt - 1
+      const int sb_free = sb == 0 ? B_SLOTS - 1 : sb - 1;
+      const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1, sb_next = sb == B_SLOTS - 1 ? 0 : sb + 1;
+      const int kb1 = kbase + min(kt + B_SLOTS - 1, nk - 1) * BK, ka2 = kbase + min(kt + 2, nk - 1) * BK;
+#pragma unroll
+      for (int ks = 0; ks < KG - 1; ++ks) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+          mfma(ks & 1, i);
+          if (i < R) read_frag(a_base, b_base, ks + 1, (ks + 1) & 1, i);
+          if (ks == 0 && i < B_LOADS) issue_b1(kb1, sb_free, i);     // B first: it is needed a step earlier
+          if (ks > 0 && i < HALF) issue_a1(ka2, sa_free, (ks - 1) * HALF + i);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // as above
+      __syncthreads();
 #pragma unroll
       for (int i = 0; i < G; ++i) {
-        mfma(ks & 1, i);
-        if (AHEAD_OF_GROUP) continue;
-        if (i < R) read_frag(a_base, b_base, ks + 1, (ks + 1) & 1, i);
-        load_tile(i);
+        mfma((KG - 1) & 1, i);
+        if (i < R) read_frag(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_next * B_BYTES, 0, 0, i);
         __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
+      sa = sa_next;
+      sb = sb_next;
     }
-#pragma unroll
-    for (int i = 0; i < BAR_AT; ++i) mfma((KG - 1) & 1, i);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // vmcnt(AHEAD): this wave's loads of step kt + 1 have
-                                                        // landed; lgkmcnt(0): its fragment reads of step kt are done
-    __syncthreads();                         // everybody's have; everybody is done reading step kt
-#pragma unroll
-    for (int r = 0; r < (AHEAD_OF_GROUP ? R : 0); ++r) read_frag(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_next * B_BYTES, 0, 0, r);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = BAR_AT; i < G; ++i) {
-      mfma((KG - 1) & 1, i);
-      if (AHEAD_OF_GROUP) continue;
-      if (i - BAR_AT < R) read_frag(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_next * B_BYTES, 0, 0, i - BAR_AT);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int r = AHEAD_OF_GROUP ? R : G - BAR_AT; r < R; ++r) read_frag(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_next * B_BYTES, 0, 0, r);
-    sa = sa_next;
-    sb = sb_next;
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);   // the repeated loads of the last steps have landed before the LDS is released
 
@@ -343,56 +363,50 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
   } else if constexpr (EPI == EPI_LINEAR) {
     const int f0 = f_blk + row0;
     // Residuals arrive the same way, as 16-byte loads of the lane's eight features, and are swapped
-    // back into the accumulator layout.  Those of all the wave's token tiles (one tile at a time where four waves
-    // hold four each: registers) are fetched before the first result is stored: `out` may be the
-    // residual buffer itself, so the compiler cannot move these loads above stores on its own, and with
-    // few loads in flight per lane the epilogue is bound by memory latency.
-    constexpr int NG = TW > 2 ? 1 : TW;       // token tiles whose residuals are in flight together
-    u32x4 res[NG][FM][2];
+    // back into the accumulator layout.  All residual values of the wave's tile are fetched before
+    // the first result is stored: `out` may be the residual buffer itself, so the compiler cannot
+    // move these loads above stores on its own, and with few loads in flight per lane the epilogue
+    // is bound by memory latency.
+    u32x4 res[TW][FM][2];
+    if (a.residual != nullptr) {
 #pragma unroll
-    for (int n0 = 0; n0 < TW; n0 += NG) {
-      if (a.residual != nullptr) {
-#pragma unroll
-        for (int n = 0; n < NG; ++n) {
-          const int t = min(t_blk + wt * 32 * TW + (n0 + n) * 32 + l32, a.n_sel - 1);
-#pragma unroll
-          for (int m = 0; m < FM; ++m) {
-            const int fm = min(f0 + m * MROW, a.O - 32);
-            const size_t row = (size_t)t * a.O + fm + 8 * hi;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) res[n][m][q] = *reinterpret_cast<const u32x4*>(a.residual + row + 16 * q);
-          }
-        }
-      }
-      if (NG < TW) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int n = n0; n < n0 + NG; ++n) {
-        const int t = t_blk + wt * 32 * TW + n * 32 + l32;
-        const bool t_ok = t < a.n_sel;
+      for (int n = 0; n < TW; ++n) {
+        const int t = min(t_blk + wt * 32 * TW + n * 32 + l32, a.n_sel - 1);
 #pragma unroll
         for (int m = 0; m < FM; ++m) {
-          const int fm = f0 + m * MROW;
-          if (fm >= a.O) continue;            // uniform for the wave
-          if (a.residual != nullptr) {
+          const int fm = min(f0 + m * MROW, a.O - 32);
+          const size_t row = (size_t)t * a.O + fm + 8 * hi;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              // r[0], r[1]: features +0..3 of the lane's eight, r[2], r[3]: +4..7
-              const u32x4 r = res[n - n0][m][q];
-              const auto d0 = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);   // dword 0 of groups 2q, 2q + 1
-              const auto d1 = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);   // dword 1
+          for (int q = 0; q < 2; ++q) res[n][m][q] = *reinterpret_cast<const u32x4*>(a.residual + row + 16 * q);
+        }
+      }
+    }
 #pragma unroll
-              for (int e = 0; e < 2; ++e) {
-                const int i0 = 4 * (2 * q + e);
-                acc[m][n][i0 + 0] += bf16_lo(d0[e]);
-                acc[m][n][i0 + 1] += bf16_hi(d0[e]);
-                acc[m][n][i0 + 2] += bf16_lo(d1[e]);
-                acc[m][n][i0 + 3] += bf16_hi(d1[e]);
-              }
+    for (int n = 0; n < TW; ++n) {
+      const int t = t_blk + wt * 32 * TW + n * 32 + l32;
+      const bool t_ok = t < a.n_sel;
+#pragma unroll
+      for (int m = 0; m < FM; ++m) {
+        const int fm = f0 + m * MROW;
+        if (fm >= a.O) continue;            // uniform for the wave
+        if (a.residual != nullptr) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            // r[0], r[1]: features +0..3 of the lane's eight, r[2], r[3]: +4..7
+            const u32x4 r = res[n][m][q];
+            const auto d0 = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);   // dword 0 of groups 2q, 2q + 1
+            const auto d1 = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);   // dword 1
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const int i0 = 4 * (2 * q + e);
+              acc[m][n][i0 + 0] += bf16_lo(d0[e]);
+              acc[m][n][i0 + 1] += bf16_hi(d0[e]);
+              acc[m][n][i0 + 2] += bf16_lo(d1[e]);
+              acc[m][n][i0 + 3] += bf16_hi(d1[e]);
             }
           }
-          store_tile(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, acc[m][n], t_ok);
-          if (NG < TW) __builtin_amdgcn_sched_barrier(0);
         }
+        store_tile(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, acc[m][n], t_ok);
       }
     }
     return;
@@ -491,11 +505,11 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
   }
 }
 
-template <int EPI, int D, int STYLE, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void gemm_kernel(
+template <int EPI, int D, int STYLE, int NB>
+__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_kernel(
     GemmArgs a, RopeTable rope, ChunkTable chunks) {
   __shared__ __align__(1024) unsigned char lds[gemm_lds_bytes(NB)];
-  gemm_workgroup<EPI, D, STYLE, NB, NW>(a, rope, chunks, lds);
+  gemm_workgroup<EPI, D, STYLE, NB>(a, rope, chunks, lds);
 }
 
 // The projection with the rotation of the device-resident chunks in the same launch: workgroups from
@@ -503,19 +517,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 // is what `move` skips) and different limits (matrix cores, memory), and the rotation runs on the compute units that
 // the projection's last round leaves idle instead of in a launch of its own before it.  Few tokens per workgroup:
 // with four times as many, fetched all heads at once, one waits for the last of them (8192 tokens, 1228 rows 208 -> 215 us).
-constexpr int kMoveThreads = 512;
 template <int D, int STYLE, int NB>
-__global__ __launch_bounds__(kMoveThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void qkv_move_kernel(
+__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void qkv_move_kernel(
     GemmArgs a, RopeTable rope, ChunkTable chunks, ReropeChunks move, uint16_t* k_buf, uint16_t* v_buf, int32_t move_after) {
   __shared__ __align__(1024) unsigned char lds[gemm_lds_bytes(NB)];
   if ((int)blockIdx.x >= move_after) {
     const int block = blockIdx.x - move_after, blocks = gridDim.x - move_after;
-    if (a.Hkv == 8) rerope_chunk_tokens<D, STYLE, 8, true>(k_buf, v_buf, 8, rope, move, kMoveThreads, block, blocks);
-    else if (a.Hkv == 2) rerope_chunk_tokens<D, STYLE, 2, true>(k_buf, v_buf, 2, rope, move, kMoveThreads, block, blocks);
-    else rerope_chunk_tokens<D, STYLE, 0, true>(k_buf, v_buf, a.Hkv, rope, move, kMoveThreads, block, blocks);
+    if (a.Hkv == 8) rerope_chunk_tokens<D, STYLE, 8, true>(k_buf, v_buf, 8, rope, move, kGemmThreads, block, blocks);
+    else if (a.Hkv == 2) rerope_chunk_tokens<D, STYLE, 2, true>(k_buf, v_buf, 2, rope, move, kGemmThreads, block, blocks);
+    else rerope_chunk_tokens<D, STYLE, 0, true>(k_buf, v_buf, a.Hkv, rope, move, kGemmThreads, block, blocks);
     return;
   }
-  gemm_workgroup<EPI_QKV_ROPE, D, STYLE, NB, 8>(a, rope, chunks, lds);
+  gemm_workgroup<EPI_QKV_ROPE, D, STYLE, NB>(a, rope, chunks, lds);
 }
 
 // Sum of the k_parts partial tiles of EPI_PARTIAL (+ residual), rounded to bf16 and written to
@@ -570,11 +583,11 @@ static int pick_nb(const GemmArgs& a, bool swiglu) {
 }
 
 template <typename Kernel>
-static ct_status launch_gemm(Kernel kernel, int threads, const GemmArgs& a, const RopeTable& rope, const ChunkTable& tab,
+static ct_status launch_gemm(Kernel kernel, const GemmArgs& a, const RopeTable& rope, const ChunkTable& tab,
                              KernelClass kc, hipStream_t s) {
   const int items = a.v_count * a.k_parts;
   const int per_xcd = (items + kNumXCDs - 1) / kNumXCDs;
-  dim3 grid(per_xcd * kNumXCDs), block(threads);
+  dim3 grid(per_xcd * kNumXCDs), block(kGemmThreads);
   launch_kernel(kc, kernel, grid, block, 0, s, a, rope, tab);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "gemm kernel launch");
@@ -584,12 +597,7 @@ static ct_status launch_gemm(Kernel kernel, int threads, const GemmArgs& a, cons
 template <int EPI, int D, int STYLE, int NB>
 static ct_status launch_variant(const GemmArgs& a, const RopeTable& rope, const ChunkTable& tab, KernelClass kc,
                                 hipStream_t s) {
-  // Eight waves, or four (one per SIMD, 128 x 128 wave tiles), which read a third less from LDS per MFMA
-  // and so leave the power-limited clock higher, but run an epilogue with less overlap.  Four for
-  // 256-token tiles (K = 4096, n = 4915: gate/up 903 us, 936 us with eight; down projection 465 and 501)
-  // unless the rotation is in the epilogue (QKV at n = 4915: 218 us with four, 214 with eight).
-  constexpr int NW = NB == 2 && EPI != EPI_QKV_ROPE ? 4 : 8;
-  return launch_gemm(gemm_kernel<EPI, D, STYLE, NB, NW>, 64 * NW, a, rope, tab, kc, s);
+  return launch_gemm(gemm_kernel<EPI, D, STYLE, NB>, a, rope, tab, kc, s);
 }
 
 template <int D, int STYLE, int NB>
@@ -597,8 +605,8 @@ static ct_status launch_qkv_variant(const GemmArgs& a, const RopeTable& rope, co
                                     void* k_buf, void* v_buf, hipStream_t s) {
   if (move == nullptr) return launch_variant<EPI_QKV_ROPE, D, STYLE, NB>(a, rope, tab, KC_QKV, s);
   const int gemm_blocks = (a.v_count + kNumXCDs - 1) / kNumXCDs * kNumXCDs;
-  const int64_t move_blocks = (move->total_tokens * (D / 16) + kMoveThreads - 1) / kMoveThreads;
-  launch_kernel(KC_QKV, qkv_move_kernel<D, STYLE, NB>, dim3((unsigned)(gemm_blocks + move_blocks)), dim3(kMoveThreads), 0, s, a,
+  const int64_t move_blocks = (move->total_tokens * (D / 16) + kGemmThreads - 1) / kGemmThreads;
+  launch_kernel(KC_QKV, qkv_move_kernel<D, STYLE, NB>, dim3((unsigned)(gemm_blocks + move_blocks)), dim3(kGemmThreads), 0, s, a,
                 rope, tab, *move, static_cast<uint16_t*>(k_buf), static_cast<uint16_t*>(v_buf), gemm_blocks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "projection kernel launch");
