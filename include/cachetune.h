@@ -211,9 +211,10 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
                                    size_t workspace_bytes, void* compute_stream, void* copy_stream);
 
 /* Scratch bytes ct_selected_attention / ct_partial_prefill_layer need for this problem
- * size (0 on invalid arguments).  For few selected rows the amount includes room for splitting
- * the key range over more workgroups; a call with less, down to what it cannot do without, splits
- * less and takes longer. */
+ * size (0 on invalid arguments).  For few selected rows the amount includes room in which
+ * ct_partial_prefill_layer splits the key range over more workgroups; a layer call with less, down to
+ * what it cannot do without, splits less: it takes longer, and its sums are formed in another order
+ * (the last bit of an output may differ). */
 size_t ct_workspace_bytes(const ct_layer_cfg* cfg, int32_t n_ctx, int32_t n_sel);
 
 /* Optional extra workspace of ct_partial_prefill_layer for layers whose chunks come from host

@@ -148,6 +148,9 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
 // (A partial result also goes through memory: contexts up to 512 keys stay whole.)  Layer calls, split against
 // whole: tiny model, 1024 tokens, 153 rows 28.7 / 34.3 us, 2048 tokens, 102 rows 32 / 54 us; Llama-3-8B 2048 tokens,
 // 20 rows 62 / 89 us, 1024 rows (128 pairs) 92 / 100 us, 8192 tokens, 81 rows 88 / 103 us.
+// For the layer and stack calls, whose workspace is taken up by their rows in any case.  The attention entry points keep
+// to plan_attention: what needs no scratch there leaves the workspace, and the array that all calls on a GPU share,
+// alone, so such calls may overlap on several streams.
 AttnPlan plan_attention_within(const ct_layer_cfg* cfg, int n_ctx, int n_sel, size_t scratch_bytes) {
   AttnPlan p = plan_attention(cfg, n_ctx, n_sel);
   const long pairs = (long)p.n_tiles * cfg->n_kv_heads;
@@ -544,7 +547,6 @@ ct_status ct_selected_attention(const ct_layer_cfg* cfg, const void* q_sel, cons
       return fail(CT_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, p.ws_bytes);
     if (((uintptr_t)workspace & 255) != 0) return fail(CT_ERR_WORKSPACE, "workspace is not 256-byte aligned");
   }
-  if (workspace != nullptr && ((uintptr_t)workspace & 255) == 0) p = plan_attention_within(cfg, n_ctx, n_sel, workspace_bytes);
   return launch_attention(cfg, p, q_sel, k_buf, v_buf, n_ctx, sel_idx, n_sel, out, lse, workspace,
                           static_cast<hipStream_t>(stream));
 }

@@ -69,7 +69,8 @@ ct_status ct_selected_attention_static(const ct_layer_cfg* cfg, const void* q_se
                 n_ctx, n_sel, need, kStaticScratchBytes);
   void* ptr = nullptr;
   if ((st = static_scratch(&ptr)) != CT_OK) return st;
-  return launch_attention(cfg, plan_attention_within(cfg, n_ctx, n_sel, kStaticScratchBytes), q_sel, k_buf, v_buf, n_ctx, sel_idx, n_sel, out, lse, ptr, static_cast<hipStream_t>(stream));
+  return launch_attention(cfg, plan_attention(cfg, n_ctx, n_sel), q_sel, k_buf, v_buf, n_ctx, sel_idx, n_sel, out, lse, ptr,
+                          static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"
