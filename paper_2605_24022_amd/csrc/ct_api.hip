@@ -144,8 +144,13 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
 
 // With few (tile, head) pairs a launch lasts as long as one workgroup takes to walk its keys, 1.4 us per 64 of
 // them.  Up to half a round of pairs is split further, into one round of workgroups over at least 256 keys
-// each, as far as the scratch goes; from there on a second round costs what the shorter walk gains.
-// (A partial result also goes through memory: contexts up to 512 keys stay whole.)  Layer calls, split against
+// each, as far as the scratch goes; from there on a second round costs what the shorter walk gains.  At most 32 parts:
+// the merge reads them one after the other (8/2 heads of 64, 16384 tokens, 100 rows: 64 parts 68 us, 32 49, 8 61).
+// The parts also go through memory, 133 KB each, which short walks do not win back: the keys that the last row
+// is expected to see (n_sel rows anywhere) have to reach 560 and 5 more per pair.  Attention and merge, whole / split:
+// 32/8 heads of 128, 100 rows (16 pairs) of 513 tokens 20.4 / 22.0 us, 768 25.3 / 23.2, 1024 30.4 / 24.7, 2048 49 / 30;
+// 400 rows (56 pairs) of 768 27.0 / 27.8, 1024 31.5 / 30.5; 800 rows (104) of 1024 32.2 / 33.6, 1536 42.2 / 38.6;
+// 8/2 heads of 64, 100 rows (4) of 513 16.7 / 17.1, 640 18.9 / 17.9.  Layer calls, split against
 // whole: tiny model, 1024 tokens, 153 rows 28.7 / 34.3 us, 2048 tokens, 102 rows 32 / 54 us; Llama-3-8B 2048 tokens,
 // 20 rows 62 / 89 us, 1024 rows (128 pairs) 92 / 100 us, 8192 tokens, 81 rows 88 / 103 us.
 // For the layer and stack calls, whose workspace is taken up by their rows in any case.  The attention entry points keep
@@ -154,9 +159,9 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
 AttnPlan plan_attention_within(const ct_layer_cfg* cfg, int n_ctx, int n_sel, size_t scratch_bytes) {
   AttnPlan p = plan_attention(cfg, n_ctx, n_sel);
   const long pairs = (long)p.n_tiles * cfg->n_kv_heads;
-  if (pairs <= 0 || pairs > kNumCUs / 2 || n_ctx <= 512) return p;
+  if (pairs <= 0 || pairs > kNumCUs / 2 || (int64_t)n_ctx * n_sel / (n_sel + 1) < 560 + 5 * pairs) return p;
   const size_t per_split = (size_t)pairs * 256 * (size_t)(cfg->head_dim + 2) * sizeof(float);
-  long want = kNumCUs / pairs;
+  long want = kNumCUs / pairs < 32 ? kNumCUs / pairs : 32;
   if (want > (long)(scratch_bytes / per_split)) want = (long)(scratch_bytes / per_split);
   if (want < 2) return p;
   int keys = (int)((n_ctx + want - 1) / want);

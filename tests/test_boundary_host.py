@@ -228,6 +228,23 @@ def test_workspace_size_covers_staging_and_partials():
     assert B.ct_attention_state_bytes(c, 32768, 0) == 0 and B.ct_attention_state_bytes(c, 100, 200) == 0
 
 
+@pytest.mark.parametrize("hq,hkv,d,n_ctx,n_sel,parts", [
+    (8, 2, 64, 513, 100, 1), (8, 2, 64, 640, 100, 3),          # 4 (tile, head) pairs: from 580 visible keys on
+    (32, 8, 128, 768, 400, 1), (32, 8, 128, 1024, 400, 4),     # 56: from 840
+    (32, 8, 128, 1024, 800, 1), (32, 8, 128, 1536, 800, 2),    # 104: from 1080
+    (32, 8, 128, 1024, 1, 1), (32, 8, 128, 2048, 1, 8),        # one row sees half the context
+    (8, 2, 64, 16384, 100, 32), (32, 2, 128, 32768, 1, 32),    # never more than 32
+    (8, 2, 64, 131072, 100, 64)])                              # (the general rule asks for more than that by itself)
+def test_layer_workspace_holds_the_parts_of_the_key_range(hq, hkv, d, n_ctx, n_sel, parts):
+    """How many parts the layer call splits the key range into, from the scratch it asks for.  Short walks stay whole:
+    the merge takes longer than they do."""
+    up = lambda x: (x + 255) // 256 * 256
+    pairs = -(-n_sel // (256 // (hq // hkv))) * hkv
+    scratch = pairs * parts * 256 * (d + 2) * 4 if parts > 1 else 0
+    staging = up(n_sel * hq * d * 2) + 2 * up(n_sel * hkv * d * 2) + 256
+    assert B.ct_workspace_bytes(B.make_cfg(hq * d, hq, hkv, d, 1e4), n_ctx, n_sel) == up(scratch) + staging
+
+
 def test_norm_and_gemm_validation():
     assert _status(B.ct_rmsnorm, None, FAKE, 1e-5, 4, 512, FAKE) == B.CT_ERR_NULL
     assert _status(B.ct_rmsnorm, FAKE, FAKE, 1e-5, 4, 100, FAKE) == B.CT_ERR_UNSUPPORTED
