@@ -104,6 +104,22 @@ ct_status pooled_events(size_t n, hipEvent_t** out) {
 }
 
 // ------------------------------------------------------------------------------ planning
+// Tuning knobs: split below this many (tile, head) pairs, and keys per split (0: not set).
+static long knob_split_target() {
+  static const long v = []() {
+    const char* e = getenv("CT_ATTN_SPLIT_TARGET");
+    return e != nullptr && atol(e) > 0 ? atol(e) : 0L;
+  }();
+  return v;
+}
+static int knob_split_keys() {
+  static const int v = []() {
+    const char* e = getenv("CT_ATTN_SPLIT_KEYS");
+    return e != nullptr && atoi(e) >= 64 ? (atoi(e) + 63) / 64 * 64 : 0;
+  }();
+  return v;
+}
+
 AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
   AttnPlan p;
   const int g = cfg->n_q_heads / cfg->n_kv_heads;
@@ -116,20 +132,13 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
   // measured on MI355X, an unsplit launch wins as soon as there are about 1.5 pairs per
   // compute unit (each split costs an fp32 partial (O, m, l) round trip and a merge kernel).
   const long pairs = (long)p.n_tiles * cfg->n_kv_heads;
-  static const long target = []() {                     // tuning knob: split below this many (tile, head) pairs
-    const char* v = getenv("CT_ATTN_SPLIT_TARGET");
-    return v != nullptr && atol(v) > 0 ? atol(v) : 384L;  // 1.5 x 256 compute units
-  }();
+  const long target = knob_split_target() > 0 ? knob_split_target() : 384;   // 1.5 x 256 compute units
   if (pairs > 0 && pairs < target && n_ctx > 2048) {
     int want = (int)((target + pairs - 1) / pairs);
     int keys = (n_ctx + want - 1) / want;
     keys = ((keys + 1023) / 1024) * 1024;               // whole K tiles, not too small
     if (keys < 2048) keys = 2048;
-    static const int forced = []() {                    // tuning knob: keys per split
-      const char* v = getenv("CT_ATTN_SPLIT_KEYS");
-      return v != nullptr ? atoi(v) : 0;
-    }();
-    if (forced >= 64) keys = (forced + 63) / 64 * 64;
+    if (knob_split_keys() > 0) keys = knob_split_keys();
     int ns = (n_ctx + keys - 1) / keys;
     if (ns > 1) {
       p.n_splits = ns;
@@ -153,12 +162,14 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
 // 8/2 heads of 64, 100 rows (4) of 513 16.7 / 17.1, 640 18.9 / 17.9.  Layer calls, split against
 // whole: tiny model, 1024 tokens, 153 rows 28.7 / 34.3 us, 2048 tokens, 102 rows 32 / 54 us; Llama-3-8B 2048 tokens,
 // 20 rows 62 / 89 us, 1024 rows (128 pairs) 92 / 100 us, 8192 tokens, 81 rows 88 / 103 us.
+// With a tuning knob set the plan is plan_attention's, which follows them.
 // For the layer and stack calls, whose workspace is taken up by their rows in any case.  The attention entry points keep
 // to plan_attention: what needs no scratch there leaves the workspace, and the array that all calls on a GPU share,
 // alone, so such calls may overlap on several streams.
 AttnPlan plan_attention_within(const ct_layer_cfg* cfg, int n_ctx, int n_sel, size_t scratch_bytes) {
   AttnPlan p = plan_attention(cfg, n_ctx, n_sel);
   const long pairs = (long)p.n_tiles * cfg->n_kv_heads;
+  if (knob_split_target() > 0 || knob_split_keys() > 0) return p;
   if (pairs <= 0 || pairs > kNumCUs / 2 || (int64_t)n_ctx * n_sel / (n_sel + 1) < 560 + 5 * pairs) return p;
   const size_t per_split = (size_t)pairs * 256 * (size_t)(cfg->head_dim + 2) * sizeof(float);
   long want = kNumCUs / pairs < 32 ? kNumCUs / pairs : 32;

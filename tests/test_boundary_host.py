@@ -3,6 +3,8 @@ rejects bad arguments before it touches HIP."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -243,6 +245,18 @@ def test_layer_workspace_holds_the_parts_of_the_key_range(hq, hkv, d, n_ctx, n_s
     scratch = pairs * parts * 256 * (d + 2) * 4 if parts > 1 else 0
     staging = up(n_sel * hq * d * 2) + 2 * up(n_sel * hkv * d * 2) + 256
     assert B.ct_workspace_bytes(B.make_cfg(hq * d, hq, hkv, d, 1e4), n_ctx, n_sel) == up(scratch) + staging
+
+
+@pytest.mark.parametrize("knob", ["CT_ATTN_SPLIT_KEYS=65536", "CT_ATTN_SPLIT_TARGET=1"])
+def test_split_knobs_hold_for_the_layer_call(knob):
+    """A setting that asks for whole key ranges is not overridden: the layer asks for no scratch beside its rows."""
+    code = ("from paper_2605_24022_amd import binding as B\n"
+            "print(B.ct_workspace_bytes(B.make_cfg(4096, 32, 8, 128, 1e4), 2048, 20),"
+            " B.ct_workspace_bytes(B.make_cfg(4096, 32, 8, 128, 1e4), 8192, 81))")
+    name, value = knob.split("=")
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, **{name: value}), capture_output=True, text=True,
+                       cwd=ROOT, check=True)
+    assert [int(v) for v in r.stdout.split()] == [n * (32 + 2 * 8) * 128 * 2 + 256 for n in (20, 81)]
 
 
 def test_norm_and_gemm_validation():
