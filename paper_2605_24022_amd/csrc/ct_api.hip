@@ -652,9 +652,12 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
     v_rows = ws + off;
     off += up((size_t)n_sel * row_bytes);
     // room behind the staging rows for the attention state: the attention of host-pool layers can
-    // then follow the chunk groups key range by key range
+    // then follow the chunk groups key range by key range.  The caller asks for that with more than
+    // ct_workspace_bytes() (whose room for splits is not used here, and is none of the state's: a short context is
+    // transferred sooner in one launch than in two).
     const size_t state_bytes = attention_state_bytes(cfg, n_ctx, n_sel);
-    if (p.n_splits == 1 && workspace_bytes >= off + state_bytes) attn_state = reinterpret_cast<float*>(ws + off);
+    if (p.n_splits == 1 && workspace_bytes >= ct_workspace_bytes(cfg, n_ctx, n_sel) + state_bytes)
+      attn_state = reinterpret_cast<float*>(ws + off);
   }
 
   // Transfer stream: enqueue every pinned-host chunk's transfer first so the link starts at once.

@@ -125,3 +125,40 @@ def test_attention_that_needs_no_scratch_leaves_it_alone(hq, hkv, d, n_ctx, n_se
     B.ct_profile_reset()
     assert bool((ws == 0xa5).all())
     assert torch.isfinite(plain).all() and torch.equal(plain, given) and torch.equal(plain, static)
+
+
+def test_host_pool_takes_the_state_from_room_asked_for():
+    """The room for splits in ct_workspace_bytes is none of the attention state's: with that amount a short context in
+    pinned memory comes in one launch and is followed by one attention launch, with the state's bytes on top by several."""
+    hq, hkv, d, n_chunks, length, n_sel, hidden = 32, 8, 128, 4, 512, 307, 128
+    n_ctx = n_chunks * length
+    g = torch.Generator(device="cuda").manual_seed(5)
+    cfg = B.make_cfg(hidden, hq, hkv, d, 1.0e4)
+    x, w, k, v = (torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+                  for s in ((n_sel, hidden), ((hq + 2 * hkv) * d, hidden), (n_ctx, hkv, d), (n_ctx, hkv, d)))
+    w *= hidden ** -0.5
+    kp, vp = (torch.empty(n_ctx, hkv, d, dtype=torch.bfloat16, pin_memory=True) for _ in range(2))
+    kp.copy_(k)
+    vp.copy_(v)
+    chunks = B.make_chunks([dict(k=kp[c * length:], v=vp[c * length:], n_tokens=length, old_pos_start=0, new_pos_start=c * length,
+                                 location=1) for c in range(n_chunks)])
+    sel = (torch.arange(n_sel, device="cuda") * n_ctx // n_sel).to(torch.int32)
+    need, state = B.ct_workspace_bytes(cfg, n_ctx, n_sel), B.ct_attention_state_bytes(cfg, n_ctx, n_sel)
+    ws = torch.empty(need + state, dtype=torch.uint8, device="cuda")
+    copy, got = torch.cuda.Stream(), []
+    for amount in (need, need + state):
+        say(f"host pool, workspace of {amount} bytes")
+        kb, vb = (torch.zeros(n_ctx, hkv, d, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        out = torch.full((n_sel, hq, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+        B.ct_profile_reset()
+        B.ct_set_profiling(True)
+        B.ct_partial_prefill_layer(cfg, chunks, n_chunks, x, None, sel, n_sel, -1.0, w, None, kb, vb, out, ws, amount, None, copy)
+        B.ct_set_profiling(False)
+        torch.cuda.synchronize()
+        got.append((B.ct_profile_read("attention")[0], kb, vb, out))
+        B.ct_profile_reset()
+    assert got[0][0] == 1 and got[1][0] == 2
+    assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][2], got[1][2])
+    # the same sums in another order, probabilities and results rounded to bf16 (2^-8)
+    size = float(got[0][2].float().abs().max())
+    assert float((got[0][3].float() - got[1][3].float()).abs().max()) <= 2.0 ** -7 * size
