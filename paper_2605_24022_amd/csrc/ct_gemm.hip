@@ -522,7 +522,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2,
     GemmArgs a, RopeTable rope, ChunkTable chunks, ReropeChunks move, uint16_t* k_buf, uint16_t* v_buf, int32_t move_after) {
   __shared__ __align__(1024) unsigned char lds[gemm_lds_bytes(NB)];
   if ((int)blockIdx.x >= move_after) {
-    const int block = blockIdx.x - move_after, blocks = gridDim.x - move_after;
+    const uint32_t block = blockIdx.x - move_after, blocks = gridDim.x - move_after;
     if (a.Hkv == 8) rerope_chunk_tokens<D, STYLE, 8, true>(k_buf, v_buf, 8, rope, move, kGemmThreads, block, blocks);
     else if (a.Hkv == 2) rerope_chunk_tokens<D, STYLE, 2, true>(k_buf, v_buf, 2, rope, move, kGemmThreads, block, blocks);
     else rerope_chunk_tokens<D, STYLE, 0, true>(k_buf, v_buf, a.Hkv, rope, move, kGemmThreads, block, blocks);

@@ -132,7 +132,7 @@ __device__ __forceinline__ int count_below_near(const int32_t* __restrict__ list
 template <int D, int STYLE, int HEADS, bool NEAR>
 __device__ __forceinline__ void rerope_chunk_tokens(uint16_t* k_buf, uint16_t* v_buf, int32_t n_heads_rt,
                                                     const RopeTable& table, const ReropeChunks& chunks, int threads,
-                                                    int block, int n_blocks) {
+                                                    uint32_t block, uint32_t n_blocks) {
   constexpr int GROUPS = D / 16;
   const int64_t gid = (int64_t)block * threads + threadIdx.x;
   const int jg = (int)(gid % GROUPS);
