@@ -816,7 +816,7 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
       rc.delta_step[i] = ch.raw_keys ? 1 : 0;
     }
     close();
-    if ((n_sel == 0 || !projection_leaves_units(cfg, n_sel) || !move_beside_projection(rc, k_buf, v_buf, row_bytes, n_ctx, workspace, workspace_bytes)) &&
+    if ((n_sel == 0 || !projection_leaves_units(cfg, n_sel, rc.total_tokens) || !move_beside_projection(rc, k_buf, v_buf, row_bytes, n_ctx, workspace, workspace_bytes)) &&
         (st = flush()) != CT_OK)
       return st;
   }

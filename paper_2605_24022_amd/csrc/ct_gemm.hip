@@ -615,16 +615,23 @@ static ct_status launch_qkv_variant(const GemmArgs& a, const RopeTable& rope, co
 
 // The rotation beside the projection costs it some of its memory bandwidth, which pays as long as idle compute
 // units take most of the work.  Llama-3-8B layer, fused against a launch of its own before: 2048 tokens,
-// 307 rows 88 us against 99 us, 8192 tokens, 983 rows 154 / 163 us, 32768 tokens, 1638 rows 546 / 561 us; with
+// 307 rows 88 us against 99 us, 8192 tokens, 983 rows 154 / 163 us, 32768 tokens, 1638 rows 536 / 552 us; with
 // 240 tiles on 256 units 206 / 205 us (8192 tokens, 1228 rows) and 529 / 529 us (16384 tokens, 2457 rows).
-bool projection_leaves_units(const ct_layer_cfg* cfg, int32_t n_sel) {
+// A unit holds one such workgroup (it claims the LDS of a tile).  With the loads of eight heads in flight that still
+// reads at speed, with two or with the loop over any number it does not, and what the idle units have not moved when the
+// projection ends takes longer than in a launch of its own: at most 3 MB for each.  Inputs from memory, fused / apart:
+// 16/16 heads of 64, 32768 tokens, 9830 rows (6.1 MB) 1093 / 1074 us, 1638 rows (2.7 MB) 381 / 384, 327 rows (1.2 MB)
+// 214 / 218; 32/2 heads of 128, 131072 tokens, 1310 rows (4.6 MB) 1844 / 1812; 32/8 of 128, 131072, 1310 (9.6 MB) 2133 / 2180.
+bool projection_leaves_units(const ct_layer_cfg* cfg, int32_t n_sel, int64_t move_tokens) {
   GemmArgs a;
   memset(&a, 0, sizeof(a));
   a.n_sel = n_sel;
   a.O = (cfg->n_q_heads + 2 * cfg->n_kv_heads) * cfg->head_dim;
   fill_tiles(&a, false, pick_nb(a, false));
-  const int last = a.v_count % kNumCUs;
-  return last > 0 && last <= kNumCUs - kNumCUs / 8;
+  const int last = a.v_count % kNumCUs, idle = kNumCUs - last;
+  if (last == 0 || idle < kNumCUs / 8) return false;
+  const int64_t moved = move_tokens * cfg->n_kv_heads * cfg->head_dim * 2 * 4;   // keys and values, read and written
+  return cfg->n_kv_heads == 8 || moved <= (int64_t)idle * 3000000;
 }
 
 ct_status launch_qkv(const ct_layer_cfg* cfg, const void* hidden, const int32_t* hidden_rows, const int32_t* sel_pos,

@@ -124,8 +124,9 @@ ct_status stream_in_host_chunks(const ct_layer_cfg* cfg, const ct_chunk* chunks,
                                 stream_in_group_fn after_group = nullptr, void* ctx = nullptr);
 // Whether the stream-in kernel leaves the rows of the recompute set alone (it does unless switched off).
 bool stream_in_skips_selected();
-// Whether the last round of the projection's workgroups leaves an eighth of the compute units or more to others.
-bool projection_leaves_units(const ct_layer_cfg* cfg, int32_t n_sel);
+// Whether the last round of the projection's workgroups leaves an eighth of the compute units or more to others, and
+// these are enough for the rotation of move_tokens reused tokens.
+bool projection_leaves_units(const ct_layer_cfg* cfg, int32_t n_sel, int64_t move_tokens);
 // Whether the projection may run beside the rotation of these chunks: no source lies in what the projection
 // writes - the layer buffers of n_ctx rows, except a chunk that stands in its own place, and the workspace.
 bool move_beside_projection(const ReropeChunks& m, const void* k_buf, const void* v_buf, size_t row_bytes, int32_t n_ctx,

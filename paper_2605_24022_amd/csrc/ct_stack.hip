@@ -364,7 +364,7 @@ ct_status ct_partial_prefill_stack_tap(const ct_layer_cfg* cfg, int32_t ffn_dim,
         rc.delta_step[i] = ch.raw_keys ? 1 : 0;
       }
       close();
-      if (rc.n > 0 && (!projection_leaves_units(cfg, n_sel) || !move_beside_projection(rc, kb, vb, row_bytes, n_ctx, workspace, workspace_bytes)) &&
+      if (rc.n > 0 && (!projection_leaves_units(cfg, n_sel, rc.total_tokens) || !move_beside_projection(rc, kb, vb, row_bytes, n_ctx, workspace, workspace_bytes)) &&
           (st = flush()) != CT_OK)
         return st;
     }

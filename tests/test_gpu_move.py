@@ -78,3 +78,35 @@ def test_layer_equals_its_steps(hq, hkv, d, style, lengths, n_sel, where):
     # the key range may be split in another way: probabilities and results are rounded to bf16 (2^-8) from other sums
     size = float(vb.float().abs().max())
     assert float((out.float() - want.float()).abs().max()) <= 2.0 ** -7 * size
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_ctx,n_sel,apart", [
+    (16, 16, 64, 32768, 9830, 1),      # 44 units left, 6.1 MB to move for each, any number of heads
+    (32, 2, 128, 131072, 1310, 1),     # 58 units, 4.6 MB
+    (16, 16, 64, 32768, 1638, 0),      # 100 units, 2.7 MB
+    (32, 8, 128, 32768, 4915, 0)])     # 32 units, 8.4 MB, but eight heads
+def test_much_to_move_has_a_launch_of_its_own(hq, hkv, d, n_ctx, n_sel, apart):
+    say(f"move rule heads={hq}/{hkv} d={d} n_ctx={n_ctx} n_sel={n_sel}")
+    g = torch.Generator(device="cuda").manual_seed(n_sel)
+    hidden = 64
+    cfg = B.make_cfg(hidden, hq, hkv, d, 1.0e4)
+    sel = (torch.arange(n_sel, device="cuda") * n_ctx // n_sel).to(torch.int32)
+    x, w, k, v = _rand(g, n_sel, hidden), _rand(g, (hq + 2 * hkv) * d, hidden), _rand(g, n_ctx, hkv, d), _rand(g, n_ctx, hkv, d)
+    kb, vb = (torch.zeros_like(k) for _ in range(2))
+    want_k, want_v = (torch.zeros_like(k) for _ in range(2))
+    B.ct_rerope_chunk(cfg, k, want_k, v, want_v, n_ctx, 7, 0, 0)
+    q, ks, vs = (torch.empty(n_sel, h, d, device="cuda", dtype=torch.bfloat16) for h in (hq, hkv, hkv))
+    B.ct_qkv_selected(cfg, x, None, sel, n_sel, w, None, q, ks, vs)
+    want_k[sel.long()], want_v[sel.long()] = ks, vs
+    chunks = B.make_chunks([dict(k=k, v=v, n_tokens=n_ctx, old_pos_start=7, new_pos_start=0, location=0)])
+    ws_bytes = B.ct_workspace_bytes(cfg, n_ctx, n_sel)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    B.ct_profile_reset()
+    B.ct_set_profiling(True)
+    B.ct_partial_prefill_layer(cfg, chunks, 1, x, None, sel, n_sel, -1.0, w, None, kb, vb, q, ws, ws_bytes, None, torch.cuda.Stream())
+    B.ct_set_profiling(False)
+    torch.cuda.synchronize()
+    launches = B.ct_profile_read("rerope")[0]
+    B.ct_profile_reset()
+    assert launches == apart
+    assert torch.equal(kb, want_k) and torch.equal(vb, want_v)
