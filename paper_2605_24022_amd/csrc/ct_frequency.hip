@@ -850,14 +850,15 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 // go out kTopkBatch at a time, scores that share the first byte (nearly all do) are added by one lane, and each
 // wave sweeps a stretch of its own without barriers.  15 % of 32768 scores: 92 -> 38 us, of 4 x 1500 8.4 -> 7.2 us.
 constexpr int kTopkBatch = 8;
-__global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ scores, int32_t n, int32_t k,
+__global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ scores, int32_t n_tokens, int32_t k,
                                                     int32_t* __restrict__ idx_out) {
   __shared__ uint32_t hist[256];
   __shared__ uint32_t sh_prefix, sh_need;
   __shared__ uint32_t n_above[16], n_tie[16];
-  const float* s = scores + (int64_t)blockIdx.x * n;
+  const float* s = scores + (int64_t)blockIdx.x * n_tokens;
   int32_t* out = idx_out + (int64_t)blockIdx.x * k;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const uint32_t n = n_tokens;     // (unsigned: positions run past the end by up to a batch)
   if (k <= 0) return;
   // radix select, most significant byte first: after the loop `prefix` is the key of the k-th
   // largest score and `need` the number of tokens with exactly that key that are still taken
@@ -866,7 +867,7 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
     if (tid < 256) hist[tid] = 0;
     __syncthreads();
     const uint32_t himask = shift == 24 ? 0u : (0xffffffffu << (shift + 8));
-    for (int i0 = tid; i0 - tid < n; i0 += 1024 * kTopkBatch) {
+    for (uint32_t i0 = tid; i0 - tid < n; i0 += 1024 * kTopkBatch) {
       float x[kTopkBatch];
 #pragma unroll
       for (int b = 0; b < kTopkBatch; ++b) x[b] = i0 + b * 1024 < n ? s[i0 + b * 1024] : 0.f;
@@ -919,23 +920,23 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
   }
   // ordered sweep: tokens above the threshold, and the first `need` tokens on it.  Wave w owns one
   // stretch of tokens; it counts both kinds, and what the waves before it hold says where it writes.
-  const int stretch = (n + 1023) / 1024 * 64, begin = wv * stretch, end = min(n, begin + stretch);
+  const uint32_t stretch = (n + 1023) / 1024 * 64, begin = wv * stretch, end = min(n, begin + stretch);
   auto sweep = [&](auto&& body) __attribute__((always_inline)) {
-    for (int i0 = begin; i0 < end; i0 += 64 * kTopkBatch) {
+    for (uint32_t i0 = begin; i0 < end; i0 += 64 * kTopkBatch) {
       float x[kTopkBatch];
 #pragma unroll
       for (int b = 0; b < kTopkBatch; ++b) x[b] = i0 + b * 64 + lane < end ? s[i0 + b * 64 + lane] : 0.f;
 #pragma unroll
       for (int b = 0; b < kTopkBatch; ++b) {
         if (i0 + b * 64 >= end) break;
-        const int i = i0 + b * 64 + lane;
+        const uint32_t i = i0 + b * 64 + lane;
         const uint32_t key = score_key(x[b]);
         body(i, i < end && key > prefix, i < end && key == prefix);
       }
     }
   };
   uint32_t above_here = 0, ties_here = 0;
-  sweep([&](int, bool above, bool tie) __attribute__((always_inline)) {
+  sweep([&](uint32_t, bool above, bool tie) __attribute__((always_inline)) {
     above_here += __popcll(__ballot(above));
     ties_here += __popcll(__ballot(tie));
   });
@@ -951,11 +952,11 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
   }
   at += min(ties, need);
   const uint64_t before = (1ull << lane) - 1ull;
-  sweep([&](int i, bool above, bool tie) __attribute__((always_inline)) {
+  sweep([&](uint32_t i, bool above, bool tie) __attribute__((always_inline)) {
     const uint64_t tie_lanes = __ballot(tie);
     const bool take = above || (tie && ties + __popcll(tie_lanes & before) < need);
     const uint64_t take_lanes = __ballot(take);
-    if (take) out[at + __popcll(take_lanes & before)] = i;
+    if (take) out[at + __popcll(take_lanes & before)] = (int32_t)i;
     ties += __popcll(tie_lanes);
     at += __popcll(take_lanes);
   });

@@ -242,3 +242,15 @@ def test_offline_selection_feeds_the_online_layer():
                                                  sh.rope_theta, sh.rope_style)
     assert_close(f64_of(out), want, "attention output with the frequency-guided recompute set")
     assert_close(f64_of(k_buf), k_want, "fused K with the frequency-guided recompute set")
+
+
+def test_topk_near_the_largest_length():
+    """Positions run past the end of the scores by up to a batch of loads, also where that is past 2^31."""
+    n, k = 2 ** 31 - 4097, 6
+    say(f"topk n={n}")
+    s = torch.zeros(n, device="cuda")
+    peaks = [3, 2 ** 30 + 1, n - 4096, n - 1]
+    s[torch.tensor(peaks, device="cuda")] = torch.tensor([2.0, 5.0, 1.0, 3.0], device="cuda")
+    out = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+    B.ct_topk_indices(s, 1, n, k, out)
+    assert out.tolist() == [0, 1] + peaks      # the two lowest of the zeros, which tie
