@@ -849,7 +849,10 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 // One workgroup per sequence; scores stay in L2, so what counts is the chain of loads, atomics and barriers: loads
 // go out kTopkBatch at a time, scores that share the first byte (nearly all do) are added by one lane, and each
 // wave sweeps a stretch of its own without barriers.  15 % of 32768 scores: 92 -> 38 us, of 4 x 1500 8.4 -> 7.2 us.
+// SHORT: up to one score per thread, which stays in a register through all passes: 15 % of 512 scores 8.4 -> 6.6 us, of 300 x 1024
+// 10.2 -> 7.6 us (batches of loads again and again took longer there than single loads had: 7.8 and 10.1 us).
 constexpr int kTopkBatch = 8;
+template <bool SHORT>
 __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ scores, int32_t n_tokens, int32_t k,
                                                     int32_t* __restrict__ idx_out) {
   __shared__ uint32_t hist[256];
@@ -860,6 +863,7 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const uint32_t n = n_tokens;     // (unsigned: positions run past the end by up to a batch)
   if (k <= 0) return;
+  const uint32_t own_key = SHORT && (uint32_t)tid < n ? score_key(s[tid]) : 0u;
   // radix select, most significant byte first: after the loop `prefix` is the key of the k-th
   // largest score and `need` the number of tokens with exactly that key that are still taken
   uint32_t prefix = 0, need = (uint32_t)k;
@@ -867,26 +871,34 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
     if (tid < 256) hist[tid] = 0;
     __syncthreads();
     const uint32_t himask = shift == 24 ? 0u : (0xffffffffu << (shift + 8));
-    for (uint32_t i0 = tid; i0 - tid < n; i0 += 1024 * kTopkBatch) {
-      float x[kTopkBatch];
-#pragma unroll
-      for (int b = 0; b < kTopkBatch; ++b) x[b] = i0 + b * 1024 < n ? s[i0 + b * 1024] : 0.f;
-#pragma unroll
-      for (int b = 0; b < kTopkBatch; ++b) {
-        if (i0 - tid + b * 1024 >= n) break;
-        const uint32_t key = score_key(x[b]), bin = (key >> shift) & 255u;
-        bool left = i0 + b * 1024 < n && (key & himask) == prefix;
-        if (shift == 24) {     // the first byte is the same for most: added by one lane for all that share it
-          const uint64_t live = __ballot(left);
-          if (live != 0) {
-            const int first = __ffsll((unsigned long long)live) - 1;
-            const bool same = left && bin == (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
-            const uint64_t who = __ballot(same);
-            if (lane == first) atomicAdd(&hist[bin], (uint32_t)__popcll(who));
-            left = left && !same;
-          }
+    // adds the keys of a wave's lanes that are `in` (all lanes come here) and agree with the prefix
+    auto count = [&](uint32_t key, bool in) __attribute__((always_inline)) {
+      const uint32_t bin = (key >> shift) & 255u;
+      bool left = in && (key & himask) == prefix;
+      if (shift == 24) {     // the first byte is the same for most: added by one lane for all that share it
+        const uint64_t live = __ballot(left);
+        if (live != 0) {
+          const int first = __ffsll((unsigned long long)live) - 1;
+          const bool same = left && bin == (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
+          const uint64_t who = __ballot(same);
+          if (lane == first) atomicAdd(&hist[bin], (uint32_t)__popcll(who));
+          left = left && !same;
         }
-        if (left) atomicAdd(&hist[bin], 1u);
+      }
+      if (left) atomicAdd(&hist[bin], 1u);
+    };
+    if constexpr (SHORT) {
+      count(own_key, (uint32_t)tid < n);
+    } else {
+      for (uint32_t i0 = tid; i0 - tid < n; i0 += 1024 * kTopkBatch) {
+        float x[kTopkBatch];
+#pragma unroll
+        for (int b = 0; b < kTopkBatch; ++b) x[b] = i0 + b * 1024 < n ? s[i0 + b * 1024] : 0.f;
+#pragma unroll
+        for (int b = 0; b < kTopkBatch; ++b) {
+          if (i0 - tid + b * 1024 >= n) break;
+          count(score_key(x[b]), i0 + b * 1024 < n);
+        }
       }
     }
     __syncthreads();
@@ -922,6 +934,10 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
   // stretch of tokens; it counts both kinds, and what the waves before it hold says where it writes.
   const uint32_t stretch = (n + 1023) / 1024 * 64, begin = wv * stretch, end = min(n, begin + stretch);
   auto sweep = [&](auto&& body) __attribute__((always_inline)) {
+    if constexpr (SHORT) {     // (wave w's stretch of 64 is what its threads hold)
+      body((uint32_t)tid, (uint32_t)tid < n && own_key > prefix, (uint32_t)tid < n && own_key == prefix);
+      return;
+    }
     for (uint32_t i0 = begin; i0 < end; i0 += 64 * kTopkBatch) {
       float x[kTopkBatch];
 #pragma unroll
@@ -1183,7 +1199,8 @@ ct_status ct_topk_indices(const float* scores, int32_t n_batch, int32_t n_tokens
   if (n_batch == 0 || k == 0) return CT_OK;
   if (scores == nullptr || idx_out == nullptr) return fail(CT_ERR_NULL, "scores and idx_out must be non-NULL");
   hipStream_t s = (hipStream_t)stream;
-  launch_kernel(KC_TOPK, topk_kernel, dim3(n_batch), dim3(1024), 0, s, scores, n_tokens, k, idx_out);
+  launch_kernel(KC_TOPK, n_tokens <= 1024 ? topk_kernel<true> : topk_kernel<false>, dim3(n_batch), dim3(1024), 0, s, scores,
+                n_tokens, k, idx_out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "topk launch");
   return CT_OK;

@@ -244,6 +244,24 @@ def test_offline_selection_feeds_the_online_layer():
     assert_close(f64_of(k_buf), k_want, "fused K with the frequency-guided recompute set")
 
 
+@pytest.mark.parametrize("n,n_batch", [(63, 1), (64, 3), (65, 1), (512, 40), (1000, 2), (1023, 1)])
+def test_topk_of_short_sequences(n, n_batch):
+    """One score per thread: waves that are full, partly full and empty; ties across waves, infinities, the lowest float."""
+    rng = np.random.default_rng([65, n])
+    s = np.round(rng.standard_normal((n_batch, n)) * 2).astype(np.float32)
+    s[:, ::9] = -np.inf
+    s[:, 1::11] = np.finfo(np.float32).min
+    s[:, 2::13] = np.inf
+    sd = torch.from_numpy(s).cuda()
+    for k in (1, n // 6, n // 2, n - 1, n):
+        say(f"topk n={n} batch={n_batch} k={k}")
+        out = torch.full((n_batch, k), -7, dtype=torch.int32, device="cuda")
+        B.ct_topk_indices(sd, n_batch, n, k, out)
+        got = out.cpu().numpy()
+        for b in range(n_batch):
+            assert np.array_equal(got[b], O.topk_indices(s[b], k)), (n, k, b)
+
+
 def test_topk_near_the_largest_length():
     """Positions run past the end of the scores by up to a batch of loads, also where that is past 2^31."""
     n, k = 2 ** 31 - 4097, 6
