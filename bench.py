@@ -106,6 +106,59 @@ def cpu_baseline(wl, sample_rows: int, O, W, np):
     }
 
 
+def projection_and_rotation_alone(B, cfg, wl, sp, torch, hidden, rows, wqkv, chunks, k_buf, v_buf, stream, copy, reps: int = 10):
+    """Seconds per call of the projection of the selected rows, and of the rotation of all reused rows with the copy of
+    their values, each in launches of its own: in a layer call the second may ride on the first's launch."""
+    sh, n = sp.shape, sp.n_sel
+    pos = torch.from_numpy(wl.new_pos[wl.sel_idx]).cuda()
+    q, k, v = (torch.empty((n, h, sh.head_dim), dtype=torch.bfloat16, device="cuda")
+               for h in (sh.n_q_heads, sh.n_kv_heads, sh.n_kv_heads))
+
+    def project():
+        B.ct_qkv_selected(cfg, hidden, rows, pos, n, wqkv, None, q, k, v, stream)
+
+    def rotate():       # nothing recomputed: the layer call assembles the buffers from the chunks
+        B.ct_partial_prefill_layer(cfg, chunks, sp.n_chunks, None, None, None, 0, -1.0, None, None, k_buf, v_buf, None, None, 0,
+                                   stream, copy)
+    out = {}
+    for name, call in (("qkv", project), ("rerope", rotate)):
+        for _ in range(2):
+            call()
+        torch.cuda.synchronize()
+        B.ct_profile_reset()
+        B.ct_set_profiling(True)
+        for _ in range(reps):
+            call()
+        torch.cuda.synchronize()
+        B.ct_set_profiling(False)
+        out[name] = B.ct_profile_read(name)[1] * 1e-3 / reps
+    B.ct_profile_reset()
+    return out
+
+
+def projection_and_rotation_rates(kern, work, alone):
+    """What `extra` says about the projection and the rotation.  kern: kernel classes of a layer call (ms per step); work:
+    qkv_flops, and for the rows that are rotated / for all rows the bytes of the keys (read and written) and those moved
+    with the values; alone: seconds of launches that do one of the two, for calls where one launch does both."""
+    out = {}
+    fused = "qkv" in kern and "rerope" not in kern and alone is not None
+    if fused:
+        t = kern["qkv"]["ms_per_step"] * 1e-3
+        out["qkv_with_rotation"] = {"ms": t * 1e3, "tflops": work["qkv_flops"] / t / 1e12, "gbs_moved": work["moved_bytes"] / t / 1e9}
+        out["qkv_and_rerope_measured"] = "in launches of their own, outside the layer call; there one launch does both"
+        t_qkv, t_rope, keys, moved = alone["qkv"], alone["rerope"], work["rerope_bytes_all"], work["moved_bytes_all"]
+    else:
+        t_qkv, t_rope = (kern[c]["ms_per_step"] * 1e-3 if c in kern else None for c in ("qkv", "rerope"))
+        keys, moved = work["rerope_bytes"], work["moved_bytes"]
+    if t_qkv:
+        out["qkv_tflops"] = work["qkv_flops"] / t_qkv / 1e12
+    if t_rope:
+        out["rerope_gbs_algorithmic"] = keys / t_rope / 1e9
+        out["rerope_frac_of_hbm_peak"] = keys / t_rope / 1e9 / PEAK_HBM_GBS
+        out["rerope_plus_vcopy_gbs_moved"] = moved / t_rope / 1e9     # the same launch copies the reused values
+    return out
+
+
 def cold_cache_bandwidth(B, cfg, wl, sp, torch, np, reps: int = 3):
     """Stand-alone bandwidth kernels under a cold-cache protocol: every launch works on a
     different buffer out of a ring of >= 1 GiB, so nothing it reads is left in the last-level
@@ -268,7 +321,8 @@ def bench_offline(args, B, W, np, torch) -> int:
         # each, the usual count) for each of the row_elems / 2 packed column pairs of K and of V
         "roofline": {"bound": "alu", "achieved": fft_flop / (us_f * 1e-6) / 1e12 if us_f else None, "peak": 157.3,
                      "unit": "TFLOP/s", "frac": fft_flop / (us_f * 1e-6) / 157.3e12 if us_f else None, "traffic": None,
-                     "kernel": "freq_energy_kernel (+ freq_finish_kernel), cold cache"},
+                     "kernel": ("freq_fixed_kernel" if n in (256, 512, 1024, 2048, 4096) and row * n >= 32768 and row % (32768 // n) == 0 else
+                                "freq_mixed_kernel" if n <= 4096 else "freq_long_{a,b,c}_kernel") + " (+ freq_finish_kernel), cold cache"},
         "extra": {"scores_us": us_f, "topk_us": us_t, "algorithmic_bytes_per_step": bytes_per_step,
                   "algorithmic_flop_per_step": fft_flop,
                   "scores_hbm_GBps": score_bytes / (us_f * 1e-6) / 1e9 if us_f else None,
@@ -665,15 +719,13 @@ def main() -> int:
                     "algorithmic_bytes_per_launch": 2.0 * n * Hq * D * 2 + 2.0 * N * Hkv * D * 2,
                     "algorithmic_flops_per_launch": attn_flops}
         extra["sel_attn_tflops"] = ach
-    if "qkv" in kern:
-        extra["qkv_tflops"] = qkv_flops / (kern["qkv"]["ms_per_step"] * 1e-3) / 1e12
-    if "rerope" in kern:
-        gbs = rerope_bytes / (kern["rerope"]["ms_per_step"] * 1e-3) / 1e9
-        extra["rerope_gbs_algorithmic"] = gbs
-        extra["rerope_frac_of_hbm_peak"] = gbs / PEAK_HBM_GBS
-        # the same launch also copies the reused values pool -> buffer: bytes it really moves
-        moved = 4.0 * N * Hkv * D * 2
-        extra["rerope_plus_vcopy_gbs_moved"] = moved / (kern["rerope"]["ms_per_step"] * 1e-3) / 1e9
+    alone = None
+    if "qkv" in kern and "rerope" not in kern and not host_pool and n < N:
+        alone = projection_and_rotation_alone(B, cfg, wl, sp, torch, hidden, rows, wqkv, chunks, k_buf, v_buf, compute, copy)
+    row = Hkv * D * 2
+    extra.update(projection_and_rotation_rates(kern, {
+        "qkv_flops": qkv_flops, "rerope_bytes": rerope_bytes, "rerope_bytes_all": 2.0 * N * row + 8.0 * N,
+        "moved_bytes": 4.0 * (N - n) * row, "moved_bytes_all": 4.0 * N * row}, alone))
     if "scatter" in kern:
         extra["scatter_gbs"] = scatter_bytes / (kern["scatter"]["ms_per_step"] * 1e-3) / 1e9
 
