@@ -29,9 +29,10 @@ def _check(got, want, scale):
     assert (err <= 2.0 ** -8 * want.abs() + 1e-3 * scale).all(), float(err.max())
 
 
-# few tiles take 128 tokens each; 2500 rows of 4096 features (4096: of SwiGLU's halves) fill one round of 256-token tiles
+# few tiles take 128 tokens each; 2500 rows of 4096 features fill one round of 256-token tiles, of SwiGLU, whose tiles
+# hold 128 features of each half, 2500 rows of 2048
 @pytest.mark.parametrize("k_len", [64, 128, 192, 704])
-@pytest.mark.parametrize("n,n_out", [(1, 64), (127, 320), (129, 256), (300, 1088), (2500, 4096), (2305, 4032)])
+@pytest.mark.parametrize("n,n_out", [(1, 64), (127, 320), (129, 256), (300, 1088), (2500, 4096), (2305, 4032), (2500, 2048), (2305, 1984)])
 def test_linear_and_swiglu(n, k_len, n_out):
     say(f"gemm tiles n={n} k={k_len} out={n_out}")
     g = torch.Generator(device="cuda").manual_seed(n + k_len)

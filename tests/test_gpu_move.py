@@ -30,6 +30,8 @@ def _rand(g, *shape):
     (8, 8, 64, 1, [333], 300, "own"),                 # chunks stand in their own place
     (16, 8, 128, 0, [256, 256], 64, "shifted"),       # a source in the layer buffer
     (32, 8, 128, 0, [1300], 1228, "pool"),            # 240 tiles: a launch of its own
+    (16, 8, 128, 0, [1300, 1, 1299], 2100, "pool"), (16, 8, 128, 1, [1300, 1, 1299], 2100, "pool"),    # 256-token tiles,
+    (32, 16, 64, 0, [1300, 1, 1299], 2100, "pool"), (32, 16, 64, 1, [1300, 1, 1299], 2100, "own"),     # any head count
     (8, 2, 64, 0, [100, 28], 128, "pool")])           # nothing reused
 def test_layer_equals_its_steps(hq, hkv, d, style, lengths, n_sel, where):
     say(f"move heads={hq}/{hkv} d={d} chunks={len(lengths)} n_sel={n_sel} {where}")
