@@ -153,7 +153,10 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
 
 // With few (tile, head) pairs a launch lasts as long as one workgroup takes to walk its keys, 1.4 us per 64 of
 // them.  Up to half a round of pairs is split further, into one round of workgroups over at least 256 keys
-// each, as far as the scratch goes; from there on a second round costs what the shorter walk gains.  At most 32 parts:
+// each, as far as the scratch goes; from there on a second round costs what the shorter walk gains.  (Layer calls with
+// at least 128 or 192 keys: tiny model, 2048 tokens, 102 rows 36.8 and 34.2 against 33.2 us with 256, 4096 tokens, 40
+// rows 48.8 and 42.4 / 38.7, Llama-3-8B 4096 tokens, 40 rows 83.9 and 76.2 / 73.1; up to 1024 tokens 192 are up to 4 %
+// ahead, with 16/16 heads 10 %.)  At most 32 parts:
 // the merge reads them one after the other (8/2 heads of 64, 16384 tokens, 100 rows: 64 parts 68 us, 32 49, 8 61).
 // The parts also go through memory, 133 KB each, which short walks do not win back: the keys that the last row
 // is expected to see (n_sel rows anywhere) have to reach 560 and 5 more per pair.  Attention and merge, whole / split:
@@ -776,8 +779,9 @@ ct_status ct_partial_prefill_layer(const ct_layer_cfg* cfg, const ct_chunk* chun
 
   // The recomputed keys and values go straight from the projection's epilogue to their rows of
   // the layer buffers (the scatter of Sec. 4.2 fused into the GEMM) when nothing else writes those
-  // rows afterwards: the launch that rotates device chunks writes every row of its chunks and is
-  // issued first; the stream-in kernel leaves the selected rows alone; plain host copies (memory
+  // rows: the rotation of device chunks, ahead of the projection or beside it in one launch, skips the rows in
+  // sel_idx, and the epilogue writes those rows alone (move_beside_projection has checked that no source lies
+  // among them); the stream-in kernel leaves the selected rows alone; plain host copies (memory
   // the device cannot address) overwrite them at a time of their own, so then the rows wait in
   // the workspace and a scatter launch follows the copies.
   const bool direct = n_sel > 0 && (!any_host || (streamed && stream_in_skips_selected()));

@@ -26,8 +26,8 @@
 
 namespace ct {
 
-// One workgroup of 1024 threads per compute unit.  (Two of 512 threads with half the strip each
-// were measured: no faster, the kernel is bound by vector instructions, not by waiting.)
+// One workgroup of 1024 threads per compute unit (two of 512 with half the columns each read the rows in 16-byte
+// pieces: figures at freq_fixed_kernel).
 constexpr int kFreqThreads = 1024;
 constexpr int kFreqMaxElems = 16384;   // complex values of a strip held in LDS (16 per thread)
 constexpr int kFreqMaxTokens = 4096;
@@ -162,7 +162,7 @@ constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppMirr
 // of values first .. first + max(1, 16 / CP) - 1 in e[0 ..].
 template <int CP>
 __device__ __forceinline__ int reduce_scatter16(float (&e)[16], int c) {
-  int first = 0, h = 16;
+  int first = 0;
   if constexpr (CP >= 64) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) e[i] += __shfl_xor(e[i], 32);
@@ -191,7 +191,6 @@ __device__ __forceinline__ int reduce_scatter16(float (&e)[16], int c) {
     halve<kDppXor1, 4>(e, c & 1);
     first = (c & 2 ? 8 : 0) + (c & 1 ? 4 : 0);
   }
-  (void)h;
   return first;
 }
 
@@ -519,7 +518,7 @@ __device__ __forceinline__ void mix_first(float2* data, const float2* tw, const 
     }
   }
 }
-// Its inverse: `store(i, row, c, value)` takes the results.
+// Its inverse: `done(v, u, m0, c)` takes the results, v[i] being row u + i m0 of sequence c.
 template <int R, int T, class Done>
 __device__ __forceinline__ void mix_last(const float2* data, const float2* tw, const MixPlan& p, Done&& done) {
   const int m0 = p.r1 * p.r2, nb = m0 << p.lg_cp, step = (p.r1 * p.pitch) << p.lg_cp;
@@ -558,7 +557,7 @@ __device__ __forceinline__ void mix_second(float2* data, const float2* tw1, cons
   }
 }
 // Third stage: rows j R2 + i (i < R2), j = k0 R1 + k1, bins bin0 + i R0 R1 with bin0 = k0 + R0 k1.
-// `mid(v, bin0, bin_step, c, place)` does what belongs between the two transforms, from and to registers;
+// `mid(v, bin0, bin_step, c)` does what belongs between the two transforms, from and to registers;
 // LOAD / STORE: the values come from, and go back to, LDS.
 template <int R, int T, bool LOAD, bool STORE, class Mid>
 __device__ __forceinline__ void mix_third(float2* data, const MixPlan& p, Mid&& mid) {
@@ -606,6 +605,9 @@ __device__ __forceinline__ void write_energy(const float2 (&v)[R], int lg, int c
 // Sequences that fit: as freq_fixed_kernel, a persistent workgroup per compute unit.  Bound by vector instructions
 // and LDS accesses.  K and V, against sorting Stockham passes (one per radix up to 16, two barriers each):
 // 4 x 1500 x 1024 75 -> 35 us, 4 x 3072 x 1024 158 -> 80 us, 4 x 4050 x 1000 303 -> 144 us; errors are smaller.
+// (One token per sequence, which needs no transform, takes a microsecond longer: 8.3 -> 9.4 us with the finishing
+// launch.)  The passes of all radices in one body hold more scalar values than there are registers: 111 of them
+// here, 100 in freq_long_c_kernel, are kept in lanes of vector registers; none goes to memory.
 __global__ __launch_bounds__(kFreqThreads) void freq_mixed_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                                   int64_t batch_stride, int32_t row_elems, int32_t n_work,
                                                                   int32_t groups, MixPlan p, float* __restrict__ partial) {
@@ -815,7 +817,7 @@ __global__ __launch_bounds__(kFreqLongThreads) void freq_long_c_kernel(const flo
 // memory speed (32 x 2048 tokens, 64 groups: 7 us against 19 us with a thread per token), and the
 // quarters are added in a fixed order.
 __global__ __launch_bounds__(256) void freq_finish_kernel(const float* __restrict__ partial, int32_t n, int32_t groups,
-                                                          int32_t n_batch, float* __restrict__ scores) {
+                                                          float* __restrict__ scores) {
   __shared__ float part[2][4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int blocks = (n + 63) / 64;                 // workgroups per sequence
@@ -1144,7 +1146,7 @@ ct_status ct_frequency_scores(const void* k, const void* v, int32_t n_batch, int
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "long-sequence frequency score launch");
     launch_kernel(KC_FREQ, freq_finish_kernel, dim3((unsigned)((int64_t)n_batch * ((n_tokens + 63) / 64))), dim3(256), 0, s,
-                  (const float*)partial, n_tokens, groups, n_batch, scores);
+                  (const float*)partial, n_tokens, groups, scores);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "frequency score finish launch");
     return CT_OK;
@@ -1186,7 +1188,7 @@ ct_status ct_frequency_scores(const void* k, const void* v, int32_t n_batch, int
     launch_kernel(KC_FREQ, freq_mixed_kernel, dim3(grid), dim3(kFreqThreads), (unsigned)p.mix.lds_bytes(0), s,
                   (const uint16_t*)k, (const uint16_t*)v, batch_stride, row_elems, n_work, p.groups, p.mix, (float*)workspace);
   launch_kernel(KC_FREQ, freq_finish_kernel, dim3((unsigned)((int64_t)n_batch * ((n_tokens + 63) / 64))), dim3(256), 0, s,
-                (const float*)workspace, n_tokens, p.groups, n_batch, scores);
+                (const float*)workspace, n_tokens, p.groups, scores);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "frequency score launch");
   return CT_OK;

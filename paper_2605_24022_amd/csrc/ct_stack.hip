@@ -331,7 +331,8 @@ ct_status ct_partial_prefill_stack_tap(const ct_layer_cfg* cfg, int32_t ffn_dim,
     if ((st = launch_rmsnorm(hidden_sel, lw.attn_norm, rms_eps, n_sel, cfg->hidden, ws + L.x_norm, cs)) != CT_OK) return st;
     // The projection's epilogue writes the recomputed keys and values straight to their rows of
     // the layer buffers unless plain host copies, which overwrite those rows at a time of their
-    // own, bring this layer's chunks in; device chunks are rotated into place first.
+    // own, bring this layer's chunks in.  The rotation of device chunks, ahead of the projection or beside it in
+    // one launch, skips those rows.
     bool host_here = false;
     for (int c = 0; c < n_chunks && !full; ++c) host_here |= lw.chunks[c].location != 0;
     const bool direct = full || !host_here || (streamed[l & 1] && stream_in_skips_selected());
