@@ -5,13 +5,17 @@
 //   S^T = K Q^T            A = K tile rows (keys) from LDS,       B = Q^T kept in registers
 //   O^T += V^T P^T         A = V^T (head_dim x keys) from LDS,    B = P^T taken straight from
 //                                                                     the S^T accumulators
-// In the 32x32 MFMA accumulator layout lane l holds column l%32 (one query) and 16 rows
-// (keys), so the row maximum and row sum of the softmax are in-lane reductions plus one
-// exchange with lane l^32, the rescale factor of the online softmax is a per-lane scalar,
-// and the probabilities need no trip through LDS: accumulator registers 8t..8t+7 of an
-// S^T tile are exactly the B operand of PV step t once V^T is stored in LDS with the same
-// key order (keys of a 32-key sub-tile are laid out as 16-byte units (t, lane-half) holding
-// keys 16t + 8a + 4*half + b, a in {0,1}, b in 0..3).
+// In the 16x16 MFMA accumulator layout lane l holds column l%16 (one query) and 4 rows (keys) of each
+// tile, so the row maximum and row sum of the softmax are in-lane reductions plus an exchange
+// between the four rows of 16 lanes, the rescale factor of the online softmax is a per-lane
+// scalar per column tile, and the probabilities need no trip through LDS: the accumulators of the
+// 16-key tiles 2t and 2t+1 are exactly the B operand of PV step t (32 keys) once V^T is read in the
+// same key order (lane row h takes keys 32t + 4h + 0..3 and 32t + 16 + 4h + 0..3).
+// 16 x 16 x 32 and not 32 x 32 x 16: the chip is limited by power, and an accumulator tile that is
+// read and written half as often per flop costs less of it (nothing but MFMAs on data-like operands:
+// 2.10 PFLOP/s against 1.83).  32768 tokens, 32/8 heads of 128, all rows: 7.59 -> 7.07 ms, 4915 rows
+// 1.258 -> 1.189 ms; where the clock is not held down by power (few workgroups) the twice as many
+// instructions take back part of it.
 //
 // Work decomposition.  A workgroup (8 waves, two per SIMD) owns one KV head and a tile of 256
 // query columns = (256 / G) selected tokens x the G query heads of that KV head; every wave
@@ -26,6 +30,8 @@
 // keys of one head through its own L2; tiles are issued heaviest first.
 #include <math.h>
 #include <stdlib.h>
+
+#include <type_traits>
 
 #include "ct_internal.h"
 
@@ -80,19 +86,20 @@ __host__ __device__ inline int tile_load_row(int k0, int row_in_tile, int k_hi) 
   return key < k_hi - 1 ? key : k_hi - 1;
 }
 
-// v_permlane32_swap exchanges the upper half of the first operand with the lower half of
-// the second: with both operands x, result[0] is (x | partner) and result[1] is
-// (partner | x) over (lanes 0-31 | lanes 32-63), so any commutative combination of the two
-// results combines every lane with lane ^ 32.
-__device__ __forceinline__ float max_with_lane_xor32(float x) {
-  const uint32_t u = __float_as_uint(x);
-  auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_with_lane_xor32(float x) {
-  const uint32_t u = __float_as_uint(x);
-  auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+// Reductions over the four 16-lane rows of a wave, of two values x and y at once.
+// v_permlane32_swap exchanges the upper half of its first operand with the lower half of the second:
+// combining its two results leaves x over (l, l ^ 32) in the lower half and y in the upper one.
+// v_permlane16_swap exchanges the odd rows of the first with the even rows of the second, which adds the
+// other row of each half, and a last v_permlane32_swap hands both results to all lanes.
+template <typename Op>
+__device__ __forceinline__ void reduce_rows(float& x, float& y, Op op) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  uint32_t c = __float_as_uint(op(__uint_as_float(r[0]), __uint_as_float(r[1])));
+  r = __builtin_amdgcn_permlane16_swap(c, c, false, false);
+  c = __float_as_uint(op(__uint_as_float(r[0]), __uint_as_float(r[1])));
+  r = __builtin_amdgcn_permlane32_swap(c, c, false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
 }
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -104,15 +111,13 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 template <int D>
 __device__ __forceinline__ int swz_k(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
 template <int D>
-__device__ __forceinline__ int swz_v(int r) {
-  return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : (((r & 1) << 2) | ((r >> 1) & 3));
-}
+__device__ __forceinline__ int swz_v(int r) { return D == 128 ? (r & 7) << 1 : ((r >> 1) & 3) << 1; }
 
-// A workgroup has 8 waves, two per SIMD; every wave owns 32 query columns (one MFMA column
-// tile) and all keys, so the workgroup owns 256 query columns.
+// A workgroup has 8 waves, two per SIMD; every wave owns 32 query columns (two MFMA column
+// tiles) and all keys, so the workgroup owns 256 query columns.
 //
 // Ping-pong schedule.  The work of a wave on key tile i splits into a matrix-core part
-//   M(i): O^T += V^T(i-1) P^T(i-1), then S^T(i) = K(i) Q^T            (32 MFMAs)
+//   M(i): O^T += V^T(i-1) P^T(i-1), then S^T(i) = K(i) Q^T            (64 MFMAs)
 // and a vector-ALU part
 //   V(i): causal mask, online softmax of S^T(i) into P^T(i), rescale of O^T.
 // The loop runs in periods separated by one workgroup barrier.  Waves 0-3 (one per SIMD) run
@@ -122,6 +127,9 @@ __device__ __forceinline__ int swz_v(int r) {
 // there makes every wave wait for the slowest of eight twice per period: measured 2 % slower).
 // K(i) and V(i-1) are the tiles in use during period i; K(i+2) and V(i+1) are fetched during
 // it with direct global->LDS loads into three K and three V stages.
+// One loop for both groups, V(i) then M(i+1), with the barrier between the two for waves 0-3 and
+// behind them for waves 4-7: written as two loops, the compiler kept the initial accumulators for both
+// (253 registers and scratch reloads in the loop; 191 now).
 template <int D>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_kernel(AttnArgs a) {
   constexpr int NWAVES = 8;
@@ -129,8 +137,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int NST = 3;                       // LDS stages per tensor
   constexpr int ROWB = D * 2;                  // bytes per key row in LDS (no padding)
   constexpr int TILE_BYTES = BN * ROWB;        // one K (or V) tile
-  constexpr int KS = D / 16;                   // MFMA k-steps over head_dim
-  constexpr int MT = D / 32;                   // O^T row tiles
+  constexpr int KS = D / 32;                   // MFMA k-steps over head_dim
+  constexpr int MT = D / 16;                   // O^T row tiles
   constexpr int PCS = D / 8;                   // 16-byte pieces per key row
   constexpr int RPI = 64 / PCS;                // key rows covered by one wave-wide 16-byte load
   constexpr int INSTS = BN / RPI / NWAVES;     // such loads per wave, tile and tensor
@@ -140,7 +148,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __shared__ __align__(1024) unsigned char v_lds[NST * TILE_BYTES];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, hi = lane >> 5;
+  const int l16 = lane & 15, h = lane >> 4;
   const bool group_b = wave >= NWAVES / 2;
 
   // ---- work item ---------------------------------------------------------------------------
@@ -159,27 +167,31 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int k_lo = item.k_lo, k_hi = item.k_hi;
   const int n_kt = (k_hi - k_lo + BN - 1) / BN;
 
-  // ---- this lane's query column ------------------------------------------------------------------
-  const int col = wave * 32 + l32;
-  const int tok_raw = tok0 + (col & (a.TM - 1));
-  const bool valid = tok_raw < a.n_sel;
-  const int tokv = valid ? tok_raw : a.n_sel - 1;
-  const int hq = g * a.G + (col >> a.tm_shift);
-  // keys from k_hi on belong to a later launch (or to nobody): the causal mask is taken against
-  // min(position, k_hi - 1), which cuts the last key tile of the range where the range ends
-  const int pos = min(a.sel_idx[tokv], k_hi - 1);
-  int wmin = pos;
+  // ---- this lane's two query columns (16 apart) ----------------------------------------------------
+  // row of q and out behind the lane's column n (of a token that is not there: the last one's)
+  auto query_row = [&](int col, bool& valid, int& tokv) __attribute__((always_inline)) -> size_t {
+    const int tok_raw = tok0 + (col & (a.TM - 1));
+    valid = tok_raw < a.n_sel;
+    tokv = valid ? tok_raw : a.n_sel - 1;
+    return (size_t)tokv * a.Hq + g * a.G + (col >> a.tm_shift);
+  };
+  int pos[2];
+  bf16x8 qf[2][KS];     // Q^T fragments: B operand, lane = column, 8 consecutive head_dim elements per k-step
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) wmin = min(wmin, __shfl_xor(wmin, off));
-  wmin = __builtin_amdgcn_readfirstlane(wmin);
-
-  // Q^T fragments: B operand, lane = column, 8 consecutive head_dim elements per k-step
-  bf16x8 qf[KS];
-  {
-    const uint16_t* qp = a.q + ((size_t)tokv * a.Hq + hq) * D + hi * 8;
+  for (int n = 0; n < 2; ++n) {
+    bool valid;
+    int tokv;
+    const uint16_t* qp = a.q + query_row(wave * 32 + l16 + 16 * n, valid, tokv) * D + h * 8;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
+    for (int ks = 0; ks < KS; ++ks) qf[n][ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 32);
+    // keys from k_hi on belong to a later launch (or to nobody): the causal mask is taken against
+    // min(position, k_hi - 1), which cuts the last key tile of the range where the range ends
+    pos[n] = min(a.sel_idx[tokv], k_hi - 1);
   }
+  int wmin = min(pos[0], pos[1]);
+#pragma unroll
+  for (int off = 8; off >= 1; off >>= 1) wmin = min(wmin, __shfl_xor(wmin, off));
+  wmin = __builtin_amdgcn_readfirstlane(wmin);
 
   // ---- global -> LDS staging (direct loads, no registers) ----------------------------------
   // load i of this wave fills LDS rows (NWAVES * i + wave) * RPI .. + RPI - 1 of a tile; this
@@ -216,102 +228,114 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
 
   // ---- per-lane LDS read offsets ----------------------------------------------------------------
-  // K fragment (sub-tile u, k-step ks): row 32u + l32, logical piece 2ks + hi, i.e. byte offset
-  //   l32 * ROWB + ((2ks + hi) ^ swizzle) * 16 + u * 32 * ROWB  =  (k_a ^ (ks << 5)) + u * 32 * ROWB,
+  // K fragment (16-key tile u, k-step ks): row 16u + l16, logical piece 4ks + h, i.e. byte offset
+  //   l16 * ROWB + ((4ks + h) ^ swizzle) * 16 + u * 16 * ROWB  =  (k_a ^ (ks << 6)) + u * 16 * ROWB,
   // because the swizzle is an exclusive-or on bits the row term leaves clear: one register holds
   // k_a and every fragment address is that register exclusive-or a constant.
-  const int k_a = l32 * ROWB + ((hi ^ swz_k<D>(l32)) * 16);
-  // V^T fragment (row tile m, sub-tile u, step t, half a2): 16-lane block b reads 4 key rows x
+  const int k_a = l16 * ROWB + ((h ^ swz_k<D>(l16)) * 16);
+  // V^T fragment (row tile m, 32-key step t, half a2): 16-lane block h reads 4 key rows x
   // 16 head_dim columns; lane j of the block addresses row j / 4, 8-byte chunk j % 4:
-  //   r = 8 a2 + 4 hi + j / 4 (+ 32u + 16t, which leave the swizzle unchanged), piece pc = 4m + 2 (lane / 16 % 2) + j % 4 / 2,
-  //   offset r * ROWB + (pc ^ swizzle(r)) * 16 + 8 (j % 2)  =  (v_a ^ (m << 6) ^ (a2 << 5, D = 128 only)) + a2 * 8 * ROWB
-  // for the same reason (checked for every lane, m and a2 on the host when this was written).
-  const int vj = lane & 15, vdh = (lane >> 4) & 1;
-  const int v_a = (4 * hi + (vj >> 2)) * ROWB + (((2 * vdh + ((vj & 3) >> 1)) ^ swz_v<D>(4 * hi + (vj >> 2))) * 16) + 8 * (vj & 1);
-  constexpr int V_A2_XOR = D == 128 ? 32 : 0;
+  //   r = 4h + j / 4 (+ 32t + 16 a2, which leave the swizzle unchanged), piece pc = 2m + j % 4 / 2,
+  //   offset r * ROWB + (pc ^ swizzle(r)) * 16 + 8 (j % 2)  =  (v_a ^ (m << 5)) + (32t + 16 a2) * ROWB.
+  const int v_r = 4 * h + (l16 >> 2);
+  const int v_a = v_r * ROWB + ((((l16 & 3) >> 1) ^ swz_v<D>(v_r)) * 16) + 8 * (l16 & 1);
 
   // ---- state ---------------------------------------------------------------------------------------
-  f32x16 o[MT];
+  f32x4 o[MT][2];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[m][i] = 0.f;
-  float m_run = -INFINITY;
-  float l_run = 0.f;   // per-lane partial row sum; lanes l and l^32 are added at the end
+    for (int n = 0; n < 2; ++n) o[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run[2] = {-INFINITY, -INFINITY};
+  float l_run[2] = {0.f, 0.f};   // per-lane partial row sums; the four rows of lanes are added at the end
   if (resumable && k_lo > 0) {   // what the launch for the previous key range left
     const float* base = a.state + ((size_t)tile * a.Hkv + g) * (size_t)(COLS * (D + 2));
-    const float* op = base + (size_t)col * D + 4 * hi;
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int n = 0; n < 2; ++n) {
+      const int col = wave * 32 + l16 + 16 * n;
+      const float* op = base + (size_t)col * D + 4 * h;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x4 w = *reinterpret_cast<const f32x4*>(op + m * 32 + 8 * q4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[m][4 * q4 + e] = w[e];
-      }
-    m_run = base[COLS * D + col];
-    l_run = hi == 0 ? base[COLS * D + COLS + col] : 0.f;
+      for (int m = 0; m < MT; ++m) o[m][n] = *reinterpret_cast<const f32x4*>(op + m * 16);
+      m_run[n] = base[COLS * D + col];
+      l_run[n] = h == 0 ? base[COLS * D + COLS + col] : 0.f;
+    }
   }
-  f32x16 s[2];         // S^T of the tile whose scores were computed last (two 32-key sub-tiles)
-  bf16x8 pf[2][2];     // P^T fragments (sub-tile u, 16-key step t) of the tile whose softmax was done last
+  // scores above which the reference of the exponents moves: 2^8 above it
+  const float limit_step = 8.0f / a.scale_log2;
+  float m_limit[2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+  for (int n = 0; n < 2; ++n) m_limit[n] = m_run[n] == -INFINITY ? -INFINITY : m_run[n] / a.scale_log2 + limit_step;
+  f32x4 s[4][2];       // S^T of the tile whose scores were computed last (four 16-key tiles)
+  bf16x8 pf[2][2];     // P^T fragments (32-key step t, column tile n) of the tile whose softmax was done last
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) pf[u][t][e] = (__bf16)0.0f;
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pf[t][n][e] = (__bf16)0.0f;
 
   typedef __attribute__((ext_vector_type(8))) short s16x8;
-  auto load_vfrag = [&](const unsigned char* vrow, int m) __attribute__((always_inline)) -> bf16x8 {
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vrow + (v_a ^ (m << 6))));
-    const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) s16x4*)(vrow + ((v_a ^ (m << 6) ^ V_A2_XOR) + 8 * ROWB)));
-    const s16x8 both = __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
-    return *reinterpret_cast<const bf16x8*>(&both);
-  };
 
   // ---- M part: O^T += V^T P^T (previous tile), S^T = K Q^T (this tile) ----------------------------
-  // One stream of NPV + NQK (fragment read, MFMA) steps.  A step needs one A fragment from LDS;
-  // with one wave per SIMD in this part nothing else hides the LDS latency, so the reads run PD
-  // fragments (PD * 32 MFMA cycles) ahead of their MFMAs through a ring of PD + 1 fragment
-  // registers, across the PV -> QK boundary as well.  The first PD fragments are read before the
-  // first MFMA can issue (a wave issues in order, one LDS instruction per ~15 cycles), so the
-  // distance is no longer than the LDS latency asks for: 3 or 4 (7 costs 1.5 %, 2 costs 1 %).
+  // One stream of NPV + NQK fragments, two MFMAs (one per column tile) each.  With one wave per SIMD in
+  // this part nothing else hides the LDS latency, so the reads run PD fragments ahead of their MFMAs
+  // through a ring of PD + 1, across the PV -> QK boundary as well, one LDS instruction per MFMA:
+  // a wave issues in order, one LDS instruction per ~15 cycles, about the time of an MFMA (both reads
+  // of a V^T fragment in a row: 3 % of the launch).  Distances of 2 to 6 measure the same within 0.3 %.
   // The wave runs it at raised priority: its instruction stream is sparse and must not queue
-  // behind the dense softmax stream of the other wave on the SIMD.
-  // The first period has no previous tile and the last one no next tile; both still run the
-  // whole stream (P^T = 0 in the first, S^T unused in the last, the stages hold loaded data).
-  constexpr int NPV = 4 * MT, NQK = 2 * KS;
+  // behind the dense softmax stream of the other wave on the SIMD (without: 4 to 6 % of the launch).
+  // The first M part has no previous tile and runs the QK half alone, the last one the PV half.
+  constexpr int NPV = 2 * MT, NQK = 4 * KS;
 #ifndef CT_ATTN_PD
 #define CT_ATTN_PD 4
 #endif
   constexpr int PD = CT_ATTN_PD;
-  auto load_frag = [&](int j, const unsigned char* vb, const unsigned char* kb) __attribute__((always_inline)) -> bf16x8 {
-    if (j < NPV) return load_vfrag(vb + 16 * (j / MT) * ROWB, j % MT);
-    const int ks = (j - NPV) >> 1, u = (j - NPV) & 1;
-    return *reinterpret_cast<const bf16x8*>(kb + (k_a ^ (ks << 5)) + u * 32 * ROWB);
+  // V^T fragments take two LDS instructions (halves of their keys), K fragments one.
+  s16x8 fr[PD + 1];
+  auto load_first = [&](int j, const unsigned char* vb, const unsigned char* kb) __attribute__((always_inline)) {
+    s16x8& f = fr[j % (PD + 1)];
+    if (j < NPV) {
+      const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) s16x4*)(vb + 32 * (j / MT) * ROWB + (v_a ^ ((j % MT) << 5))));
+      f = __builtin_shufflevector(x, x, 0, 1, 2, 3, -1, -1, -1, -1);
+    } else {
+      const int ks = (j - NPV) >> 2, u = (j - NPV) & 3;
+      f = *reinterpret_cast<const s16x8*>(kb + (k_a ^ (ks << 6)) + u * 16 * ROWB);
+    }
   };
-  auto part_m = [&](const unsigned char* vb, const unsigned char* kb, auto&& dma) __attribute__((always_inline)) {
+  auto load_second = [&](int j, const unsigned char* vb) __attribute__((always_inline)) {
+    if (j >= NPV) return;
+    s16x8& f = fr[j % (PD + 1)];
+    const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) s16x4*)(vb + (32 * (j / MT) + 16) * ROWB + (v_a ^ ((j % MT) << 5))));
+    f = __builtin_shufflevector(f, __builtin_shufflevector(x, x, 0, 1, 2, 3, -1, -1, -1, -1), 0, 1, 2, 3, 8, 9, 10, 11);
+  };
+  auto part_m = [&](auto first, auto end, const unsigned char* vb, const unsigned char* kb, auto&& dma) __attribute__((always_inline)) {
+    constexpr int J0 = decltype(first)::value, J1 = decltype(end)::value;
     __builtin_amdgcn_s_setprio(3);
-    bf16x8 fr[PD + 1];
 #pragma unroll
-    for (int j = 0; j < PD; ++j) fr[j] = load_frag(j, vb, kb);
+    for (int j = J0; j < J0 + PD; ++j) {
+      load_first(j, vb, kb);
+      load_second(j, vb);
+    }
     dma();   // behind the first fragment reads: issued while the wave would wait for them anyway
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int j = J0; j < J1; ++j) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[u][i] = 0.f;
-#pragma unroll
-    for (int j = 0; j < NPV + NQK; ++j) {
-      if (j + PD < NPV + NQK) fr[(j + PD) % (PD + 1)] = load_frag(j + PD, vb, kb);
-      if (j < NPV) {
-        const int gi = j / MT, m = j % MT;
-        o[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j % (PD + 1)], pf[gi >> 1][gi & 1], o[m], 0, 0, 0);
-      } else {
-        const int ks = (j - NPV) >> 1, u = (j - NPV) & 1;
-        s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j % (PD + 1)], qf[ks], s[u], 0, 0, 0);
+      for (int n = 0; n < 2; ++n) {
+        if (j + PD < J1 && n == 0) load_first(j + PD, vb, kb);
+        if (j + PD < J1 && n == 1) load_second(j + PD, vb);
+        const bf16x8 f = *reinterpret_cast<const bf16x8*>(&fr[j % (PD + 1)]);
+        if (j < NPV) {
+          const int t = j / MT, m = j % MT;
+          o[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, pf[t][n], o[m][n], 0, 0, 0);
+        } else {
+          const int ks = (j - NPV) >> 2, u = (j - NPV) & 3;
+          const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+          s[u][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, qf[n][ks], ks == 0 ? zero : s[u][n], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // keep the read-ahead distance as written
       }
-      __builtin_amdgcn_sched_barrier(0);   // keep the read-ahead distance as written
     }
     __builtin_amdgcn_s_setprio(0);
   };
@@ -319,57 +343,74 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // ---- V part: causal mask, online softmax, P^T fragments, rescale of O^T -------------------------
   auto part_v = [&](int k0) __attribute__((always_inline)) {
     if (k0 + BN - 1 > wmin) {   // only tiles that reach past the earliest query of this wave
-      const int rel = pos - k0 - 4 * hi;   // key offsets (32u + 8(i/4) + i%4) <= rel are visible
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+      for (int n = 0; n < 2; ++n) {
+        const int rel = pos[n] - k0 - 4 * h;   // key offsets 16u + i <= rel are visible
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (32 * u + 8 * (i >> 2) + (i & 3) > rel) s[u][i] = -INFINITY;
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (16 * u + i > rel) s[u][n][i] = -INFINITY;
+      }
     }
-    float mx = s[0][0];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[u][i]);
-    mx = max_with_lane_xor32(mx);
     // The reference of the exponents follows the running maximum lazily: it moves only when the
     // tile's maximum exceeds it by more than 2^8, so probabilities stay below 256 (bf16 keeps
     // their relative precision, the sums are fp32) and the rescale of O^T becomes rare.  A
     // rescale in one wave holds up the whole workgroup at the next barrier, and with the exact
     // maximum some wave of the eight has one in most periods.
-    const float m_tile = mx * a.scale_log2;
-    const bool changed = m_tile > m_run + 8.0f;
-    const float m_new = changed ? m_tile : m_run;
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = changed ? __builtin_amdgcn_exp2f(m_run - m_use) : 1.0f;
-    m_run = m_new;
-    float rs0 = 0.f, rs1 = 0.f;
+    float mx[2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int n = 0; n < 2; ++n) {
+      mx[n] = m_limit[n];
 #pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][i], a.scale_log2, -m_use));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][i + 1], a.scale_log2, -m_use));
-        s[u][i] = p0;
-        s[u][i + 1] = p1;
-        rs0 += p0;
-        rs1 += p1;
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx[n] = fmaxf(mx[n], s[u][n][i]);
+    }
+    reduce_rows(mx[0], mx[1], [](float x, float y) { return fmaxf(x, y); });
+    if (__any(mx[0] > m_limit[0] || mx[1] > m_limit[1])) {
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        if (mx[n] > m_limit[n]) {
+          const float m_new = mx[n] * a.scale_log2;
+          const float alpha = __builtin_amdgcn_exp2f(m_run[n] - m_new);   // (0 from the first reference on)
+          m_run[n] = m_new;
+          m_limit[n] = mx[n] + limit_step;
+          l_run[n] *= alpha;
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[m][n][i] *= alpha;
+        }
       }
-    l_run = l_run * alpha + (rs0 + rs1);
+    }
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int n = 0; n < 2; ++n) {
+      const float m_use = m_run[n] == -INFINITY ? 0.f : m_run[n];
+      float rs0 = l_run[n], rs1 = 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][n][i], a.scale_log2, -m_use));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][n][i + 1], a.scale_log2, -m_use));
+          s[u][n][i] = p0;
+          s[u][n][i + 1] = p1;
+          rs0 += p0;
+          rs1 = u + i == 0 ? p1 : rs1 + p1;
+        }
+      l_run[n] = rs0 + rs1;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         u32x4 w;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = pack_bf16(s[u][8 * t + 2 * e], s[u][8 * t + 2 * e + 1]);
-        pf[u][t] = *reinterpret_cast<bf16x8*>(&w);
+        for (int e = 0; e < 4; ++e) w[e] = pack_bf16(s[2 * t + (e >> 1)][n][2 * (e & 1)], s[2 * t + (e >> 1)][n][2 * (e & 1) + 1]);
+        asm volatile("" : "+v"(w));   // (as below)
+        pf[t][n] = *reinterpret_cast<bf16x8*>(&w);
       }
-    if (__any(changed)) {
-#pragma unroll
-      for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[m][i] *= alpha;
+      // done here, ahead of the barrier: left alone, the compiler moves the sums behind the matrix part and the
+      // exponentials behind the barrier
+      asm volatile("" : "+v"(l_run[n]));
     }
   };
 
@@ -383,82 +424,81 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // wait for the look-ahead tile loads.
   __builtin_amdgcn_s_waitcnt(0x0f70);
   issue_rows(a.k, k_lane_off, k_lo, k_lds_addr);                           // K(0)
-  issue_rows(a.v, v_lane_off, k_lo, v_lds_addr + 2 * TILE_BYTES);          // stands in for V(-1): keeps the load count uniform
   issue_rows(a.k, k_lane_off, k_lo + BN, k_lds_addr + TILE_BYTES);         // K(1)
   issue_rows(a.v, v_lane_off, k_lo, v_lds_addr);                           // V(0)
-  __builtin_amdgcn_s_waitcnt(WAIT_OLDER);                                  // K(0) has landed (and the stand-in)
+  __builtin_amdgcn_s_waitcnt(WAIT_OLDER);                                  // K(0) has landed
   __syncthreads();
   auto end_of_period = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(WAIT_OLDER);     // this wave's loads of the previous period have landed
     __syncthreads();                            // everybody's have; everybody is done with K(i), V(i-1)
   };
   // Period i uses K(i) and V(i-1); its M parts fetch K(i+2) and V(i+1) into the stages of
-  // K(i-1) and V(i-2), which nobody reads any more.  The two groups run separate loops with
-  // the same number of barriers; nothing but the order of the two parts differs, and no barrier
-  // is needed between them: both groups read the same tiles for the whole period.
+  // K(i-1) and V(i-2), which nobody reads any more.  Nothing but the place of the barrier differs
+  // between the two groups: both read the same tiles for the whole period.
   // The look-ahead loads of period i (K(i+2), V(i+1)) are issued by each wave at the start of its
-  // M part, right behind the first fragment reads: the wave has to wait for those anyway, so the
-  // queueing of the four waves' loads at the texture addresser costs it nothing there (measured:
-  // anywhere later in the MFMA stream it costs 4.5 %, before the softmax part 1.5 %).
+  // M part, right behind the first fragment reads (at the start of the QK half instead: the same within 0.5 %).
   auto refill = [&](int i, int st_im1, int st_ip1) __attribute__((always_inline)) {
     issue_rows(a.k, k_lane_off, k_lo + (i + 2) * BN, k_lds_addr + st_im1 * TILE_BYTES);
     issue_rows(a.v, v_lane_off, k_lo + (i + 1) * BN, v_lds_addr + st_ip1 * TILE_BYTES);
   };
-  int st_i = 0, st_im1 = 2;                     // stage indices of tiles i and i - 1 (i mod 3)
-  if (!group_b) {
-    for (int i = 0; i <= n_kt; ++i) {
-      const int st_ip1 = st_i == 2 ? 0 : st_i + 1;
-      part_m(v_lds + st_im1 * TILE_BYTES, k_lds + st_i * TILE_BYTES, [&]() __attribute__((always_inline)) { refill(i, st_im1, st_ip1); });
-      if (i < n_kt) part_v(k_lo + i * BN);
-      end_of_period();
-      st_im1 = st_i;
-      st_i = st_ip1;
-    }
-  } else {
-    for (int i = 0; i <= n_kt; ++i) {
-      const int st_ip1 = st_i == 2 ? 0 : st_i + 1;
-      if (i >= 1) part_v(k_lo + (i - 1) * BN);
-      part_m(v_lds + st_im1 * TILE_BYTES, k_lds + st_i * TILE_BYTES, [&]() __attribute__((always_inline)) { refill(i, st_im1, st_ip1); });
-      end_of_period();
-      st_im1 = st_i;
-      st_i = st_ip1;
-    }
+  int st_i = 0;                                 // stage of tile i (i mod 3)
+  using J0 = std::integral_constant<int, 0>;
+  using JQK = std::integral_constant<int, NPV>;
+  using JEND = std::integral_constant<int, NPV + NQK>;
+  part_m(JQK{}, JEND{}, v_lds, k_lds, [&]() __attribute__((always_inline)) { refill(0, 2, 1); });
+  if (group_b) end_of_period();
+  for (int i = 0; i + 1 < n_kt; ++i) {
+    const int st_ip1 = st_i == 2 ? 0 : st_i + 1, st_ip2 = st_ip1 == 2 ? 0 : st_ip1 + 1;
+    part_v(k_lo + i * BN);
+    if (!group_b) end_of_period();
+    part_m(J0{}, JEND{}, v_lds + st_i * TILE_BYTES, k_lds + st_ip1 * TILE_BYTES,
+           [&]() __attribute__((always_inline)) { refill(i + 1, st_i, st_ip2); });
+    if (group_b) end_of_period();
+    st_i = st_ip1;
   }
+  part_v(k_lo + (n_kt - 1) * BN);
+  if (!group_b) end_of_period();
+  part_m(J0{}, JQK{}, v_lds + st_i * TILE_BYTES, k_lds, []() __attribute__((always_inline)) {});
   __builtin_amdgcn_s_waitcnt(0x0f70);           // drain the look-ahead loads before the LDS is released
 
   // ---- epilogue -------------------------------------------------------------------------------
-  const float l_tot = sum_with_lane_xor32(l_run);
+  float l_tot[2] = {l_run[0], l_run[1]};
+  reduce_rows(l_tot[0], l_tot[1], [](float x, float y) { return x + y; });
+  int tid_e = threadIdx.x;
+  asm("" : "+v"(tid_e));   // places of the results are worked out again here: nothing of them stays in registers during the loop
+  const int col_e = (tid_e >> 6) * 32 + (tid_e & 15), h_e = (tid_e >> 4) & 3;
   if (resumable ? k_hi == kmax : kmax <= a.split_keys) {   // the tile's key range ends here: final result
-    if (valid) {
-      const float inv = 1.0f / l_tot;
-      uint16_t* op = a.out + ((size_t)tokv * a.Hq + hq) * D + 4 * hi;
 #pragma unroll
-      for (int m = 0; m < MT; ++m)
+    for (int n = 0; n < 2; ++n) {
+      bool valid;
+      int tokv;
+      const size_t row = query_row(col_e + 16 * n, valid, tokv);
+      if (!valid) continue;
+      const float inv = 1.0f / l_tot[n];
+      uint16_t* op = a.out + row * D + 4 * h_e;
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          u32x2 w;
-          w[0] = pack_bf16(o[m][4 * q4 + 0] * inv, o[m][4 * q4 + 1] * inv);
-          w[1] = pack_bf16(o[m][4 * q4 + 2] * inv, o[m][4 * q4 + 3] * inv);
-          *reinterpret_cast<u32x2*>(op + m * 32 + 8 * q4) = w;
-        }
-      if (a.lse != nullptr && hi == 0)
-        a.lse[(size_t)tokv * a.Hq + hq] = (m_run + __builtin_log2f(l_tot)) * 0.69314718055994531f;
+      for (int m = 0; m < MT; ++m) {
+        u32x2 w;
+        w[0] = pack_bf16(o[m][n][0] * inv, o[m][n][1] * inv);
+        w[1] = pack_bf16(o[m][n][2] * inv, o[m][n][3] * inv);
+        *reinterpret_cast<u32x2*>(op + m * 16) = w;
+      }
+      if (a.lse != nullptr && h_e == 0) a.lse[row] = (m_run[n] + __builtin_log2f(l_tot[n])) * 0.69314718055994531f;
     }
   } else {
     // partial results: [item][COLS columns][D] fp32, then m[COLS], l[COLS]
     const size_t item = ((size_t)tile * a.Hkv + g) * a.n_splits + split;
     float* base = (resumable ? a.state : a.partial) + item * (size_t)(COLS * (D + 2));
-    float* op = base + (size_t)col * D + 4 * hi;
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int n = 0; n < 2; ++n) {
+      const int col = col_e + 16 * n;
+      float* op = base + (size_t)col * D + 4 * h_e;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        f32x4 w = {o[m][4 * q4 + 0], o[m][4 * q4 + 1], o[m][4 * q4 + 2], o[m][4 * q4 + 3]};
-        *reinterpret_cast<f32x4*>(op + m * 32 + 8 * q4) = w;
+      for (int m = 0; m < MT; ++m) *reinterpret_cast<f32x4*>(op + m * 16) = o[m][n];
+      if (h_e == 0) {
+        base[COLS * D + col] = m_run[n];
+        base[COLS * D + COLS + col] = l_tot[n];
       }
-    if (hi == 0) {
-      base[COLS * D + col] = m_run;
-      base[COLS * D + COLS + col] = l_tot;
     }
   }
 }
@@ -559,7 +599,7 @@ ct_status launch_attention(const ct_layer_cfg* cfg, const AttnPlan& p, const voi
 }
 
 // Host-side replay of the key rows one launch reads (same item and row functions as the kernel, same
-// tile loads: the prologue's K(0), K(1), V(0) and stand-in, then K(i + 2) and V(i + 1) in period i).
+// tile loads: the prologue's K(0), K(1) and V(0), then K(i + 2) and V(i + 1) in period i < n_kt).
 ct_status attention_rows_read(const ct_layer_cfg* cfg, const int32_t* sel_idx_host, int32_t n_sel, int32_t n_ctx,
                               int32_t key_after, int32_t key_upto, bool resumable, int32_t* first_row,
                               int32_t* last_row) {
@@ -572,7 +612,7 @@ ct_status attention_rows_read(const ct_layer_cfg* cfg, const int32_t* sel_idx_ho
       const ItemRange it = item_range(kmax, split, p.split_keys, resumable, key_after, key_upto);
       if (!it.active) continue;
       const int n_kt = (it.k_hi - it.k_lo + BN - 1) / BN;
-      for (int t = 0; t <= n_kt + 2; ++t)          // tiles 0 .. n_kt + 2 of the item are loaded
+      for (int t = 0; t <= n_kt + 1; ++t)          // tiles 0 .. n_kt + 1 of the item are loaded
         for (int r = 0; r < BN; r += BN - 1) {     // first and last row of a tile bound the others
           const int row = tile_load_row(it.k_lo + t * BN, r, it.k_hi);
           lo = row < lo ? row : lo;
