@@ -6,29 +6,32 @@
 //     projection and FFN down projection with the residual added, and the SwiGLU gate/up pair.
 //
 // The kernel computes the transposed product  C^T[f, t] = sum_e W[f, e] * X[row(t), e]
-// (features in the MFMA M dimension, tokens in N) so that, in the 32x32 accumulator layout,
-// a lane holds one token (column) and groups of four consecutive features (rows):
+// (features in the MFMA M dimension, tokens in N) so that, in the 16x16 accumulator layout,
+// a lane holds one token (column) and four consecutive features (rows) of every tile:
 //   - both elements of every RoPE pair of a token sit in the same lane (no cross-lane
 //     traffic in the epilogue), and the token's position is a per-lane scalar;
-//   - results leave as 16-byte stores of eight consecutive bf16 features (two half waves swap halves).
+//   - results leave as 16-byte stores of eight consecutive bf16 features (odd and even rows of lanes swap halves of
+//     two neighbouring tiles).
 // Both operands are K-contiguous in memory (W is out-features major, X is token major).
 // Tiles go from global memory straight into LDS (global_load_lds_dwordx4, no register
 // staging): a wave-wide load fills 8 rows of 128 bytes, the 16-byte pieces of a row are
 // XOR-swizzled so that the 128-bit fragment reads of 16 consecutive rows hit distinct banks.
 //
 // Workgroup: 512 threads = 8 waves, two to a SIMD; tile 256 features x 256 (or 128) tokens x 64 (K step),
-// 32 x 32 x 16 MFMAs.  Reading the fragments from LDS takes about as long as multiplying them, so the wave tiles are
-// as square as the registers of two waves allow: 64 x 64 on 128 tokens (128 x 32 read a quarter more: QKV of 1228 rows
-// 67 -> 63 us, of 153 rows 47 -> 39 us), 128 x 64 on 256 tokens.
-// LDS holds three weight tiles and two (of 128 tokens: three) token tiles: loads run two and one
-// (two) K steps ahead.  One barrier per K step, ahead of the step's last MFMA group so
-// that it passes while the matrix core is busy.  On 128-token tiles fragment reads and tile loads go out one by one
-// between the MFMAs (sent in bursts ahead of each group of MFMAs they held it up: gate/up, K = 4096, n = 1638:
-// 400 -> 350 us together with the 64 x 64 tiles); on 256-token tiles they stay in bursts.
-// Not kept on 256-token tiles: four waves with 128 x 128 each, which read a third less from LDS but have one wave to
-// hide an epilogue behind (and with a residual spill): linear 2458 x 4096 x 4096 with weights from memory 107 us against
-// 101, 4915 x 2048 x 2048 71 / 63, gate/up 4915 x 4096 x 14336 924 / 919; only from reductions of 8192 on are they ahead
-// (4915 x 8192 x 28672 3594 / 3636).  Read-behind-MFMA there: linear 2458 x 4096 x 4096 107 against 101 us as well.
+// 16 x 16 x 32 MFMAs: a launch over the whole chip is limited by power, and an accumulator tile of 16 x 16 x 32 is read
+// and written half as often per flop as one of 32 x 32 x 16 (linear 8192 x 8192 x 8192 802 -> 761 us with the old order of
+// the loop; where few units work nothing changes).  Wave tiles are 64 x 64 on 128 tokens, 128 x 64 on 256 tokens.
+// LDS holds three weight tiles and two (of 128 tokens: three) token tiles, and the loads of two K steps are in flight.
+// On 256 tokens the slot of a step's token tile becomes free in the middle of the step, behind a barrier of its
+// own, once all waves have its fragments in registers: with the token tile one step ahead instead (and no second
+// barrier) 8192 x 8192 x 8192 takes 737 us against 723, QKV of 4915 rows 184 against 179.  Each barrier has MFMAs of the
+// same wave ahead of it and behind it, so it passes while the matrix core is busy.  Fragment reads and tile loads
+// go out one by one behind the MFMAs (in bursts ahead of each group of 16: 737 us as well).
+// Before, with 32 x 32 x 16 MFMAs / now: QKV 1228 rows 57 / 53 us, 2458 rows 102 / 92, 4915 rows 200 / 183, 32768 rows
+// 1235 / 1145; gate/up of 4915 rows 909 / 856; down projection of 4915 rows (K = 14336) 471 / 433.
+// Not kept: on 128 tokens two wave groups that take one k-step each, with wave tiles of 128 x 64 and the halves added
+// through LDS (a quarter fewer fragment reads; gate/up of 1228 rows 280 -> 288 us: reads from LDS are not the limit,
+// at 128 tokens a step's tiles are 48 bytes per cycle and unit out of L2).
 // Workgroups are numbered so that the ones resident on one XCD (ids congruent mod 8) cover a
 // patch of neighbouring tiles and share their W and X tiles in that XCD's L2.
 #include <string.h>
@@ -50,7 +53,7 @@ constexpr int BK = 64;            // reduction elements per stage
 constexpr int ROWB = BK * 2;      // LDS row in bytes (unpadded, swizzled)
 constexpr int A_BYTES = BF * ROWB;
 constexpr int A_SLOTS = 3;        // LDS slots of weight tiles
-// LDS slots of token tiles of 128 * nb rows; they are loaded b_slots - 1 steps ahead
+// LDS slots of token tiles of 128 * nb rows
 constexpr int b_slots(int nb) { return nb == 1 ? 3 : 2; }
 constexpr int gemm_lds_bytes(int nb) { return A_SLOTS * A_BYTES + b_slots(nb) * 128 * nb * ROWB; }
 
@@ -84,10 +87,21 @@ struct GemmArgs {
 };
 typedef GemmArgs QkvArgs;
 
-__device__ __forceinline__ int32_t position_of_row(const ChunkTable& tab, int32_t r) {
-  int c = 0;
-  while (c + 1 < tab.n && r >= tab.row_start[c + 1]) ++c;
-  return tab.new_start[c] + (r - tab.row_start[c]);
+// Buffer rows -> new positions.  The walk over the chunks is the same for all lanes, so the table comes in scalar
+// loads that do not wait for one another (a walk per lane, one dependent load per chunk and token, held every epilogue up).
+template <int N>
+__device__ __forceinline__ void rows_to_positions(const ChunkTable& tab, int32_t (&r)[N]) {
+  int32_t shift[N];
+#pragma unroll
+  for (int n = 0; n < N; ++n) shift[n] = tab.new_start[0] - tab.row_start[0];
+#pragma unroll 4
+  for (int c = 1; c < tab.n; ++c) {
+    const int32_t start = tab.row_start[c], by = tab.new_start[c] - start;
+#pragma unroll
+    for (int n = 0; n < N; ++n) shift[n] = r[n] >= start ? by : shift[n];
+  }
+#pragma unroll
+  for (int n = 0; n < N; ++n) r[n] += shift[n];
 }
 
 // swizzle of the 16-byte pieces of LDS row r (rows are 128 bytes: two rows per 256-byte bank span)
@@ -117,16 +131,16 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
   constexpr int A_LOADS = BF / 8 / NWAVES;   // wave-wide loads (8 rows each) per wave and stage
   constexpr int BT = 128 * NB;
   constexpr int WF = NB == 1 ? 4 : 2, WT = NWAVES / WF;   // waves along features and tokens
-  constexpr int FM = BF / 32 / WF, TW = BT / 32 / WT; // 32 x 32 MFMA tiles per wave
-  // tile row of feature tile m of wave wf: FM = 4 owns 128 consecutive rows; FM = 2 owns 32 rows and,
-  // where the epilogue pairs rows 64 apart (gate with up, halves of a 128-wide head), the 32 that go with them
+  constexpr int FM = BF / 16 / WF, TW = BT / 16 / WT;   // 16 x 16 MFMA tiles per wave
+  // rows of a wave's feature tiles: 256 tokens 128 consecutive rows; 128 tokens 64 rows or,
+  // where the epilogue pairs rows 64 apart (gate with up, halves of a 128-wide head), 32 and the 32 that go with them
   constexpr bool PAIR64 = EPI == EPI_SWIGLU || (EPI == EPI_QKV_ROPE && D == 128);
   constexpr int B_BYTES = BT * ROWB;
   constexpr int B_LOADS = BT / 8 / NWAVES;
   constexpr int B_SLOTS = b_slots(NB);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, hi = lane >> 5;
+  const int l16 = lane & 15, h = lane >> 4;
 
   // ---- workgroup -> tile, XCD aware (consecutive ids go to different XCDs) ----------------
   const int items = a.v_count * a.k_parts;
@@ -161,6 +175,18 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
     const uint32_t xr = a.hidden_rows ? (uint32_t)a.hidden_rows[t] : (uint32_t)t;
     b_off[j] = (xr * a.E + (((lane & 7) ^ swz(row)) * 8)) * 2;
   }
+  const int wf = wave % WF, wt = wave / WF;
+  const int t0 = wt * 16 * TW + l16;      // the lane's first token of the tile (of TW, 16 apart)
+  // what the rotation in the epilogue needs to know of the lane's tokens, fetched with the row indices
+  [[maybe_unused]] int32_t pos[TW], kv_row[TW];
+  if constexpr (EPI == EPI_QKV_ROPE) {
+#pragma unroll
+    for (int n = 0; n < TW; ++n) {
+      const int t = min(t_blk + t0 + 16 * n, a.n_sel - 1);
+      pos[n] = a.sel_pos ? a.sel_pos[t] : a.sel_idx[t];
+      kv_row[n] = a.kv_rows ? a.kv_rows[t] : t;
+    }
+  }
   typedef __attribute__((address_space(3))) void* lds_ptr_t;
   const uint32_t lds_addr0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
   auto dma16 = [&](const uint16_t* base, uint32_t byte_off, uint32_t lds_addr) __attribute__((always_inline)) {
@@ -185,36 +211,26 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
     for (int j = 0; j < B_LOADS; ++j) issue_b1(k0, slot, j);
   };
 
-  const int wf = wave % WF, wt = wave / WF;
-  const int row0 = FM == 4 ? wf * 128 : PAIR64 ? (wf >> 1) * 128 + (wf & 1) * 32 : wf * 64;
-  constexpr int MROW = FM == 2 && PAIR64 ? 64 : 32;   // rows from one feature tile of the wave to the next
-  // fragment read offsets inside a stage (bytes): row base + swizzled piece, per k-step
-  int a_frag[BK / 16], b_frag[BK / 16];
-#pragma unroll
-  for (int ks = 0; ks < BK / 16; ++ks) {
-    a_frag[ks] = (row0 + l32) * ROWB + (((2 * ks + hi) ^ swz(l32)) * 16);
-    b_frag[ks] = (wt * 32 * TW + l32) * ROWB + (((2 * ks + hi) ^ swz(l32)) * 16);
-  }
+  constexpr bool SPLIT = NB == 1 && PAIR64;
+  const int row0 = NB == 2 ? wf * 128 : SPLIT ? (wf >> 1) * 128 + (wf & 1) * 32 : wf * 64;
+  auto m_row = [](int m) __attribute__((always_inline)) { return SPLIT ? (m >> 1) * 64 + (m & 1) * 16 : m * 16; };
+  // fragment read offsets inside a stage (bytes): row base + swizzled piece; the second k-step's piece is 4 further,
+  // which is an exclusive-or on bits the row term leaves clear
+  const int a_frag = (row0 + l16) * ROWB + ((h ^ swz(l16)) * 16);
+  const int b_frag = (wt * 16 * TW + l16) * ROWB + ((h ^ swz(l16)) * 16);
 
-  f32x16 acc[FM][TW];
+  f32x4 acc[FM][TW];
 #pragma unroll
   for (int m = 0; m < FM; ++m)
 #pragma unroll
-    for (int n = 0; n < TW; ++n)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[m][n][i] = 0.f;
+    for (int n = 0; n < TW; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Pipeline.  The weight tile of K step kt + 2 and the token tile of step kt + 1 are in flight
-  // while step kt is multiplied (all 160 KiB of LDS: 3 + 2 slots of 32 KiB; a 128-token tile leaves room
-  // for a third token slot, and kt + 2 is in flight for both); with one step in
-  // flight the load path alone (issue, L2 latency, barrier) takes as long as the MFMAs of a step.
-  // Loads are issued in the order B(kt + 1), A(kt + 2), so when step kt + 1 is about to start
-  // everything but the newest loads - A(kt + 2), and B(kt + 2) with three slots - is waited for.  Past the end the last
-  // step is loaded again into the free slots, which keeps the number of loads in flight, and the
-  // wait, uniform.
+  // Pipeline.  The tiles of K step kt + 2 are sent for while step kt is multiplied, so the loads of one step may stay in
+  // flight at its end.  Past the end the last step is loaded again into the free slots, which keeps the number of
+  // loads in flight, and the wait, uniform.
   // The workgroup barrier of a step sits ahead of its last MFMA group, not after it: a wave waits
   // for its loads of the next step, meets the others, and the first fragment reads of the
-  // next step go out ahead of that group (or between its MFMAs), so the barrier and the
+  // next step go out between the MFMAs of that group, so the barrier and the
   // LDS latency that follows it pass while the matrix core still has work.  (All waves of
   // a workgroup stand at the barrier together, so the other wave of the SIMD cannot cover it.)
   // this workgroup's part of the reduction: K steps kbeg .. kbeg + nk - 1
@@ -222,143 +238,120 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
   const int kbeg = (int)((long)kp * nk_all / a.k_parts);
   const int nk = (int)((long)(kp + 1) * nk_all / a.k_parts) - kbeg;
   const int kbase = kbeg * BK;
-  constexpr int AHEAD = B_SLOTS == 3 ? A_LOADS + B_LOADS : A_LOADS;   // loads of a step that may stay in flight at its end
+  constexpr int AHEAD = A_LOADS + B_LOADS;                            // loads of a step that may stay in flight at its end
   constexpr int WAIT_STEP = AHEAD | 0x0f70;                           // s_waitcnt vmcnt(AHEAD)
   static_assert(AHEAD < 16, "vmcnt field");
   __builtin_amdgcn_s_waitcnt(0x0f70);   // ordinary loads so far (row indices) are complete
   const int k1 = kbase + min(1, nk - 1) * BK;
   issue_a(kbase, 0);
   issue_b(kbase, 0);
-  if (B_SLOTS == 3) issue_b(k1, 1);
   issue_a(k1, 1);
+  issue_b(k1, 1);
+  if constexpr (EPI == EPI_QKV_ROPE) {
+    if (a.sel_pos == nullptr) rows_to_positions(chunks, pos);   // while the first tiles are on their way
+  }
   int sa = 0, sb = 0;
-  // Two register sets of fragments: those of MFMA group ks + 1 are read while group ks runs.
-  bf16x8 fa[2][FM], fb[2][TW];
-  constexpr int G = FM * TW, R = FM + TW;    // MFMAs and fragment reads of a group
-  constexpr int KG = BK / 16;
-  constexpr int HALF = A_LOADS / 2;
-  auto read_frag = [&](const unsigned char* a_base, const unsigned char* b_base, int ks, int set, int r) __attribute__((always_inline)) {
-    if (r < TW) fb[set][r] = *reinterpret_cast<const bf16x8*>(b_base + b_frag[ks] + r * 32 * ROWB);
-    else fa[set][r - TW] = *reinterpret_cast<const bf16x8*>(a_base + a_frag[ks] + (r - TW) * MROW * ROWB);
+  // Fragments: two register sets of four feature tiles each, two of the four token tiles.
+  bf16x8 fa[2][4], fb[2][TW];
+  auto read_a = [&](const unsigned char* a_base, int ks, int m, int set) __attribute__((always_inline)) {
+    fa[set][m & 3] = *reinterpret_cast<const bf16x8*>(a_base + (a_frag ^ (ks << 6)) + m_row(m) * ROWB);
   };
-  auto mfma = [&](int set, int i) __attribute__((always_inline)) {
-    const int m = i / TW, n = i % TW;
-    acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][m], fb[set][n], acc[m][n], 0, 0, 0);
+  auto read_b = [&](const unsigned char* b_base, int ks, int n, int set) __attribute__((always_inline)) {
+    fb[set][n] = *reinterpret_cast<const bf16x8*>(b_base + (b_frag ^ (ks << 6)) + n * 16 * ROWB);
   };
+  // MFMA i of the 16 on feature tiles m0 .. m0 + 3 of k-step ks; these are in set `aset`, the token tiles in set ks
+  auto mfma = [&](int aset, int ks, int m0, int i) __attribute__((always_inline)) {
+    const int m = m0 + (i >> 2), n = i & 3;
+    acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[aset][i >> 2], fb[ks][n], acc[m][n], 0, 0, 0);
+  };
+  const unsigned char* const b_lds = lds + A_SLOTS * A_BYTES;
   __builtin_amdgcn_s_waitcnt(WAIT_STEP);   // this wave's loads of step 0 have landed
   __syncthreads();                         // everybody's have
 #pragma unroll
-  for (int r = 0; r < R; ++r) read_frag(lds, lds + A_SLOTS * A_BYTES, 0, 0, r);
-  if constexpr (NB == 2) {
-    // The two waves of a SIMD take turns: one sends a group's loads and reads while the other multiplies (one by one
-    // between the MFMAs: QKV of 1638 gathered rows in the layer 94 -> 104 us, of 16384 rows 670 -> 682 us).  This loop
-    // and the one for 128-token tiles stay apart: written as one, with the order chosen by a constant, the compiler
-    // formed the LDS addresses of the loads one from the other and reads of cold weights took 3 to 10 % longer (QKV of
-    // 1638 rows 93 -> 96 us, linear 2458 x 14336 x 4096 287 -> 318 us).
-    auto read_group = [&](const unsigned char* a_base, const unsigned char* b_base, int ks, int set) __attribute__((always_inline)) {
+  for (int r = 0; r < 4; ++r) {
+    read_b(b_lds, 0, r, 0);
+    read_a(lds, 0, r, 0);
+  }
+  for (int kt = 0; kt < nk; ++kt) {
+    const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slot of step kt - 1
+    const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1;
+    const int sb_next = sb == B_SLOTS - 1 ? 0 : sb + 1;
+    const unsigned char *a_base = lds + sa * A_BYTES, *a_next = lds + sa_next * A_BYTES;
+    const unsigned char *b_base = b_lds + sb * B_BYTES, *b_next = b_lds + sb_next * B_BYTES;
+    const int k2 = kbase + min(kt + 2, nk - 1) * BK;
+    if constexpr (NB == 2) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) read_frag(a_base, b_base, ks, set, r);
-    };
-    auto mfma_group = [&](int set) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < G; ++i) mfma(set, i);
-    };
-    for (int kt = 0; kt < nk; ++kt) {
-      const unsigned char* a_base = lds + sa * A_BYTES;
-      const unsigned char* b_base = lds + A_SLOTS * A_BYTES + sb * B_BYTES;
-      const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slot of step kt - 1
-      const int sb_free = sb ^ 1;
-      const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1;
-      const int kb1 = kbase + min(kt + 1, nk - 1) * BK, ka2 = kbase + min(kt + 2, nk - 1) * BK;
-#pragma unroll
-      for (int ks = 0; ks < KG - 1; ++ks) {
-        if (ks == 0) issue_b(kb1, sb_free);     // B first: it is needed a step earlier
-#pragma unroll
-        for (int j = 0; j < HALF; ++j)
-          if (ks > 0) issue_a1(ka2, sa_free, (ks - 1) * HALF + j);
-        read_group(a_base, b_base, ks + 1, (ks + 1) & 1);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_group(ks & 1);
+      for (int i = 0; i < 16; ++i) {
+        mfma(0, 0, 0, i);
+        if (i < 4) read_a(a_base, 0, 4 + i, 1);
+        else if (i < 8) read_b(b_base, 1, i - 4, 1);
+        else if (i % 2 == 0) issue_a1(k2, sa_free, (i - 8) / 2);
         __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // vmcnt(AHEAD): this wave's loads of step kt + 1 have
-                                                          // landed; lgkmcnt(0): its fragment reads of step kt are done
-      __syncthreads();                         // everybody's have; everybody is done reading step kt
-      read_group(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_free * B_BYTES, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_group((KG - 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);
-      sa = sa_next;
-      sb = sb_free;
+      __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0): this wave has read all of the token tile
+      __syncthreads();                         // everybody has: its slot is free for step kt + 2
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        mfma(1, 0, 4, i);
+        if (i < 4) read_a(a_base, 1, i, 0);
+        else if (i == 4 || i == 8) issue_b1(k2, sb, (i - 4) / 4);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        mfma(0, 1, 0, i);
+        if (i < 4) read_a(a_base, 1, 4 + i, 1);
+        else if (i == 4 || i == 8) issue_b1(k2, sb, 2 + (i - 4) / 4);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      const int sb_free = sb == 0 ? B_SLOTS - 1 : sb - 1;   // slot of step kt - 1
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        mfma(0, 0, 0, i);
+        if (i < B_LOADS) issue_b1(k2, sb_free, i);
+        else if (i < B_LOADS + A_LOADS) issue_a1(k2, sa_free, i - B_LOADS);
+        if (i < 4) read_b(b_base, 1, i, 1);
+        else if (i < 8) read_a(a_base, 1, i - 4, 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-  } else {
-    // a read behind each MFMA, and the tile loads between them, so that no burst of memory instructions holds up
-    // the matrix core of a wave
-    static_assert(R <= G && HALF <= G && B_LOADS <= G, "a read and a load behind every MFMA");
-    for (int kt = 0; kt < nk; ++kt) {
-      const unsigned char* a_base = lds + sa * A_BYTES;
-      const unsigned char* b_base = lds + A_SLOTS * A_BYTES + sb * B_BYTES;
-      const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slots of step kt - 1
-      const int sb_free = sb == 0 ? B_SLOTS - 1 : sb - 1;
-      const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1, sb_next = sb == B_SLOTS - 1 ? 0 : sb + 1;
-      const int kb1 = kbase + min(kt + B_SLOTS - 1, nk - 1) * BK, ka2 = kbase + min(kt + 2, nk - 1) * BK;
+    __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // vmcnt(AHEAD): this wave's loads of step kt + 1 have
+                                                        // landed; lgkmcnt(0): its fragment reads of step kt are done
+    __syncthreads();                           // everybody's have; everybody is done reading step kt
 #pragma unroll
-      for (int ks = 0; ks < KG - 1; ++ks) {
-#pragma unroll
-        for (int i = 0; i < G; ++i) {
-          mfma(ks & 1, i);
-          if (i < R) read_frag(a_base, b_base, ks + 1, (ks + 1) & 1, i);
-          if (ks == 0 && i < B_LOADS) issue_b1(kb1, sb_free, i);     // B first: it is needed a step earlier
-          if (ks > 0 && i < HALF) issue_a1(ka2, sa_free, (ks - 1) * HALF + i);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // as above
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < G; ++i) {
-        mfma((KG - 1) & 1, i);
-        if (i < R) read_frag(lds + sa_next * A_BYTES, lds + A_SLOTS * A_BYTES + sb_next * B_BYTES, 0, 0, i);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      sa = sa_next;
-      sb = sb_next;
+    for (int i = 0; i < 16; ++i) {
+      mfma(1, 1, FM - 4, i);
+      if (i < 4) read_b(b_next, 0, i, 0);
+      else if (i < 8) read_a(a_next, 0, i - 4, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    sa = sa_next;
+    sb = sb_next;
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);   // the repeated loads of the last steps have landed before the LDS is released
 
   // ---- epilogues ---------------------------------------------------------------------------------
-  // accumulator element i of tile (m, n): row f0 + m*32 + 8*(i/4) + 4*hi + i%4, token = column l32
-  // In an accumulator tile the lanes l and l + 32 hold features 8g + 0..3 and 8g + 4..7 of one
-  // token (g = 0..3).  v_permlane32_swap between the packed results of groups 2q and 2q + 1 gives
-  // lane l all eight features of group 2q and lane l + 32 those of group 2q + 1, so a tile leaves as
-  // two 16-byte stores per lane instead of four 8-byte ones.  `p` points at the token's row at the
-  // tile's first feature.  Every lane of the wave must come here (the swap crosses the two halves
-  // of the wave); `ok` gates the store alone.
-  auto store_tile = [&](uint16_t* p, const f32x16& c, bool ok) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int g0 = 8 * q, g1 = 8 * q + 4;
-      const auto x0 = __builtin_amdgcn_permlane32_swap(pack_bf16(c[g0], c[g0 + 1]), pack_bf16(c[g1], c[g1 + 1]), false, false);
-      const auto x1 = __builtin_amdgcn_permlane32_swap(pack_bf16(c[g0 + 2], c[g0 + 3]), pack_bf16(c[g1 + 2], c[g1 + 3]), false, false);
-      const u32x4 out16 = {x0[0], x1[0], x0[1], x1[1]};
-      if (ok) *reinterpret_cast<u32x4*>(p + 16 * q + 8 * hi) = out16;
-    }
+  // accumulator element i of tile (m, n): feature m_row(m) + 4 h + i, token l16 (h: the lane's row of 16 lanes).
+  // The packed results of tiles m and m + 1 (features 0 .. 31 of a run of 32) are exchanged between odd and even rows of
+  // lanes (v_permlane16_swap), which gives each lane eight features of its token from feature
+  // 16 (h & 1) + 8 (h >> 1) of the run on: one 16-byte store for two tiles.  `p` points at the token's row at the run's
+  // first feature.  Every lane of the wave must come here; `ok` gates the store alone.
+  const int f8 = 16 * (h & 1) + 8 * (h >> 1);
+  auto store_run = [&](uint16_t* p, const f32x4& x, const f32x4& y, bool ok) __attribute__((always_inline)) {
+    const auto w0 = __builtin_amdgcn_permlane16_swap(pack_bf16(x[0], x[1]), pack_bf16(y[0], y[1]), false, false);
+    const auto w1 = __builtin_amdgcn_permlane16_swap(pack_bf16(x[2], x[3]), pack_bf16(y[2], y[3]), false, false);
+    const u32x4 out16 = {w0[0], w1[0], w0[1], w1[1]};
+    if (ok) *reinterpret_cast<u32x4*>(p + f8) = out16;
   };
   if constexpr (EPI == EPI_PARTIAL) {
     // fp32 partial sums of this part of the reduction, token major inside the tile, 16-byte stores
     float* dst = a.partial + (size_t)item * (BT * BF);
 #pragma unroll
-    for (int n = 0; n < TW; ++n) {
-      const int tl = wt * 32 * TW + n * 32 + l32;
+    for (int n = 0; n < TW; ++n)
 #pragma unroll
       for (int m = 0; m < FM; ++m)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 w = {acc[m][n][4 * g + 0], acc[m][n][4 * g + 1], acc[m][n][4 * g + 2], acc[m][n][4 * g + 3]};
-          *reinterpret_cast<f32x4*>(dst + (size_t)tl * BF + row0 + m * MROW + 8 * g + 4 * hi) = w;
-        }
-    }
+        *reinterpret_cast<f32x4*>(dst + (size_t)(t0 + 16 * n) * BF + row0 + m_row(m) + 4 * h) = acc[m][n];
     return;
   } else if constexpr (EPI == EPI_LINEAR) {
     const int f0 = f_blk + row0;
@@ -367,46 +360,39 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
     // the first result is stored: `out` may be the residual buffer itself, so the compiler cannot
     // move these loads above stores on its own, and with few loads in flight per lane the epilogue
     // is bound by memory latency.
-    u32x4 res[TW][FM][2];
+    u32x4 res[TW][FM / 2];
     if (a.residual != nullptr) {
 #pragma unroll
       for (int n = 0; n < TW; ++n) {
-        const int t = min(t_blk + wt * 32 * TW + n * 32 + l32, a.n_sel - 1);
+        const int t = min(t_blk + t0 + 16 * n, a.n_sel - 1);
 #pragma unroll
-        for (int m = 0; m < FM; ++m) {
-          const int fm = min(f0 + m * MROW, a.O - 32);
-          const size_t row = (size_t)t * a.O + fm + 8 * hi;
-#pragma unroll
-          for (int q = 0; q < 2; ++q) res[n][m][q] = *reinterpret_cast<const u32x4*>(a.residual + row + 16 * q);
+        for (int m = 0; m < FM; m += 2) {
+          const int fm = min(f0 + m_row(m), a.O - 32);
+          res[n][m / 2] = *reinterpret_cast<const u32x4*>(a.residual + (size_t)t * a.O + fm + f8);
         }
       }
     }
 #pragma unroll
     for (int n = 0; n < TW; ++n) {
-      const int t = t_blk + wt * 32 * TW + n * 32 + l32;
+      const int t = t_blk + t0 + 16 * n;
       const bool t_ok = t < a.n_sel;
 #pragma unroll
-      for (int m = 0; m < FM; ++m) {
-        const int fm = f0 + m * MROW;
+      for (int m = 0; m < FM; m += 2) {
+        const int fm = f0 + m_row(m);
         if (fm >= a.O) continue;            // uniform for the wave
         if (a.residual != nullptr) {
+          const u32x4 r = res[n][m / 2];
+          const auto d0 = __builtin_amdgcn_permlane16_swap(r[0], r[2], false, false);   // dword 0 of tiles m, m + 1
+          const auto d1 = __builtin_amdgcn_permlane16_swap(r[1], r[3], false, false);   // dword 1
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            // r[0], r[1]: features +0..3 of the lane's eight, r[2], r[3]: +4..7
-            const u32x4 r = res[n][m][q];
-            const auto d0 = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);   // dword 0 of groups 2q, 2q + 1
-            const auto d1 = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);   // dword 1
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              const int i0 = 4 * (2 * q + e);
-              acc[m][n][i0 + 0] += bf16_lo(d0[e]);
-              acc[m][n][i0 + 1] += bf16_hi(d0[e]);
-              acc[m][n][i0 + 2] += bf16_lo(d1[e]);
-              acc[m][n][i0 + 3] += bf16_hi(d1[e]);
-            }
+          for (int e = 0; e < 2; ++e) {
+            acc[m + e][n][0] += bf16_lo(d0[e]);
+            acc[m + e][n][1] += bf16_hi(d0[e]);
+            acc[m + e][n][2] += bf16_lo(d1[e]);
+            acc[m + e][n][3] += bf16_hi(d1[e]);
           }
         }
-        store_tile(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, acc[m][n], t_ok);
+        store_run(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, acc[m][n], acc[m + 1][n], t_ok);
       }
     }
     return;
@@ -414,58 +400,56 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
     const int f0 = f_blk + (row0 >> 7) * 64 + (row0 & 63);   // first output feature of this wave
 #pragma unroll
     for (int n = 0; n < TW; ++n) {
-      const int t = t_blk + wt * 32 * TW + n * 32 + l32;
+      const int t = t_blk + t0 + 16 * n;
       const bool t_ok = t < a.n_sel;
 #pragma unroll
-      for (int m = 0; m < FM / 2; ++m) {     // gate tile m, up tile m + FM / 2
-        const int fm = f0 + m * 32;
+      for (int m = 0; m < FM / 2; m += 2) {     // gate tile m, up tile m + FM / 2
+        const int fm = f0 + m * 16;
         if (fm >= a.O) continue;             // uniform for the wave
-        f32x16 y;
+        f32x4 y[2];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float gate = acc[m][n][i], up = acc[m + FM / 2][n][i];
-          y[i] = gate / (1.0f + __builtin_amdgcn_exp2f(-gate * 1.4426950408889634f)) * up;   // silu(gate) * up
-        }
-        store_tile(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, y, t_ok);
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float gate = acc[m + e][n][i], up = acc[m + e + FM / 2][n][i];
+            y[e][i] = gate / (1.0f + __builtin_amdgcn_exp2f(-gate * 1.4426950408889634f)) * up;   // silu(gate) * up
+          }
+        store_run(a.out + (size_t)(t_ok ? t : 0) * a.O + fm, y[0], y[1], t_ok);
       }
     }
     return;
   } else {
-    // accumulator element i of tile (m, n): feature f0 + m*MROW + 8*(i/4) + 4*hi + i%4, token = column l32
     const int f0 = f_blk + row0;
     const int rope_end = (a.Hq + a.Hkv) * D;   // features below this are q or k heads
     const int q_end = a.Hq * D;
   #pragma unroll
     for (int n = 0; n < TW; ++n) {
-      const int t = t_blk + wt * 32 * TW + n * 32 + l32;
+      const int t = t_blk + t0 + 16 * n;
       const bool t_ok = t < a.n_sel;
       const int tc = t_ok ? t : a.n_sel - 1;
-      const int32_t pos = a.sel_pos ? a.sel_pos[tc] : position_of_row(chunks, a.sel_idx[tc]);
-      const int32_t kv_row = a.kv_rows ? a.kv_rows[tc] : tc;
-
       if (a.bias != nullptr) {
   #pragma unroll
         for (int m = 0; m < FM; ++m)
   #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int f = min(f0 + m * MROW + 8 * (i >> 2) + 4 * hi + (i & 3), a.O - 1);
+          for (int i = 0; i < 4; ++i) {
+            const int f = min(f0 + m_row(m) + 4 * h + i, a.O - 1);
             acc[m][n][i] += bf16_lo((uint32_t)a.bias[f]);
           }
       }
 
       if (STYLE == 0) {
         // pairs (j, j + D/2), D/2 rows apart
-        constexpr int STEP = D / 2 / MROW;    // tile distance between the two halves of a pair
+        constexpr int STEP = SPLIT ? 2 : D / 32;    // tile distance between the two halves of a pair
   #pragma unroll
         for (int m = 0; m < FM; ++m) {
           if (m & STEP) continue;
-          const int fa0 = f0 + m * MROW;        // first feature of the "a" half tile
+          const int fa0 = f0 + m_row(m);        // first feature of the "a" half tile
           if (fa0 >= rope_end) continue;      // v heads are not rotated
   #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int j = (fa0 % D) + 8 * (i >> 2) + 4 * hi + (i & 3);
+          for (int i = 0; i < 4; ++i) {
+            const int j = (fa0 % D) + 4 * h + i;
             float c, s;
-            sincos_turns(pos, rope.turns[j], c, s);
+            sincos_turns(pos[n], rope.turns[j], c, s);
             const float x = acc[m][n][i], y = acc[m + STEP][n][i];
             acc[m][n][i] = x * c - y * s;
             acc[m + STEP][n][i] = x * s + y * c;
@@ -474,13 +458,13 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
       } else {
   #pragma unroll
         for (int m = 0; m < FM; ++m) {
-          const int fa0 = f0 + m * MROW;
+          const int fa0 = f0 + m_row(m);
           if (fa0 >= rope_end) continue;
   #pragma unroll
-          for (int i = 0; i < 16; i += 2) {
-            const int j = ((fa0 % D) + 8 * (i >> 2) + 4 * hi + (i & 3)) >> 1;
+          for (int i = 0; i < 4; i += 2) {
+            const int j = ((fa0 % D) + 4 * h + i) >> 1;
             float c, s;
-            sincos_turns(pos, rope.turns[j], c, s);
+            sincos_turns(pos[n], rope.turns[j], c, s);
             const float x = acc[m][n][i], y = acc[m][n][i + 1];
             acc[m][n][i] = x * c - y * s;
             acc[m][n][i + 1] = x * s + y * c;
@@ -489,17 +473,17 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
       }
 
   #pragma unroll
-      for (int m = 0; m < FM; ++m) {
-        const int fm = f0 + m * MROW;
+      for (int m = 0; m < FM; m += 2) {
+        const int fm = f0 + m_row(m);
         if (fm >= a.O) continue;             // uniform for the wave
         uint16_t* dst;
         if (fm < q_end)
           dst = a.q_out + (size_t)tc * q_end + fm;
         else if (fm < rope_end)
-          dst = a.k_out + (size_t)kv_row * (a.Hkv * D) + (fm - q_end);
+          dst = a.k_out + (size_t)kv_row[n] * (a.Hkv * D) + (fm - q_end);
         else
-          dst = a.v_out + (size_t)kv_row * (a.Hkv * D) + (fm - rope_end);
-        store_tile(dst, acc[m][n], t_ok);
+          dst = a.v_out + (size_t)kv_row[n] * (a.Hkv * D) + (fm - rope_end);
+        store_run(dst, acc[m][n], acc[m + 1][n], t_ok);
       }
     }
   }
