@@ -114,48 +114,94 @@ __device__ __forceinline__ int count_below(const int32_t* __restrict__ list, int
   }
   return lo;
 }
-// The rows of one workgroup lie next to each other: one search for the workgroup's first row
-// (the same for every thread, so its loads are scalar), then a walk over the few entries up to
-// this thread's row.  Rows far from the first one (a gap between chunks) search on their own.
-__device__ __forceinline__ int count_below_near(const int32_t* __restrict__ list, int n, int32_t first_row,
-                                                int first_below, int32_t row) {
-  if (row < first_row || row - first_row > 512) return count_below(list, n, row);
-  int i = first_below;
-  while (i < n && list[i] < row) ++i;
-  return i;
+// The rows of one wave lie next to each other: the whole wave searches the list for its first row, 64 probes at a time
+// (two or three rounds of loads instead of one per bit), and takes the entries from there on into a register each, where every lane
+// compares its own row with them.  Rows far from the first one (a gap between chunks) search on their own.
+// With one search by halves per workgroup and a walk over the entries in memory per thread, and a walk over the chunk table
+// with a load per chunk, 6964 of 8192 rows (8 heads of 128, 8 chunks) took 15.7 us.
+struct SkipWindow {
+  int32_t first_row;
+  int below, n_near;   // entries below first_row; entries in [first_row, first_row + rows)
+  int32_t entry;       // this lane's entry: number `below + lane` of the list
+};
+// All lanes of the wave must come here with the same first_row.
+__device__ __forceinline__ SkipWindow skip_window(const int32_t* __restrict__ list, int n, int32_t first_row, int rows) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, len = n;
+  while (len > 0) {
+    const int step = (len + 63) >> 6, at = lane * step + step - 1;   // the last entry of this lane's block
+    const bool block_below = at < len && list[lo + at] < first_row;
+    const int k = __popcll(__ballot(block_below));                   // the blocks 0 .. k - 1 lie below the row
+    lo += k * step;
+    len = min(step - 1, len - k * step);
+  }
+  SkipWindow w;
+  w.first_row = first_row;
+  w.below = lo;
+  w.entry = lo + lane < n ? list[lo + lane] : 0x7fffffff;
+  w.n_near = __popcll(__ballot(w.entry < first_row + rows));
+  return w;
+}
+// Number of listed rows < row, and whether the row itself is listed.
+__device__ __forceinline__ int find_near(const SkipWindow& w, const int32_t* __restrict__ list, int n, int32_t row, int rows, bool* listed) {
+  int below = w.below;
+  bool hit = false;
+  for (int i = 0; i < w.n_near; ++i) {
+    const int32_t e = __builtin_amdgcn_readlane(w.entry, i);
+    below += e < row;
+    hit |= e == row;
+  }
+  if (row < w.first_row || row - w.first_row >= rows) {
+    below = count_below(list, n, row);
+    hit = below < n && list[below] == row;
+  }
+  *listed = hit;
+  return below;
+}
+
+// Chunk of token t: the same walk for all lanes, scalar loads that do not wait for one another.
+// (Token numbers stay below 2^24, the limit of the layer buffers' rows.)
+__device__ __forceinline__ int chunk_of(const ReropeChunks& chunks, int32_t t) {
+  int c = 0;
+#pragma unroll 4
+  for (int i = 1; i < chunks.n; ++i) c += t >= (int32_t)chunks.tok_start[i];
+  return c;
 }
 
 // Several chunks in one launch: buffer row -> chunk by search in the (small) table.  The work of workgroup
 // `block` of `n_blocks`.
-// NEAR: the grid covers every token once, so a workgroup's rows are neighbours and share one search
+// NEAR: the grid covers every token once, so a wave's rows are neighbours and share one search
 // of the skip list; otherwise (few workgroups striding over the tokens) every token searches.
 template <int D, int STYLE, int HEADS, bool NEAR>
 __device__ __forceinline__ void rerope_chunk_tokens(uint16_t* k_buf, uint16_t* v_buf, int32_t n_heads_rt,
                                                     const RopeTable& table, const ReropeChunks& chunks, int threads,
                                                     uint32_t block, uint32_t n_blocks) {
   constexpr int GROUPS = D / 16;
+  constexpr int WAVE_ROWS = 64 / GROUPS;
   const int64_t gid = (int64_t)block * threads + threadIdx.x;
   const int jg = (int)(gid % GROUPS);
   const int64_t t_step = (int64_t)n_blocks * (threads / GROUPS);
-  int32_t first_row = 0;
-  int first_below = 0;
+  SkipWindow near = {};
   if (NEAR && chunks.skip_rows != nullptr) {
-    const int64_t t0 = (int64_t)block * (threads / GROUPS);   // the workgroup's first token
-    int c0 = 0;
-    while (c0 + 1 < chunks.n && t0 >= chunks.tok_start[c0 + 1]) ++c0;
-    first_row = chunks.row_start[c0] + (int32_t)(t0 - chunks.tok_start[c0]);
-    first_below = count_below(chunks.skip_rows, chunks.n_skip, first_row);
+    const int32_t t0 = __builtin_amdgcn_readfirstlane((int32_t)(gid / GROUPS));   // the wave's first token
+    const int c0 = __builtin_amdgcn_readfirstlane(chunk_of(chunks, t0));
+    near = skip_window(chunks.skip_rows, chunks.n_skip, chunks.row_start[c0] + (t0 - (int32_t)chunks.tok_start[c0]), WAVE_ROWS);
   }
   for (int64_t t_all = gid / GROUPS; t_all < chunks.total_tokens; t_all += t_step) {   // ordinal among the listed tokens
-    int c = 0;
-    while (c + 1 < chunks.n && t_all >= chunks.tok_start[c + 1]) ++c;
+    const int c = chunk_of(chunks, (int32_t)t_all);
     const int32_t t = (int32_t)(t_all - chunks.tok_start[c]);
     int32_t t_src = t;   // row inside the chunk's source
     if (chunks.skip_rows != nullptr) {   // is this buffer row in the sorted skip list?
       const int32_t row = chunks.row_start[c] + t;
-      const int lo = NEAR ? count_below_near(chunks.skip_rows, chunks.n_skip, first_row, first_below, row)
-                          : count_below(chunks.skip_rows, chunks.n_skip, row);
-      if (lo < chunks.n_skip && chunks.skip_rows[lo] == row) continue;
+      bool listed;
+      int lo;
+      if (NEAR) {
+        lo = find_near(near, chunks.skip_rows, chunks.n_skip, row, WAVE_ROWS, &listed);
+      } else {
+        lo = count_below(chunks.skip_rows, chunks.n_skip, row);
+        listed = lo < chunks.n_skip && chunks.skip_rows[lo] == row;
+      }
+      if (listed) continue;
       // a compact source holds only the rows that are kept: step over the skipped ones before this row
       if ((chunks.compact_mask >> c) & 1u) t_src = t - (lo - count_below(chunks.skip_rows, chunks.n_skip, chunks.row_start[c]));
     }

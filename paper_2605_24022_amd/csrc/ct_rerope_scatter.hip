@@ -24,12 +24,14 @@ __global__ __launch_bounds__(kReropeThreads) void rerope_kernel(
   const int64_t gid = (int64_t)blockIdx.x * kReropeThreads + threadIdx.x;
   const int64_t token = gid / GROUPS;
   const int jg = (int)(gid % GROUPS);
-  if (token >= n_tokens) return;
+  bool listed = false;
   if (skip_rows != nullptr) {
-    const int32_t first = (int32_t)((int64_t)blockIdx.x * (kReropeThreads / GROUPS));
-    const int at = count_below_near(skip_rows, n_skip, first, count_below(skip_rows, n_skip, first), (int32_t)token);
-    if (at < n_skip && skip_rows[at] == (int32_t)token) return;
+    constexpr int WAVE_ROWS = 64 / GROUPS;
+    const int32_t first = __builtin_amdgcn_readfirstlane((int32_t)token);
+    const SkipWindow near = skip_window(skip_rows, n_skip, first, WAVE_ROWS);
+    find_near(near, skip_rows, n_skip, (int32_t)token, WAVE_ROWS, &listed);
   }
+  if (token >= n_tokens || listed) return;
   int32_t delta;
   if (new_pos != nullptr) {
     delta = new_pos[token] - (old_pos != nullptr ? old_pos[token] : 0);
