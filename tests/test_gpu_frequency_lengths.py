@@ -37,3 +37,12 @@ def test_scores_against_fp64(n, row, n_batch, alpha):
     # roundings of 2^-24, about 4 log2(n) <= 68 of them deep, relative to the largest score
     err = float((scores.double() - want).abs().max())
     assert torch.isfinite(scores).all() and err <= 4.1e-6 * max(float(want.max()), 1e-30), err
+
+
+@pytest.mark.parametrize("n", [256, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("row,n_batch", [(128, 1), (1024, 4), (384, 3)])
+def test_power_of_two_lengths_around_half_the_spectrum(n, row, n_batch):
+    """Cutoffs at and on both sides of N / 4 (where half of the last pass is left out), strips of one and several
+    rounds, sequences that fill whole XCDs and not."""
+    for cutoff in (1, n // 8 + 1, n // 4 - 1, n // 4, n // 4 + 1, n // 2):
+        test_scores_against_fp64(n, row, n_batch, (cutoff + 0.5) / (n // 2 + 1))
