@@ -883,7 +883,7 @@ __global__ __launch_bounds__(kFreqThreads) void freq_mixed_kernel(const uint16_t
     const uint32_t* src = reinterpret_cast<const uint32_t*>(((tensor & 1) ? v : k) + (int64_t)(tensor >> 1) * batch_stride) + ((int64_t)strip << p.lg_cp);
     by_radix(p.r0, [&](auto r) __attribute__((always_inline)) {
       mix_first<decltype(r)::value, T>(data, tw, p, [&](int, int row, int c) __attribute__((always_inline)) {
-        const uint32_t pair = __builtin_nontemporal_load(src + (int64_t)row * width + c);
+        const uint32_t pair = src[(int64_t)row * width + c];
         return make_float2(bf16_lo(pair), bf16_hi(pair));
       });
     });
@@ -1096,10 +1096,11 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 // One workgroup per sequence; scores stay in L2, so what counts is the chain of loads, atomics and barriers: loads
 // go out kTopkBatch at a time, scores that share the first byte (nearly all do) are added by one lane, and each
 // wave sweeps a stretch of its own without barriers.  15 % of 32768 scores: 92 -> 38 us, of 4 x 1500 8.4 -> 7.2 us.
-// SHORT: up to one score per thread, which stays in a register through all passes: 15 % of 512 scores 8.4 -> 6.6 us, of 300 x 1024
-// 10.2 -> 7.6 us (batches of loads again and again took longer there than single loads had: 7.8 and 10.1 us).
+// KEYS > 0: up to KEYS scores per thread, which stay in registers through all passes (wave w holds the stretch it sweeps): 15 % of 512
+// scores 8.4 -> 6.6 us, of 300 x 1024 10.2 -> 7.6 us, of 4 x 1500 6.8 -> 5.0, of 16384 20.7 -> 14.0,
+// of 32768 37 -> 25; beyond that there are not registers enough.
 constexpr int kTopkBatch = 8;
-template <bool SHORT>
+template <int KEYS>
 __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ scores, int32_t n_tokens, int32_t k,
                                                     int32_t* __restrict__ idx_out) {
   __shared__ uint32_t hist[256];
@@ -1110,7 +1111,16 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const uint32_t n = n_tokens;     // (unsigned: positions run past the end by up to a batch)
   if (k <= 0) return;
-  const uint32_t own_key = SHORT && (uint32_t)tid < n ? score_key(s[tid]) : 0u;
+  uint32_t own[KEYS > 0 ? KEYS : 1];
+  const uint32_t own0 = KEYS > 0 ? wv * (KEYS * 64) + lane : 0;      // token of own[0], the others 64 apart
+#pragma unroll
+  for (int b = 0; b < KEYS; ++b) own[b] = own0 + b * 64 < n ? score_key(s[own0 + b * 64]) : 0u;
+  // n, opaque (and the threshold below): compared again in each pass instead of results being kept, two scalar registers per key
+  auto count_of = [&]() __attribute__((always_inline)) {
+    uint32_t m = n;
+    asm volatile("" : "+s"(m));
+    return m;
+  };
   // radix select, most significant byte first: after the loop `prefix` is the key of the k-th
   // largest score and `need` the number of tokens with exactly that key that are still taken
   uint32_t prefix = 0, need = (uint32_t)k;
@@ -1134,8 +1144,23 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
       }
       if (left) atomicAdd(&hist[bin], 1u);
     };
-    if constexpr (SHORT) {
-      count(own_key, (uint32_t)tid < n);
+    if constexpr (KEYS > 0) {
+      const uint32_t n = count_of();
+      if (KEYS > 1 && shift == 24) {
+        // one bin per wave is counted in a register: that of its first token
+        const uint32_t common = (uint32_t)__builtin_amdgcn_readfirstlane((int)(own[0] >> 24));
+        uint32_t same = 0;
+#pragma unroll
+        for (int b = 0; b < KEYS; ++b) {
+          const bool in = own0 + b * 64 < n;
+          same += __popcll(__ballot(in && (own[b] >> 24) == common));
+          if (in && (own[b] >> 24) != common) atomicAdd(&hist[own[b] >> 24], 1u);
+        }
+        if (lane == 0 && same > 0) atomicAdd(&hist[common], same);
+      } else {
+#pragma unroll
+        for (int b = 0; b < KEYS; ++b) count(own[b], own0 + b * 64 < n);
+      }
     } else {
       for (uint32_t i0 = tid; i0 - tid < n; i0 += 1024 * kTopkBatch) {
         float x[kTopkBatch];
@@ -1181,8 +1206,15 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
   // stretch of tokens; it counts both kinds, and what the waves before it hold says where it writes.
   const uint32_t stretch = (n + 1023) / 1024 * 64, begin = wv * stretch, end = min(n, begin + stretch);
   auto sweep = [&](auto&& body) __attribute__((always_inline)) {
-    if constexpr (SHORT) {     // (wave w's stretch of 64 is what its threads hold)
-      body((uint32_t)tid, (uint32_t)tid < n && own_key > prefix, (uint32_t)tid < n && own_key == prefix);
+    if constexpr (KEYS > 0) {
+      const uint32_t n = count_of();
+      uint32_t limit = prefix;
+      asm volatile("" : "+v"(limit));
+#pragma unroll
+      for (int b = 0; b < KEYS; ++b) {
+        const uint32_t i = own0 + b * 64;
+        body(i, i < n && own[b] > limit, i < n && own[b] == limit);
+      }
       return;
     }
     for (uint32_t i0 = begin; i0 < end; i0 += 64 * kTopkBatch) {
@@ -1442,7 +1474,9 @@ ct_status ct_topk_indices(const float* scores, int32_t n_batch, int32_t n_tokens
   if (n_batch == 0 || k == 0) return CT_OK;
   if (scores == nullptr || idx_out == nullptr) return fail(CT_ERR_NULL, "scores and idx_out must be non-NULL");
   hipStream_t s = (hipStream_t)stream;
-  launch_kernel(KC_TOPK, n_tokens <= 1024 ? topk_kernel<true> : topk_kernel<false>, dim3(n_batch), dim3(1024), 0, s, scores,
+  auto kern = n_tokens <= 1024 ? topk_kernel<1> : n_tokens <= 2048 ? topk_kernel<2> : n_tokens <= 4096 ? topk_kernel<4>
+            : n_tokens <= 8192 ? topk_kernel<8> : n_tokens <= 16384 ? topk_kernel<16> : n_tokens <= 32768 ? topk_kernel<32> : topk_kernel<0>;
+  launch_kernel(KC_TOPK, kern, dim3(n_batch), dim3(1024), 0, s, scores,
                 n_tokens, k, idx_out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "topk launch");
