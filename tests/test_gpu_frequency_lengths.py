@@ -46,3 +46,17 @@ def test_power_of_two_lengths_around_half_the_spectrum(n, row, n_batch):
     rounds, sequences that fill whole XCDs and not."""
     for cutoff in (1, n // 8 + 1, n // 4 - 1, n // 4, n // 4 + 1, n // 2):
         test_scores_against_fp64(n, row, n_batch, (cutoff + 0.5) / (n // 2 + 1))
+
+
+@pytest.mark.parametrize("n", [1023, 1025, 2047, 2048, 2049, 4096, 4097, 8191, 8193, 16384, 16385, 32767, 32768, 32769])
+@pytest.mark.parametrize("levels", [3, 1 << 20])
+def test_topk_where_scores_per_thread_change(n, levels):
+    """Both sides of every number of scores that a thread holds, with many ties and with few, of either sign."""
+    say(f"topk n={n} levels={levels}")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    scores = (torch.randint(0, levels, (3, n), generator=g, device="cuda") - levels // 2).float() / levels
+    order = torch.sort(scores.cpu(), dim=1, descending=True, stable=True).indices
+    for k in (1, n // 7, n):
+        idx = torch.full((3, k), -1, dtype=torch.int32, device="cuda")
+        B.ct_topk_indices(scores, 3, n, k, idx)
+        assert torch.equal(idx.cpu().long(), order[:, :k].sort(dim=1).values)
