@@ -387,7 +387,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
       const float m_use = m_run[n] == -INFINITY ? 0.f : m_run[n];
-      float rs0 = l_run[n], rs1 = 0.f;
+      float rs0 = 0.f, rs1 = 0.f;   // of this tile alone: added to the running sum once, not probability by probability
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -396,10 +396,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][n][i + 1], a.scale_log2, -m_use));
           s[u][n][i] = p0;
           s[u][n][i + 1] = p1;
-          rs0 += p0;
+          rs0 = u + i == 0 ? p0 : rs0 + p0;
           rs1 = u + i == 0 ? p1 : rs1 + p1;
         }
-      l_run[n] = rs0 + rs1;
+      l_run[n] += rs0 + rs1;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         u32x4 w;
