@@ -147,6 +147,11 @@ __device__ __forceinline__ void dft<16>(float2 (&v)[16], float sgn) { dft_by4<4>
 // No cache hint on the loads: with the streaming one, neighbouring strips find less of a shared line (the
 // loads alone 122 us against 71).
 // Bound by vector instructions (110 us) and LDS accesses (60 us), which overlap in part.
+// A quarter turn has no tangent: its cosine is taken as 2^-28, off by a sixteenth of the rounding of a term.  So that 2^28 times
+// a bin stays finite wherever the bin does, kept or not, the transforms run on 2^-32 of the data, and the last
+// sums scale up.  (That loses values below 2^-94; squares are lost from 2^-75 on.)  1 % of the launch.
+constexpr float kDown = 0x1p-32f, kUp = 0x1p32f;
+__device__ __forceinline__ float2 scaled(float2 a, float by) { return make_float2(by * a.x, by * a.y); }
 // e^(i x), e^(2 i x) and e^(3 i x) as tangents and cosines; r = cos 3x / cos x
 struct Tw4 {
   float t1, c1, t2, c2, t3, r;
@@ -219,7 +224,7 @@ __device__ __forceinline__ void dft2_tw(float2& v0, float2& v1, float t, float c
   v1 = axpy(v0, -c, u);
   v0 = axpy(v0, c, u);
 }
-template <bool OUTER, bool STAGED = false>        // input n = 4 n1 + n2, result k = k1 + 4 k2
+template <bool OUTER, bool STAGED = false, bool UP = false>        // input n = 4 n1 + n2, result k = k1 + 4 k2; times kUp where UP
 __device__ __forceinline__ void dft16_tw(float2 (&v)[16], const Tw16& w, float sgn) {
   float2 y[4][4];
 #pragma unroll
@@ -232,7 +237,12 @@ __device__ __forceinline__ void dft16_tw(float2 (&v)[16], const Tw16& w, float s
   if (STAGED) __builtin_amdgcn_sched_barrier(0);     // w is read from LDS: not all of it at once
 #pragma unroll
   for (int k1 = 0; k1 < 4; ++k1) {
-    dft4_tw<OUTER>(y[k1], w.b[k1], sgn);
+    Tw4 b = w.b[k1];
+    if (UP) {
+      b.c1 *= kUp, b.c2 *= kUp;
+      y[k1][0] = scaled(y[k1][0], kUp);
+    }
+    dft4_tw<OUTER>(y[k1], b, sgn);
 #pragma unroll
     for (int k2 = 0; k2 < 4; ++k2)
       if (!OUTER || k2 == 0 || k2 == 3) v[k1 + 4 * k2] = y[k1][k2];
@@ -456,8 +466,7 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
     for (int j = first; j < last; ++j) next[j] = __builtin_amdgcn_raw_buffer_load_b32(src, lane_off, j * step, 0);
   };
   fetch(source(blockIdx.x), 0, 16);
-  // cos and tan of 2 pi m / N, in a table that the strips then overwrite.  A quarter turn has no tangent: its cosine is taken as
-  // 2^-28, which is off by a sixteenth of the rounding of a term, and 2^28 times the data stay finite wherever squares did.
+  // cos and tan of 2 pi m / N, in a table that the strips then overwrite
   for (int t = tid; t < N; t += T) {
     float s, co;
     sincospif(2.f * ((float)t / (float)N), &s, &co);
@@ -514,7 +523,7 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
   for (int it = blockIdx.x; it < n_work; it += gridDim.x) {
     float2 x[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) x[j] = make_float2(bf16_lo(next[j]), bf16_hi(next[j]));
+    for (int j = 0; j < 16; ++j) x[j] = scaled(make_float2(bf16_lo(next[j]), bf16_hi(next[j])), kDown);
     // The next strip's values, a quarter at a time: a wave that issues all 16 loads at once stands behind those of the
     // others until most have arrived (32 x 2048 x 1024 from memory 195 us against 161).
     const bool more = it + (int)gridDim.x < n_work;
@@ -552,7 +561,7 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 16; ++j) x[j] = d0[P::row(j * M0) * CP];
-    dft16_tw<false>(x, lane_twiddles(), 1.f);
+    dft16_tw<false, false, true>(x, lane_twiddles(), 1.f);
     // Eq. 5: squares summed over the strip's sequences, which sit in CP adjacent lanes.  (The next strip's
     // first pass writes the places that this thread has just read: no barrier.)
     float e[16];

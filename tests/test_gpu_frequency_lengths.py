@@ -60,3 +60,28 @@ def test_topk_where_scores_per_thread_change(n, levels):
         idx = torch.full((3, k), -1, dtype=torch.int32, device="cuda")
         B.ct_topk_indices(scores, 3, n, k, idx)
         assert torch.equal(idx.cpu().long(), order[:, :k].sort(dim=1).values)
+
+
+@pytest.mark.parametrize("n", [256, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("alpha", [0.5, 0.75])
+def test_power_of_two_lengths_at_every_magnitude(n, alpha):
+    """Data scaled by a power of two give the same scores scaled by it, to the bit, from where squares are far from underflow
+    to where they are just finite; beyond that, up to the largest spectrum that bf16 data of one size have, scores are
+    infinite and never NaN."""
+    say(f"frequency magnitudes n={n} alpha={alpha}")
+    row = 128
+    g = torch.Generator(device="cuda").manual_seed(n)
+    k, v = (torch.randn((1, n, row), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    ws = torch.empty(B.ct_frequency_workspace_bytes(1, n, row), dtype=torch.uint8, device="cuda")
+
+    def scores(by):
+        out = torch.empty(1, n, device="cuda")
+        B.ct_frequency_scores((k.float() * by).to(torch.bfloat16), (v.float() * by).to(torch.bfloat16), 1, n * row, n, row, alpha, out,
+                              ws, ws.numel())
+        return out
+
+    want = scores(1.0)
+    for e in (-45, -20, 20, 40):
+        assert torch.equal(scores(2.0 ** e), want * 2.0 ** e), e
+    for e in (70, 95, 105, 112):          # (bins reach 2^(e + 8))
+        assert torch.isposinf(scores(2.0 ** e)).all(), e
