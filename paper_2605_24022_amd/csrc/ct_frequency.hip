@@ -135,208 +135,90 @@ __device__ __forceinline__ void dft<16>(float2 (&v)[16], float sgn) { dft_by4<4>
 // pass and the squares with the last.
 // N = 16 x 16 x MID (N = 256: 16 x 16), 16 elements per thread and pass, bin = k0 + 16 k1 + 256 k2 in row
 // k0 N/16 + k1 MID + k2.  The N/16 rows of one k0 are what one wave owns in all passes but the first and the
-// last, so only those two need a barrier; in between the waves drift apart and one's LDS accesses run beside
-// another's arithmetic.
-// Twiddles are applied ahead of a butterfly and as (tan, cos): a rotation is two fused multiply-adds up to the
-// factor cos, and that goes into the sums behind it.  A butterfly of 16 with its 15 twiddles is 176 instructions
-// that way against 224.  The forward middle pass takes w_256^(k0 j), the same for the whole wave (scalar
-// registers); what it leaves owed goes with the last one, w_N^(k2 (k0 + 16 k1)).
-// The next strip's values are fetched into registers meanwhile, spread over the passes.
-// 32 x 2048 x 1024, K and V from memory: 1290 -> 1054 instructions per wave and strip, 212 -> 165 us with the finishing launch
-// (145 us with the loads left out); 16 x 4096 x 1024 321 -> 237 us; the scores' error against 64 bits 8.0e-8 -> 5.6e-8 (2-norm).
+// last, so only those two need a barrier.
+// A thread's first twiddles do not depend on the strip: they are taken once from a table of rounded values and
+// stay in 30 registers, the second ones in a small LDS table (rows of 17 against bank conflicts).
+// The next strip's values are fetched into registers meanwhile, a quarter at a time: a wave that issues all 16 loads at once
+// stands behind those of the others until most have arrived (16 x 4096 x 1024 313 us against 185).
 // No cache hint on the loads: with the streaming one, neighbouring strips find less of a shared line (the
 // loads alone 122 us against 71).
-// Bound by vector instructions (110 us) and LDS accesses (60 us), which overlap in part.
-// A quarter turn has no tangent: its cosine is taken as 2^-28, off by a sixteenth of the rounding of a term.  So that 2^28 times
-// a bin stays finite wherever the bin does, kept or not, the transforms run on 2^-32 of the data, and the last
-// sums scale up.  (That loses values below 2^-94; squares are lost from 2^-75 on.)  1 % of the launch.
-constexpr float kDown = 0x1p-32f, kUp = 0x1p32f;
-__device__ __forceinline__ float2 scaled(float2 a, float by) { return make_float2(by * a.x, by * a.y); }
-// e^(i x), e^(2 i x) and e^(3 i x) as tangents and cosines; r = cos 3x / cos x
-struct Tw4 {
-  float t1, c1, t2, c2, t3, r;
-};
-// a (1 + sgn i t)
+// With all loads at once, the hint and a barrier per pass / now, 1024 columns of K and V: 32 sequences of 2048 212 / 150 us,
+// 16 of 4096 315 / 182, 32 of 1024 84 / 69, 32 of 512 43 / 39; one sequence of 4096 20 / 20.  Without the loads the passes of 32 x 2048
+// take 130 us and of 16 x 4096 138: bound by vector instructions and LDS accesses, which overlap in part.
+// Not kept: all twiddles as (tan, cos) ahead of a butterfly, whose sums absorb the cosine.  Fewer instructions (1054 per
+// wave and strip), but their sets take more LDS reads and a longer start: 32 x 2048 161 us, 16 x 4096 235, one sequence
+// of 4096 25, only 32 x 512 and 32 x 1024 2 to 3 % less; and a quarter turn has no tangent, so that large bins overflow.
+
+// a (1 + sgn i t), a + f b and a + sgn i f b
 __device__ __forceinline__ float2 lean(float2 a, float t, float sgn) {
   return make_float2(fmaf(-sgn * t, a.y, a.x), fmaf(sgn * t, a.x, a.y));
 }
-// a + f b and a + sgn i f b
 __device__ __forceinline__ float2 axpy(float2 a, float f, float2 b) { return make_float2(fmaf(f, b.x, a.x), fmaf(f, b.y, a.y)); }
 __device__ __forceinline__ float2 axpy_i(float2 a, float f, float2 b, float sgn) {
   return make_float2(fmaf(-sgn * f, b.y, a.x), fmaf(sgn * f, b.x, a.y));
 }
-// dft<4> of v[0], v[1] e^(sgn i x), v[2] e^(2 sgn i x), v[3] e^(3 sgn i x); with OUTER only v[0] and v[3]
-template <bool OUTER>
-__device__ __forceinline__ void dft4_tw(float2 (&v)[4], const Tw4& w, float sgn) {
-  const float2 u1 = lean(v[1], w.t1, sgn), u2 = lean(v[2], w.t2, sgn), u3 = lean(v[3], w.t3, sgn);
-  const float2 s0 = axpy(v[0], w.c2, u2), s1 = axpy(v[0], -w.c2, u2);
-  const float2 p = axpy(u1, w.r, u3), q = axpy(u1, -w.r, u3);
-  v[0] = axpy(s0, w.c1, p);
-  v[3] = axpy_i(s1, -w.c1, q, sgn);
-  if (OUTER) return;
-  v[2] = axpy(s0, -w.c1, p);
-  v[1] = axpy_i(s1, w.c1, q, sgn);
-}
-// dft<4> of v[0], v[1] e^(sgn i pi K / 8), v[2] and v[3] with the square and the cube of that
+// dft<4> of v[0], v[1] e^(sgn i x), v[2] e^(2 sgn i x) and v[3] e^(3 sgn i x), x = pi K / 8.  A rotation is taken as its tangent, two
+// fused multiply-adds, and its cosine goes into the sums behind it (twiddles folded into fused multiply-adds: Linzer and
+// Feig, "Implementation of efficient FFT algorithms on fused multiply-add architectures", IEEE Trans. Signal Process. 41, 1993).
 template <int K>
 __device__ __forceinline__ void dft4_by16(float2 (&v)[4], float sgn) {
+  constexpr float h = 0.7071067811865476f, lo = 0.4142135623730950f, hi = 2.414213562373095f;     // cos pi/4, tan pi/8, tan 3 pi/8
   if constexpr (K == 0) {
     dft<4>(v, sgn);
   } else if constexpr (K == 2) {          // (its square is a quarter turn, which has no tangent)
     const float2 u1 = lean(v[1], 1.f, sgn), u3 = lean(v[3], -1.f, sgn);
     const float2 s0 = cadd(v[0], mul_si(v[2], sgn)), s1 = csub(v[0], mul_si(v[2], sgn));
     const float2 p = csub(u1, u3), q = cadd(u1, u3);
-    constexpr float h = 0.7071067811865476f;
     v[0] = axpy(s0, h, p);
     v[2] = axpy(s0, -h, p);
     v[1] = axpy_i(s1, h, q, sgn);
     v[3] = axpy_i(s1, -h, q, sgn);
   } else {
-    constexpr float h = 0.7071067811865476f, lo = 0.4142135623730950f, hi = 2.414213562373095f;
-    constexpr Tw4 w = K == 1 ? Tw4{lo, 0.9238795325112867f, 1.f, h, hi, lo} : Tw4{hi, 0.3826834323650898f, -1.f, -h, lo, -hi};
-    dft4_tw<false>(v, w, sgn);
+    constexpr float c1 = K == 1 ? 0.9238795325112867f : 0.3826834323650898f, c2 = K == 1 ? h : -h;
+    constexpr float t1 = K == 1 ? lo : hi, t2 = K == 1 ? 1.f : -1.f, t3 = K == 1 ? hi : lo, r = K == 1 ? lo : -hi;      // r = cos 3x / cos x
+    const float2 u1 = lean(v[1], t1, sgn), u2 = lean(v[2], t2, sgn), u3 = lean(v[3], t3, sgn);
+    const float2 s0 = axpy(v[0], c2, u2), s1 = axpy(v[0], -c2, u2);
+    const float2 p = axpy(u1, r, u3), q = axpy(u1, -r, u3);
+    v[0] = axpy(s0, c1, p);
+    v[2] = axpy(s0, -c1, p);
+    v[1] = axpy_i(s1, c1, q, sgn);
+    v[3] = axpy_i(s1, -c1, q, sgn);
   }
 }
-// The inner sums over inputs 4 n1 + n2, n1 < 4: with OUTER only n1 = 0 and 3 are there.
-template <bool OUTER>
-__device__ __forceinline__ void dft4_inner(float2 (&v)[4], float sgn) {
-  if constexpr (!OUTER) {
-    dft<4>(v, sgn);
-  } else {
-    const float2 a = v[0], b = v[3], ib = mul_si(v[3], sgn);
-    v[0] = cadd(a, b);
-    v[1] = csub(a, ib);
-    v[2] = csub(a, b);
-    v[3] = cadd(a, ib);
-  }
-}
-// Transforms of R values.  plain: no twiddles; with OUTER only the first and last quarter of the inputs are there (the
-// others are not read).  tw: value n is multiplied by e^(sgn i n x) first, w = { x = 4 theta, theta, theta + pi / 8,
-// theta + 2 pi / 8, theta + 3 pi / 8 }; with OUTER only the first and last quarter of the results are written.  One such
-// set serves butterflies of 16 with x = theta, of 8 with theta and theta + pi / 8, of 4 with theta + i pi / 8 and of
-// 2 with theta + i pi / 8, i < 8.
-struct Tw16 {
-  Tw4 a, b[4];
-};
-template <bool QUARTER>      // a quarter turn more
-__device__ __forceinline__ void dft2_tw(float2& v0, float2& v1, float t, float c, float sgn) {
-  const float2 u = lean(QUARTER ? mul_si(v1, sgn) : v1, t, sgn);
-  v1 = axpy(v0, -c, u);
-  v0 = axpy(v0, c, u);
-}
-template <bool OUTER, bool STAGED = false, bool UP = false>        // input n = 4 n1 + n2, result k = k1 + 4 k2; times kUp where UP
-__device__ __forceinline__ void dft16_tw(float2 (&v)[16], const Tw16& w, float sgn) {
-  float2 y[4][4];
-#pragma unroll
-  for (int n2 = 0; n2 < 4; ++n2) {
-    float2 col[4] = {v[n2], v[4 + n2], v[8 + n2], v[12 + n2]};
-    dft4_tw<false>(col, w.a, sgn);
-#pragma unroll
-    for (int k1 = 0; k1 < 4; ++k1) y[k1][n2] = col[k1];
-  }
-  if (STAGED) __builtin_amdgcn_sched_barrier(0);     // w is read from LDS: not all of it at once
-#pragma unroll
-  for (int k1 = 0; k1 < 4; ++k1) {
-    Tw4 b = w.b[k1];
-    if (UP) {
-      b.c1 *= kUp, b.c2 *= kUp;
-      y[k1][0] = scaled(y[k1][0], kUp);
-    }
-    dft4_tw<OUTER>(y[k1], b, sgn);
-#pragma unroll
-    for (int k2 = 0; k2 < 4; ++k2)
-      if (!OUTER || k2 == 0 || k2 == 3) v[k1 + 4 * k2] = y[k1][k2];
-  }
-}
-template <bool OUTER>
-__device__ __forceinline__ void dft16_plain(float2 (&v)[16], float sgn) {
-  float2 y[4][4];
-#pragma unroll
-  for (int n2 = 0; n2 < 4; ++n2) {
-    float2 col[4] = {v[n2], v[4 + n2], v[8 + n2], v[12 + n2]};
-    dft4_inner<OUTER>(col, sgn);
-#pragma unroll
-    for (int k1 = 0; k1 < 4; ++k1) y[k1][n2] = col[k1];
-  }
-  dft4_by16<0>(y[0], sgn);
-  dft4_by16<1>(y[1], sgn);
-  dft4_by16<2>(y[2], sgn);
-  dft4_by16<3>(y[3], sgn);
-#pragma unroll
-  for (int k = 0; k < 16; ++k) v[k] = y[k & 3][k >> 2];
-}
-template <bool OUTER, int I>      // input n = 4 n1 + n2, result k = k1 + 2 k2
-__device__ __forceinline__ void dft8_tw(float2 (&v)[8], const Tw16& w, float sgn) {
-#pragma unroll
-  for (int n2 = 0; n2 < 4; ++n2) dft2_tw<I != 0>(v[n2], v[4 + n2], w.a.t1, w.a.c1, sgn);     // 4 (theta + pi / 8)
-#pragma unroll
-  for (int k1 = 0; k1 < 2; ++k1) {
-    float2 y[4] = {v[4 * k1], v[4 * k1 + 1], v[4 * k1 + 2], v[4 * k1 + 3]};
-    dft4_tw<OUTER>(y, w.b[I + 2 * k1], sgn);
-#pragma unroll
-    for (int k2 = 0; k2 < 4; ++k2) v[4 * k1 + k2] = y[k2];
-  }
-  const float2 r[8] = {v[0], v[4], v[1], v[5], v[2], v[6], v[3], v[7]};
-#pragma unroll
-  for (int k = 0; k < 8; ++k) v[k] = r[k];
-}
-template <bool OUTER>
-__device__ __forceinline__ void dft8_plain(float2 (&v)[8], float sgn) {
-  float2 y[2][4];
-#pragma unroll
-  for (int n2 = 0; n2 < 4; ++n2) {
-    if (OUTER) {       // inputs 0, 1, 6 and 7
-      y[0][n2] = n2 < 2 ? v[n2] : v[4 + n2];
-      y[1][n2] = n2 < 2 ? v[n2] : make_float2(-v[4 + n2].x, -v[4 + n2].y);
-    } else {
-      y[0][n2] = cadd(v[n2], v[4 + n2]);
-      y[1][n2] = csub(v[n2], v[4 + n2]);
-    }
-  }
-  dft4_by16<0>(y[0], sgn);
-  dft4_by16<2>(y[1], sgn);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) v[k] = y[k & 1][k >> 1];
-}
-// butterfly I of R values
-template <int R, bool OUTER, int I>
-__device__ __forceinline__ void dft_tw(float2 (&v)[R], const Tw16& w, float sgn) {
-  if constexpr (R == 16) dft16_tw<OUTER>(v, w, sgn);
-  else if constexpr (R == 8) dft8_tw<OUTER, I>(v, w, sgn);
-  else if constexpr (R == 4) dft4_tw<OUTER>(v, w.b[I], sgn);
-  else dft2_tw<(I >= 4)>(v[0], v[1], w.b[I % 4].t1, w.b[I % 4].c1, sgn);
-}
+// dft<16> that way; dft<R> otherwise.  OUTER (R = 4): of a forward transform (sgn < 0) results 0 and 3 alone, of an inverse one inputs 0 and 3.
 template <int R, bool OUTER>
-__device__ __forceinline__ void dft_plain(float2 (&v)[R], float sgn) {
-  if constexpr (R == 16) dft16_plain<OUTER>(v, sgn);
-  else if constexpr (R == 8) dft8_plain<OUTER>(v, sgn);
-  else if constexpr (R == 4) dft4_inner<OUTER>(v, sgn);
-  else dft<2>(v, sgn);
-}
-// a / b by a refined reciprocal (no zero, infinity or denormal here)
-__device__ __forceinline__ float quick_div(float a, float b) {
-  float y = __builtin_amdgcn_rcpf(b);
-  y = fmaf(fmaf(-b, y, 1.f), y, y);
-  const float q = a * y;
-  return fmaf(fmaf(-b, q, a), y, q);
-}
-// tab[m] = (cos, tan) of 2 pi m / N -> the set of theta = 2 pi m / N
-template <int N>
-__device__ __forceinline__ Tw4 make_tw4(const float2* tab, int m) {
-  const float2 a = tab[m & (N - 1)], b = tab[(2 * m) & (N - 1)], c = tab[(3 * m) & (N - 1)];
-  return Tw4{a.y, a.x, b.y, b.x, c.y, quick_div(c.x, a.x)};
-}
-template <int N>
-__device__ __forceinline__ Tw16 make_tw16(const float2* tab, int m) {
-  return Tw16{make_tw4<N>(tab, 4 * m),
-              {make_tw4<N>(tab, m), make_tw4<N>(tab, m + N / 16), make_tw4<N>(tab, m + N / 8), make_tw4<N>(tab, m + 3 * N / 16)}};
-}
-__device__ __forceinline__ float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
-__device__ __forceinline__ Tw4 uniform(const Tw4& w) {
-  return Tw4{uniform(w.t1), uniform(w.c1), uniform(w.t2), uniform(w.c2), uniform(w.t3), uniform(w.r)};
-}
-__device__ __forceinline__ Tw16 uniform(const Tw16& w) {
-  return Tw16{uniform(w.a), {uniform(w.b[0]), uniform(w.b[1]), uniform(w.b[2]), uniform(w.b[3])}};
+__device__ __forceinline__ void dft_fixed(float2 (&v)[R], float sgn) {
+  if constexpr (R == 16) {
+    float2 y[4][4];
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) {
+      float2 col[4] = {v[n2], v[4 + n2], v[8 + n2], v[12 + n2]};
+      dft<4>(col, sgn);
+#pragma unroll
+      for (int k1 = 0; k1 < 4; ++k1) y[k1][n2] = col[k1];
+    }
+    dft4_by16<0>(y[0], sgn);
+    dft4_by16<1>(y[1], sgn);
+    dft4_by16<2>(y[2], sgn);
+    dft4_by16<3>(y[3], sgn);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = y[k & 3][k >> 2];
+  } else if constexpr (OUTER) {
+    static_assert(R == 4, "the other lengths gain nothing or spill");
+    if (sgn < 0) {
+      const float2 t2 = cadd(v[1], v[3]), t3 = mul_si(csub(v[1], v[3]), sgn), t1 = csub(v[0], v[2]);
+      v[0] = cadd(cadd(v[0], v[2]), t2);
+      v[3] = csub(t1, t3);
+    } else {
+      const float2 a = v[0], b = v[3], ib = mul_si(v[3], sgn);
+      v[0] = cadd(a, b);
+      v[1] = csub(a, ib);
+      v[2] = csub(a, b);
+      v[3] = cadd(a, ib);
+    }
+  } else {
+    dft<R>(v, sgn);
+  }
 }
 
 // x + (x of the lane that the DPP control names)
@@ -391,23 +273,19 @@ __device__ __forceinline__ int reduce_scatter16(float (&e)[16], int c) {
   return first;
 }
 
-template <int I> using Number = std::integral_constant<int, I>;
-
 template <int N>
 struct FixedPlan {
   static constexpr int CP = kFreqMaxElems / N;            // complex sequences per strip
   static constexpr int MID = N == 256 ? 16 : N / 256;
   static constexpr int M0 = N / 16;                       // distance of the elements of a first-pass butterfly
   static constexpr int M1 = MID;                          // and of a second-pass one
-  // A wave's accesses to LDS: rows next to one another (second pass), MID apart (middle) and 16 apart (first and last); spare rows,
-  // and the order in which lanes take those of the latter two, so that either half of the wave falls on distinct banks.
-  static constexpr __host__ __device__ int row(int n) { return N == 1024 ? n + (n >> 3) + (n >> 4) : N >= 2048 ? n + (n >> 4) : n; }
-  static __device__ __forceinline__ int order(int lane_row) {
-    return N == 2048 ? (0x74216530 >> (4 * lane_row)) & 15 : N == 1024 ? (0x2130 >> (4 * lane_row)) & 15 : lane_row;
-  }
-  static constexpr int ROWS = row(N);
-  static constexpr size_t LDS_BYTES = (size_t)ROWS * CP * sizeof(float2) + (N == 256 ? 0 : MID * sizeof(Tw16)) + (N == 4096 ? 512 * sizeof(Tw4) : 0);
-  static_assert(LDS_BYTES <= 160 * 1024 && (size_t)N * sizeof(float2) <= (size_t)ROWS * CP * sizeof(float2), "LDS");
+  // one spare row per 8 (16 when the middle pass owns 16 rows): the middle pass's accesses, MID rows
+  // apart, then fall on distinct banks (N = 1024: with the order of rows that its lanes take)
+  static constexpr int PAD = MID == 16 ? 4 : 3;
+  static constexpr int ROWS = N + (N >> PAD);
+  static constexpr __host__ __device__ int row(int n) { return n + (n >> PAD); }
+  static constexpr size_t LDS_BYTES = ((size_t)ROWS * CP + (N == 256 ? 0 : MID * 17)) * sizeof(float2);
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
 // partial[tensor * groups * n + g * n + token] = sum over strip g of |N x~|^2
@@ -418,15 +296,28 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
   using P = FixedPlan<N>;
   constexpr int CP = P::CP, MID = P::MID, M0 = P::M0, M1 = P::M1, T = kFreqThreads;
   extern __shared__ float2 data[];
-  Tw16* const inv_tab = reinterpret_cast<Tw16*>(data + P::ROWS * CP);        // middle inverse pass, per row mod MID
-  Tw4* const a_tab = reinterpret_cast<Tw4*>(inv_tab + MID);                  // w0.a and w0.b[0]: butterflies of 16 in the middle need the registers
-  const int tid = threadIdx.x, c = tid % CP;
-  const int k0 = __builtin_amdgcn_readfirstlane(tid >> 6), lane_row = (tid & 63) / CP;
-  // first and last pass: rows u + j M0; second: rows k0 M0 + j M1 + lane_row; middle: rows k0 M0 + k1 MID + j for
-  // k1 = order(lane_row) + i MID, so that the twiddles of k0 + 16 k1 are those of u
-  const int k1 = N == 256 ? 0 : P::order(lane_row), u = k0 + 16 * k1;
+  float2* const tab1 = data + P::ROWS * CP;      // [u % M1][j]
+  const int tid = threadIdx.x, c = tid % CP, u = tid / CP;
+  // first (and last) pass: rows u + j M0; second: rows k0 M0 + j M1 + u % M1; middle: rows k0 M0 + k1 MID + j; k0 = u / M1 is the wave
+  const int k0 = u / M1;
   float2* const d0 = data + P::row(u) * CP + c;
-  float2* const d1 = data + (P::row(k0 * M0) + lane_row) * CP + c;
+  float2* const d1 = data + P::row(N == 256 ? 0 : k0 * M0 + u % M1) * CP + c;
+  // twiddles exp(-2 pi i u j / N) and exp(-2 pi i (u % M1) j / M0), from a table that the strips then overwrite
+  for (int t = tid; t < N; t += T) {
+    float s, co;
+    sincospif(-2.f * ((float)t / (float)N), &s, &co);
+    data[t] = make_float2(co, s);
+  }
+  __syncthreads();
+  float2 w0[16];
+#pragma unroll
+  for (int j = 1; j < 16; ++j) w0[j] = data[(u * j) % N];
+  if (N > 256 && tid < M1 * 16) tab1[(tid >> 4) * 17 + (tid & 15)] = data[((tid >> 4) * (tid & 15) * 16) % N];
+  __syncthreads();
+  const float2* const w1 = tab1 + (u % M1) * 17;
+
+  const int gone_first = cutoff, gone_last = cutoff == 0 ? N - 1 : N - cutoff;   // Eq. 3: these bins go
+  const uint32_t gone = gone_last >= gone_first ? gone_last - gone_first + 1 : 0;
   // workgroups that share 128-byte lines of the rows (adjacent strips) are given ids that differ
   // by 8, which puts them on the same XCD (and its L2) at the same time.  An XCD that has whole tensors takes every
   // second line of one first and then the others, so that what it reads at a time comes through all channels of
@@ -465,103 +356,75 @@ __global__ __launch_bounds__(kFreqThreads) void freq_fixed_kernel(const uint16_t
 #pragma unroll
     for (int j = first; j < last; ++j) next[j] = __builtin_amdgcn_raw_buffer_load_b32(src, lane_off, j * step, 0);
   };
-  fetch(source(blockIdx.x), 0, 16);
-  // cos and tan of 2 pi m / N, in a table that the strips then overwrite
-  for (int t = tid; t < N; t += T) {
-    float s, co;
-    sincospif(2.f * ((float)t / (float)N), &s, &co);
-    if (t == N / 4 || t == 3 * (N / 4)) co = 0x1p-28f;
-    data[t] = make_float2(co, quick_div(s, co));
-  }
-  __syncthreads();
-  Tw16 w0 = make_tw16<N>(data, u), w1;            // w_N^u and, the same for the wave, w_256^k0
-  if constexpr (N > 256) {
-    w1 = uniform(make_tw16<N>(data, k0 * MID));
-    if (tid < MID) inv_tab[tid] = make_tw16<N>(data, 16 * tid);
-    if (N == 4096 && c == 0) a_tab[k0 * 32 + 2 * k1] = w0.a, a_tab[k0 * 32 + 2 * k1 + 1] = w0.b[0];
-  } else {
-    w0 = uniform(w0);                             // (u is k0)
-  }
-  __syncthreads();
-
-  const int gone_first = cutoff, gone_last = cutoff == 0 ? N - 1 : N - cutoff;   // Eq. 3: these bins go
-  const uint32_t gone = gone_last >= gone_first ? gone_last - gone_first + 1 : 0;
-  auto lane_twiddles = [&]() __attribute__((always_inline)) {
-    return N == 4096 ? Tw16{a_tab[k0 * 32 + 2 * k1], {a_tab[k0 * 32 + 2 * k1 + 1], w0.b[1], w0.b[2], w0.b[3]}} : w0;
-  };
   // rows that only this wave reads and writes: its LDS accesses run in order
   auto own_rows = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
-  // Up to half of the spectrum kept (alpha <= 0.5): the second and third quarter of every last-pass butterfly go whole
-  // and are neither computed nor transformed back.
-  const bool outer = MID >= 4 && cutoff <= N / 4;
+  // the last forward pass, the mask and the first inverse pass: MID neighbouring rows.  Up to half of the spectrum kept
+  // (alpha <= 0.5), results 1 and 2 of a butterfly of four go whole and are neither computed nor transformed back (32 x 1024 x 1024 1 %).
   auto middle = [&](auto is_outer) __attribute__((always_inline)) {
-    constexpr bool OUTER = MID >= 4 && decltype(is_outer)::value;
-    auto butterfly = [&](auto number) __attribute__((always_inline)) {
-      constexpr int I = decltype(number)::value;
-      if constexpr (I < 16 / MID) {
-        float2* const dm = data + (P::row(k0 * M0) + P::row(k1 * MID) + P::row(I * MID * MID)) * CP + c;
-        float2 y[MID];
+    constexpr bool OUTER = decltype(is_outer)::value;
 #pragma unroll
-        for (int j = 0; j < MID; ++j) y[j] = dm[j * CP];
-        dft_tw<MID, OUTER, I>(y, lane_twiddles(), -1.f);
-        const int bin0 = u + 16 * I * MID;
-        constexpr int BSTEP = N == 256 ? 16 : 256;
+    for (int i = 0; i < 16 / MID; ++i) {
+      const int k1 = N == 256 ? 0 : i * MID + (N == 1024 ? (u & 1) << 1 | (u >> 1 & 1) : u % MID);
+      const int q = N == 256 ? u : k0 * 16 + k1;
+      float2* const dm = data + P::row(q * MID) * CP + c;
+      float2 y[MID];
 #pragma unroll
-        for (int j = 0; j < MID; ++j)
-          if ((!OUTER || j < MID / 4 || j >= MID - MID / 4) && (uint32_t)(bin0 + BSTEP * j - gone_first) < gone) y[j] = make_float2(0.f, 0.f);
-        dft_plain<MID, OUTER>(y, 1.f);
+      for (int j = 0; j < MID; ++j) y[j] = dm[P::row(j) * CP];
+      dft_fixed<MID, OUTER>(y, -1.f);
+      const int bin0 = N == 256 ? u : k0 + 16 * k1;
+      constexpr int BSTEP = N == 256 ? 16 : 256;
 #pragma unroll
-        for (int j = 0; j < MID; ++j) dm[j * CP] = y[j];
-      }
-    };
-    butterfly(Number<0>{}), butterfly(Number<1>{}), butterfly(Number<2>{}), butterfly(Number<3>{});
-    butterfly(Number<4>{}), butterfly(Number<5>{}), butterfly(Number<6>{}), butterfly(Number<7>{});
+      for (int j = 0; j < MID; ++j)
+        if ((!OUTER || j == 0 || j == 3) && (uint32_t)(bin0 + BSTEP * j - gone_first) < gone) y[j] = make_float2(0.f, 0.f);
+      dft_fixed<MID, OUTER>(y, 1.f);
+#pragma unroll
+      for (int j = 0; j < MID; ++j) dm[P::row(j) * CP] = y[j];
+    }
   };
+  fetch(source(blockIdx.x), 0, 16);
   for (int it = blockIdx.x; it < n_work; it += gridDim.x) {
     float2 x[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) x[j] = scaled(make_float2(bf16_lo(next[j]), bf16_hi(next[j])), kDown);
-    // The next strip's values, a quarter at a time: a wave that issues all 16 loads at once stands behind those of the
-    // others until most have arrived (32 x 2048 x 1024 from memory 195 us against 161).
+    for (int j = 0; j < 16; ++j) x[j] = make_float2(bf16_lo(next[j]), bf16_hi(next[j]));
     const bool more = it + (int)gridDim.x < n_work;
     const __amdgpu_buffer_rsrc_t src = source(more ? it + gridDim.x : it);
     auto ahead = [&](int part) __attribute__((always_inline)) {
       if (more) fetch(src, 4 * part, 4 * part + 4);
     };
     ahead(0);
-    dft16_plain<false>(x, -1.f);
+    dft_fixed<16, false>(x, -1.f);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) d0[P::row(j * M0) * CP] = x[j];
+    for (int j = 0; j < 16; ++j) d0[P::row(j * M0) * CP] = j == 0 ? x[0] : cmul(x[j], w0[j]);
     __syncthreads();
     ahead(1);
     if constexpr (N > 256) {
 #pragma unroll
       for (int j = 0; j < 16; ++j) x[j] = d1[P::row(j * M1) * CP];
-      dft16_tw<false>(x, w1, -1.f);
+      dft_fixed<16, false>(x, -1.f);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) d1[P::row(j * M1) * CP] = x[j];
+      for (int j = 0; j < 16; ++j) d1[P::row(j * M1) * CP] = j == 0 ? x[0] : cmul(x[j], w1[j]);
       own_rows();
     }
     ahead(2);
-    // the last forward pass, the mask and the first inverse pass: MID neighbouring rows
-    if (outer) middle(std::true_type{});
+    if (MID == 4 && cutoff <= N / 4) middle(std::integral_constant<bool, MID == 4>{});
     else middle(std::false_type{});
+    if (N == 256) __syncthreads();
     ahead(3);
     if constexpr (N > 256) {
       own_rows();
 #pragma unroll
-      for (int j = 0; j < 16; ++j) x[j] = d1[P::row(j * M1) * CP];
-      dft16_tw<false, MID == 16>(x, inv_tab[lane_row], 1.f);
+      for (int j = 0; j < 16; ++j) x[j] = j == 0 ? d1[0] : cmul_conj(d1[P::row(j * M1) * CP], w1[j]);
+      dft_fixed<16, false>(x, 1.f);
 #pragma unroll
       for (int j = 0; j < 16; ++j) d1[P::row(j * M1) * CP] = x[j];
+      __syncthreads();
     }
-    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 16; ++j) x[j] = d0[P::row(j * M0) * CP];
-    dft16_tw<false, false, true>(x, lane_twiddles(), 1.f);
+    for (int j = 0; j < 16; ++j) x[j] = j == 0 ? d0[0] : cmul_conj(d0[P::row(j * M0) * CP], w0[j]);
+    dft_fixed<16, false>(x, 1.f);
     // Eq. 5: squares summed over the strip's sequences, which sit in CP adjacent lanes.  (The next strip's
     // first pass writes the places that this thread has just read: no barrier.)
     float e[16];
