@@ -139,7 +139,7 @@ __device__ __forceinline__ void dft<16>(float2 (&v)[16], float sgn) { dft_by4<4>
 // A thread's first twiddles do not depend on the strip: they are taken once from a table of rounded values and
 // stay in 30 registers, the second ones in a small LDS table (rows of 17 against bank conflicts).
 // The next strip's values are fetched into registers meanwhile, a quarter at a time: a wave that issues all 16 loads at once
-// stands behind those of the others until most have arrived (16 x 4096 x 1024 313 us against 185).
+// stands behind those of the others until most have arrived (32 x 2048 x 1024 with an earlier form of the passes 195 us against 161).
 // No cache hint on the loads: with the streaming one, neighbouring strips find less of a shared line (the
 // loads alone 122 us against 71).
 // With all loads at once, the hint and a barrier per pass / now, 1024 columns of K and V: 32 sequences of 2048 212 / 150 us,
@@ -984,13 +984,18 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
   const uint32_t n = n_tokens;     // (unsigned: positions run past the end by up to a batch)
   if (k <= 0) return;
   uint32_t own[KEYS > 0 ? KEYS : 1];
-  const uint32_t own0 = KEYS > 0 ? wv * (KEYS * 64) + lane : 0;      // token of own[0], the others 64 apart
+  // Wave w holds and sweeps a stretch of its own, equal ones: n of a launch lies in (512 KEYS, 1024 KEYS], so that the upper half of
+  // the registers may go unused, the same ones in all waves.
+  const uint32_t stretch = (n + 1023) / 1024 * 64, begin = wv * stretch, end = min(n, begin + stretch);
+  auto used = [&](int b) __attribute__((always_inline)) { return KEYS <= 2 || b < KEYS / 2 || b * 64u < stretch; };
+  const uint32_t own0 = KEYS > 0 ? begin + lane : 0;      // token of own[0], the others 64 apart
 #pragma unroll
-  for (int b = 0; b < KEYS; ++b) own[b] = own0 + b * 64 < n ? score_key(s[own0 + b * 64]) : 0u;
+  for (int b = 0; b < KEYS; ++b)
+    if (used(b)) own[b] = own0 + b * 64 < n ? score_key(s[own0 + b * 64]) : 0u;
   // n, opaque (and the threshold below): compared again in each pass instead of results being kept, two scalar registers per key
   auto count_of = [&]() __attribute__((always_inline)) {
     uint32_t m = n;
-    asm volatile("" : "+s"(m));
+    if (KEYS > 1) asm volatile("" : "+s"(m));
     return m;
   };
   // radix select, most significant byte first: after the loop `prefix` is the key of the k-th
@@ -1024,6 +1029,7 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
         uint32_t same = 0;
 #pragma unroll
         for (int b = 0; b < KEYS; ++b) {
+          if (!used(b)) continue;
           const bool in = own0 + b * 64 < n;
           same += __popcll(__ballot(in && (own[b] >> 24) == common));
           if (in && (own[b] >> 24) != common) atomicAdd(&hist[own[b] >> 24], 1u);
@@ -1031,7 +1037,8 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
         if (lane == 0 && same > 0) atomicAdd(&hist[common], same);
       } else {
 #pragma unroll
-        for (int b = 0; b < KEYS; ++b) count(own[b], own0 + b * 64 < n);
+        for (int b = 0; b < KEYS; ++b)
+          if (used(b)) count(own[b], own0 + b * 64 < n);
       }
     } else {
       for (uint32_t i0 = tid; i0 - tid < n; i0 += 1024 * kTopkBatch) {
@@ -1074,16 +1081,16 @@ __global__ __launch_bounds__(1024) void topk_kernel(const float* __restrict__ sc
     need = sh_need;
     __syncthreads();
   }
-  // ordered sweep: tokens above the threshold, and the first `need` tokens on it.  Wave w owns one
-  // stretch of tokens; it counts both kinds, and what the waves before it hold says where it writes.
-  const uint32_t stretch = (n + 1023) / 1024 * 64, begin = wv * stretch, end = min(n, begin + stretch);
+  // ordered sweep: tokens above the threshold, and the first `need` tokens on it.  A wave counts both kinds in its
+  // stretch, and what the waves before it hold says where it writes.
   auto sweep = [&](auto&& body) __attribute__((always_inline)) {
     if constexpr (KEYS > 0) {
       const uint32_t n = count_of();
       uint32_t limit = prefix;
-      asm volatile("" : "+v"(limit));
+      if (KEYS > 1) asm volatile("" : "+v"(limit));
 #pragma unroll
       for (int b = 0; b < KEYS; ++b) {
+        if (!used(b)) continue;
         const uint32_t i = own0 + b * 64;
         body(i, i < n && own[b] > limit, i < n && own[b] == limit);
       }

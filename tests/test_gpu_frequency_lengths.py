@@ -48,7 +48,7 @@ def test_power_of_two_lengths_around_half_the_spectrum(n, row, n_batch):
         test_scores_against_fp64(n, row, n_batch, (cutoff + 0.5) / (n // 2 + 1))
 
 
-@pytest.mark.parametrize("n", [1023, 1025, 2047, 2048, 2049, 4096, 4097, 8191, 8193, 16384, 16385, 32767, 32768, 32769])
+@pytest.mark.parametrize("n", [1023, 1025, 2047, 2048, 2049, 3000, 4096, 4097, 8191, 8193, 9001, 16384, 16385, 20481, 32767, 32768, 32769])
 @pytest.mark.parametrize("levels", [3, 1 << 20])
 def test_topk_where_scores_per_thread_change(n, levels):
     """Both sides of every number of scores that a thread holds, with many ties and with few, of either sign."""
