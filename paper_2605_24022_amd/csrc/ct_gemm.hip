@@ -422,6 +422,17 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
     const int f0 = f_blk + row0;
     const int rope_end = (a.Hq + a.Hkv) * D;   // features below this are q or k heads
     const int q_end = a.Hq * D;
+    constexpr int STEP = STYLE != 0 ? 0 : SPLIT ? 2 : D / 32;   // tile distance between the halves of a pair (j, j + D/2)
+    // the lane's frequencies, ahead of the first store: loaded where they are used, they came in a chain of two loads per token
+    constexpr int PAIRS = STYLE == 0 ? 4 : 2;                   // per tile of "a" halves, or of neighbouring pairs
+    double turns[FM][PAIRS];
+  #pragma unroll
+    for (int m = 0; m < FM; ++m) {
+      if (m & STEP) continue;
+      const int j0 = (f0 + m_row(m)) % D + 4 * h;
+  #pragma unroll
+      for (int i = 0; i < PAIRS; ++i) turns[m][i] = rope.turns[STYLE == 0 ? j0 + i : (j0 >> 1) + i];
+    }
   #pragma unroll
     for (int n = 0; n < TW; ++n) {
       const int t = t_blk + t0 + 16 * n;
@@ -439,17 +450,14 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
 
       if (STYLE == 0) {
         // pairs (j, j + D/2), D/2 rows apart
-        constexpr int STEP = SPLIT ? 2 : D / 32;    // tile distance between the two halves of a pair
   #pragma unroll
         for (int m = 0; m < FM; ++m) {
           if (m & STEP) continue;
-          const int fa0 = f0 + m_row(m);        // first feature of the "a" half tile
-          if (fa0 >= rope_end) continue;      // v heads are not rotated
+          if (f0 + m_row(m) >= rope_end) continue;      // v heads are not rotated
   #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int j = (fa0 % D) + 4 * h + i;
             float c, s;
-            sincos_turns(pos[n], rope.turns[j], c, s);
+            sincos_turns(pos[n], turns[m][i], c, s);
             const float x = acc[m][n][i], y = acc[m + STEP][n][i];
             acc[m][n][i] = x * c - y * s;
             acc[m + STEP][n][i] = x * s + y * c;
@@ -458,13 +466,11 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
       } else {
   #pragma unroll
         for (int m = 0; m < FM; ++m) {
-          const int fa0 = f0 + m_row(m);
-          if (fa0 >= rope_end) continue;
+          if (f0 + m_row(m) >= rope_end) continue;
   #pragma unroll
           for (int i = 0; i < 4; i += 2) {
-            const int j = ((fa0 % D) + 4 * h + i) >> 1;
             float c, s;
-            sincos_turns(pos[n], rope.turns[j], c, s);
+            sincos_turns(pos[n], turns[m][i >> 1], c, s);
             const float x = acc[m][n][i], y = acc[m][n][i + 1];
             acc[m][n][i] = x * c - y * s;
             acc[m][n][i + 1] = x * s + y * c;
