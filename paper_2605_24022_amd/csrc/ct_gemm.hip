@@ -250,7 +250,6 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
   if constexpr (EPI == EPI_QKV_ROPE) {
     if (a.sel_pos == nullptr) rows_to_positions(chunks, pos);   // while the first tiles are on their way
   }
-  int sa = 0, sb = 0;
   // Fragments: two register sets of four feature tiles each, two of the four token tiles.
   bf16x8 fa[2][4], fb[2][TW];
   auto read_a = [&](const unsigned char* a_base, int ks, int m, int set) __attribute__((always_inline)) {
@@ -265,21 +264,23 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
     acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[aset][i >> 2], fb[ks][n], acc[m][n], 0, 0, 0);
   };
   const unsigned char* const b_lds = lds + A_SLOTS * A_BYTES;
+  // vmcnt(AHEAD): this wave's loads of the step after this one have landed; lgkmcnt(0): its fragment reads of this step are done
+  constexpr int WAIT_END = WAIT_STEP & ~0x0f00;
   __builtin_amdgcn_s_waitcnt(WAIT_STEP);   // this wave's loads of step 0 have landed
   __syncthreads();                         // everybody's have
+  // (in the order of the loops: the compiler's count of reads in flight at a loop's start is then exact)
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    read_b(b_lds, 0, r, 0);
-    read_a(lds, 0, r, 0);
-  }
-  for (int kt = 0; kt < nk; ++kt) {
-    const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slot of step kt - 1
-    const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1;
-    const int sb_next = sb == B_SLOTS - 1 ? 0 : sb + 1;
-    const unsigned char *a_base = lds + sa * A_BYTES, *a_next = lds + sa_next * A_BYTES;
-    const unsigned char *b_base = b_lds + sb * B_BYTES, *b_next = b_lds + sb_next * B_BYTES;
-    const int k2 = kbase + min(kt + 2, nk - 1) * BK;
-    if constexpr (NB == 2) {
+  for (int r = 0; r < 4; ++r) read_b(b_lds, 0, r, 0);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) read_a(lds, 0, r, 0);
+  if constexpr (NB == 2) {
+    int sa = 0, sb = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      const int sa_free = sa == 0 ? A_SLOTS - 1 : sa - 1;   // slot of step kt - 1
+      const int sa_next = sa == A_SLOTS - 1 ? 0 : sa + 1, sb_next = sb ^ 1;
+      const unsigned char *a_base = lds + sa * A_BYTES, *a_next = lds + sa_next * A_BYTES;
+      const unsigned char *b_base = b_lds + sb * B_BYTES, *b_next = b_lds + sb_next * B_BYTES;
+      const int k2 = kbase + min(kt + 2, nk - 1) * BK;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         mfma(0, 0, 0, i);
@@ -304,30 +305,78 @@ __device__ __forceinline__ void gemm_workgroup(const GemmArgs& a, const RopeTabl
         else if (i == 4 || i == 8) issue_b1(k2, sb, 2 + (i - 4) / 4);
         __builtin_amdgcn_sched_barrier(0);
       }
-    } else {
-      const int sb_free = sb == 0 ? B_SLOTS - 1 : sb - 1;   // slot of step kt - 1
+      __builtin_amdgcn_s_waitcnt(WAIT_END);
+      __syncthreads();                         // everybody's loads have landed; everybody is done reading step kt
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        mfma(1, 1, 4, i);
+        if (i < 4) read_b(b_next, 0, i, 0);
+        else if (i < 8) read_a(a_next, 0, i - 4, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      sa = sa_next;
+      sb = sb_next;
+    }
+  } else {
+    // Few 128-token tiles leave units idle and the clock high: the MFMAs of a step, 1024 cycles of a SIMD's two waves, have to go out
+    // one after the other.  So between two MFMAs of a wave stand at most one read or one load (three instructions), never
+    // both; the scalars of the next step are worked out in its second half, where nothing waits for them (at the start
+    // of a step, where all waves stand, the matrix cores waited with them).  QKV of 153 rows, K = 4096 40.3 -> 38.4 us,
+    // gate/up of 300 rows of 4096 x 4096 39.8 -> 38.0; all loads behind the reads, or half of them a step earlier: no gain.
+    uint32_t lds_a = lds_addr0 + 2 * A_BYTES + wave * 1024;      // where this wave's loads of step kt + 2 go
+    uint32_t lds_b = lds_addr0 + A_SLOTS * A_BYTES + 2 * B_BYTES + wave * 1024;
+    uint32_t at_a = 0, at_b = 0, next_a = A_BYTES, next_b = B_BYTES;     // slots of steps kt and kt + 1
+    const int k2 = kbase + min(2, nk - 1) * BK;
+    const uint16_t *from_a = a.wqkv + k2, *from_up = EPI == EPI_SWIGLU ? a.w_up + k2 : nullptr, *from_b = a.hidden + k2;
+    static_assert(B_SLOTS == 3 && A_SLOTS == 3 && A_LOADS == 4 && B_LOADS == 2 && FM == 4, "the order of reads and loads below");
+    auto load = [&](const uint16_t* base, uint32_t byte_off, uint32_t lds_addr, int j) __attribute__((always_inline)) {
+      asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   : : "s"(lds_addr), "v"(byte_off), "s"(base), "i"(j * NWAVES * 1024) : "memory", "m0", "scc");
+    };
+    for (int kt = 0; kt < nk; ++kt) {
+      const unsigned char *a_base = lds + at_a, *b_base = b_lds + at_b;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         mfma(0, 0, 0, i);
-        if (i < B_LOADS) issue_b1(k2, sb_free, i);
-        else if (i < B_LOADS + A_LOADS) issue_a1(k2, sa_free, i - B_LOADS);
-        if (i < 4) read_b(b_base, 1, i, 1);
-        else if (i < 8) read_a(a_base, 1, i - 4, 1);
+        constexpr int READ[16] = {0, -1, 1, -1, 2, 3, -1, 4, 5, -1, 6, 7, -1, -1, -1, -1};
+        constexpr int LOAD[16] = {-1, 0, -1, 1, -1, -1, 2, -1, -1, 3, -1, -1, -1, 4, -1, 5};
+        const int r = READ[i], j = LOAD[i];
+        if (r >= 0 && r < 4) read_b(b_base, 1, r, 1);
+        if (r >= 4) read_a(a_base, 1, r - 4, 1);
+        if (j >= 0 && j < 2) load(from_b, b_off[j & 1], lds_b, j);
+        if (j >= 2) load(EPI == EPI_SWIGLU && (j & 1) ? from_up : from_a, a_off[(j - 2) & 3], lds_a, j - 2);   // (load 1 and 3 of a tile: up rows)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_s_waitcnt(WAIT_END);
+      __syncthreads();                         // everybody's loads have landed; everybody is done reading step kt
+      const unsigned char *a_next = lds + next_a, *b_next = b_lds + next_b;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        mfma(1, 1, 0, i);
+        if (i < 4) read_b(b_next, 0, i, 0);
+        else if (i < 8) read_a(a_next, 0, i - 4, 0);
+        if (i == 9) {      // the slots of this step are free; the asm statements keep these here
+          lds_a = lds_addr0 + at_a + wave * 1024;
+          lds_b = lds_addr0 + A_SLOTS * A_BYTES + at_b + wave * 1024;
+          asm volatile("" : "+s"(lds_a), "+s"(lds_b));
+        }
+        if (i == 11) {
+          at_a = next_a;
+          at_b = next_b;
+          next_a = next_a == 2 * A_BYTES ? 0 : next_a + A_BYTES;
+          next_b = next_b == 2 * B_BYTES ? 0 : next_b + B_BYTES;
+          asm volatile("" : "+s"(at_a), "+s"(at_b), "+s"(next_a), "+s"(next_b));
+        }
+        if (i == 13) {
+          const int by = kt + 3 < nk ? BK : 0;
+          from_a += by;
+          from_b += by;
+          if (EPI == EPI_SWIGLU) from_up += by;
+          asm volatile("" : "+s"(from_a), "+s"(from_b), "+s"(from_up));
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    __builtin_amdgcn_s_waitcnt(WAIT_STEP & ~0x0f00);   // vmcnt(AHEAD): this wave's loads of step kt + 1 have
-                                                        // landed; lgkmcnt(0): its fragment reads of step kt are done
-    __syncthreads();                           // everybody's have; everybody is done reading step kt
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      mfma(1, 1, FM - 4, i);
-      if (i < 4) read_b(b_next, 0, i, 0);
-      else if (i < 8) read_a(a_next, 0, i - 4, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    sa = sa_next;
-    sb = sb_next;
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);   // the repeated loads of the last steps have landed before the LDS is released
 
