@@ -346,11 +346,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
         const int rel = pos[n] - k0 - 4 * h;   // key offsets 16u + i <= rel are visible
+        // Four selections at once.  Element by element the compiler joins their conditions: 100 instructions and
+        // 90 scalar registers, where few rows, far apart, mask nearly every tile (32/8 heads of 128, 100 rows of 2048
+        // tokens 49.5 -> 48.6 us; 16/8 heads 55.8 -> 54.1).
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (16 * u + i > rel) s[u][n][i] = -INFINITY;
+        for (int u = 0; u < 4; ++u) {
+          const f32x4 x = s[u][n];
+          s[u][n] = f32x4{rel < 16 * u ? -INFINITY : x[0], rel < 16 * u + 1 ? -INFINITY : x[1],
+                          rel < 16 * u + 2 ? -INFINITY : x[2], rel < 16 * u + 3 ? -INFINITY : x[3]};
+        }
       }
     }
     // The reference of the exponents follows the running maximum lazily: it moves only when the
