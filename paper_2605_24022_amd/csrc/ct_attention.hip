@@ -129,7 +129,7 @@ __device__ __forceinline__ int swz_v(int r) { return D == 128 ? (r & 7) << 1 : (
 // it with direct global->LDS loads into three K and three V stages.
 // One loop for both groups, V(i) then M(i+1), with the barrier between the two for waves 0-3 and
 // behind them for waves 4-7: written as two loops, the compiler kept the initial accumulators for both
-// (253 registers and scratch reloads in the loop; 191 now).
+// (253 registers and scratch reloads in the loop; 190 now).
 template <int D>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_kernel(AttnArgs a) {
   constexpr int NWAVES = 8;
@@ -144,8 +144,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int INSTS = BN / RPI / NWAVES;     // such loads per wave, tile and tensor
   static_assert(INSTS >= 1 && (NWAVES * RPI) % 16 == 0, "tile / wave count mismatch");
 
-  __shared__ __align__(1024) unsigned char k_lds[NST * TILE_BYTES];
-  __shared__ __align__(1024) unsigned char v_lds[NST * TILE_BYTES];
+  __shared__ __align__(1024) unsigned char lds[2 * NST * TILE_BYTES];     // stages of K, then of V
+  constexpr int V_LDS = NST * TILE_BYTES;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, h = lane >> 4;
@@ -207,24 +207,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // The loads are inline assembly (M0 = LDS base of the wave's 1 KiB slot, each lane lands at
   // +16 * lane): the compiler neither reorders them nor adds waits of its own; the pipeline
   // below orders them against the fragment reads with explicit vmcnt waits and barriers.
-  auto dma16 = [&](const uint16_t* base, uint32_t byte_off, uint32_t lds_addr) __attribute__((always_inline)) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0), "v"(byte_off), "s"(base) : "memory", "m0");
-  };
-  const uint32_t k_lds_addr = (uint32_t)(uintptr_t)(lds_ptr_t)k_lds;
-  const uint32_t v_lds_addr = (uint32_t)(uintptr_t)(lds_ptr_t)v_lds;
+  const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_addr + wave * 1024);     // where this wave's first load of stage 0 goes
   // One wave-wide load: rows (NWAVES * idx + wave) * RPI .. of the tile that starts at key k0.
   // Rows from k_hi on (the end of this item's key range) are replaced by row k_hi - 1: they are
   // masked (their probabilities are zero), or belong to look-ahead tiles that are never consumed,
   // but what stands in those rows may not have been written yet - a later group of chunks still on
   // the host link - and a non-finite bit pattern there would turn 0 * v into NaN in the PV product.
-  auto issue_one = [&](const uint16_t* base, uint32_t lane_off, int k0, uint32_t stage_addr, int idx) __attribute__((always_inline)) {
-    const int key = tile_load_row(k0, ld_row + NWAVES * RPI * idx, k_hi);
-    dma16(base, __umul24(key, kv_row_bytes) + lane_off, stage_addr + (NWAVES * idx + wave) * 1024);
+  auto row_offset = [&](int k0, int idx) __attribute__((always_inline)) -> uint32_t {
+    return __umul24(tile_load_row(k0, ld_row + NWAVES * RPI * idx, k_hi), kv_row_bytes);
   };
-  auto issue_rows = [&](const uint16_t* base, uint32_t lane_off, int k0, uint32_t stage_addr) __attribute__((always_inline)) {
+  // (`to`: LDS address of the wave's first load in a K stage, uniform; `at`: bytes from there)
+  auto load16 = [&](const uint16_t* base, uint32_t byte_off, uint32_t to, int at) __attribute__((always_inline)) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 : : "s"(to), "v"(byte_off), "s"(base), "i"(at) : "memory", "m0", "scc");
+  };
+  auto issue_rows = [&](const uint16_t* base, uint32_t lane_off, int k0, int at) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < INSTS; ++i) issue_one(base, lane_off, k0, stage_addr, i);
+    for (int i = 0; i < INSTS; ++i) load16(base, row_offset(k0, i) + lane_off, lds_wave, at + i * NWAVES * 1024);
   };
 
   // ---- per-lane LDS read offsets ----------------------------------------------------------------
@@ -267,12 +267,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int n = 0; n < 2; ++n) m_limit[n] = m_run[n] == -INFINITY ? -INFINITY : m_run[n] / a.scale_log2 + limit_step;
   f32x4 s[4][2];       // S^T of the tile whose scores were computed last (four 16-key tiles)
   bf16x8 pf[2][2];     // P^T fragments (32-key step t, column tile n) of the tile whose softmax was done last
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int n = 0; n < 2; ++n)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) pf[t][n][e] = (__bf16)0.0f;
 
   typedef __attribute__((ext_vector_type(8))) short s16x8;
 
@@ -281,50 +275,111 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // this part nothing else hides the LDS latency, so the reads run PD fragments ahead of their MFMAs
   // through a ring of PD + 1, across the PV -> QK boundary as well, one LDS instruction per MFMA:
   // a wave issues in order, one LDS instruction per ~15 cycles, about the time of an MFMA (both reads
-  // of a V^T fragment in a row: 3 % of the launch).  Distances of 2 to 6 measure the same within 0.3 %.
+  // of a V^T fragment in a row: 3 % of the launch).  Distances of 2 to 4 measure the same within 0.5 %, 5 costs 1 to 2 %.
+  // MFMAs, reads, tile loads and nothing else: a vector instruction between two MFMAs of a wave waits for the
+  // first of them, so addresses are worked out behind the part and not where they are used.  The tile loads go out one
+  // by one, every fourth fragment of the PV half: together ahead of the first MFMA they hold it up.
+  // With those two, before / now: 32768 tokens, 4915 rows, 32/8 heads of 128 1093 / 1083 us, 8/2 heads of 64
+  // 284 / 271; 2048 tokens, 307 rows, 32/8 heads of 128 48.8 / 48.1, 8/2 of 64 41.5 / 39.7.  Not kept: addresses in
+  // the gaps of the QK half (heads of 128 5 to 10 % slower), loads there (up to 10 %) or ahead of the softmax of waves
+  // 4-7 (10 to 20 %), a fourth stage per tensor with the loads a tile further ahead (+-0.5 %), the loop written out for the three stages, so
+  // that no address changes (the accumulators then change registers from period to period, and spill).
   // The wave runs it at raised priority: its instruction stream is sparse and must not queue
   // behind the dense softmax stream of the other wave on the SIMD (without: 4 to 6 % of the launch).
   // The first M part has no previous tile and runs the QK half alone, the last one the PV half.
   constexpr int NPV = 2 * MT, NQK = 4 * KS;
 #ifndef CT_ATTN_PD
-#define CT_ATTN_PD 4
+#define CT_ATTN_PD 3
 #endif
   constexpr int PD = CT_ATTN_PD;
+  static_assert(8 * INSTS <= NPV, "tile loads lie in the PV half");
+  // M part i reads V(i-1) and K(i) at `va` and `ka`, and sends for K(i+2) and V(i+1): rows at `off_k` and
+  // `off_v`, into the stages of K(i-1) and V(i-2), which nobody reads any more.
+  uint32_t va[MT], ka[KS], off_k[INSTS], off_v[INSTS];
+  uint32_t st_p = lds_wave + 2 * TILE_BYTES, st_c = lds_wave, st_n = lds_wave + TILE_BYTES;     // stages of tiles i - 1, i, i + 1
+  const uint32_t k_to_v = v_lane_off - k_lane_off;
+  int next_row = k_lo + 3 * BN + ld_row;                                      // row of K(i+3) for this lane's first load
+#pragma unroll
+  for (int m = 0; m < MT; ++m) va[m] = lds_addr + V_LDS + 2 * TILE_BYTES + (v_a ^ (m << 5));
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) ka[ks] = lds_addr + (k_a ^ (ks << 6));
+#pragma unroll
+  for (int x = 0; x < INSTS; ++x) {
+    off_k[x] = row_offset(k_lo + 2 * BN, x) + k_lane_off;
+    off_v[x] = row_offset(k_lo + BN, x) + v_lane_off;
+  }
+  auto refill = [&](int x) __attribute__((always_inline)) {
+    if (x < INSTS) load16(a.k, off_k[x], st_p, x * NWAVES * 1024);
+    else load16(a.v, off_v[x - INSTS], st_n, V_LDS + (x - INSTS) * NWAVES * 1024);
+  };
+  // (the asm statements keep this here)
+  auto next_addresses = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < INSTS; ++x) {
+      off_v[x] = off_k[x] + k_to_v;
+      off_k[x] = __umul24(tile_load_row(next_row, NWAVES * RPI * x, k_hi), kv_row_bytes) + k_lane_off;
+      asm volatile("" : "+v"(off_v[x]), "+v"(off_k[x]));
+    }
+    next_row += BN;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      va[m] += st_c - st_p;
+      asm volatile("" : "+v"(va[m]));
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      ka[ks] += st_n - st_c;
+      asm volatile("" : "+v"(ka[ks]));
+    }
+    const uint32_t p = st_p;
+    st_p = st_c;
+    st_c = st_n;
+    st_n = p;
+  };
   // V^T fragments take two LDS instructions (halves of their keys), K fragments one.
   s16x8 fr[PD + 1];
-  auto load_first = [&](int j, const unsigned char* vb, const unsigned char* kb) __attribute__((always_inline)) {
+  typedef __attribute__((address_space(3))) const unsigned char* lds_bytes_t;
+  auto load_first = [&](int j) __attribute__((always_inline)) {
     s16x8& f = fr[j % (PD + 1)];
     if (j < NPV) {
       const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) s16x4*)(vb + 32 * (j / MT) * ROWB + (v_a ^ ((j % MT) << 5))));
+          (__attribute__((address_space(3))) s16x4*)((lds_bytes_t)va[j % MT] + 32 * (j / MT) * ROWB));
       f = __builtin_shufflevector(x, x, 0, 1, 2, 3, -1, -1, -1, -1);
     } else {
       const int ks = (j - NPV) >> 2, u = (j - NPV) & 3;
-      f = *reinterpret_cast<const s16x8*>(kb + (k_a ^ (ks << 6)) + u * 16 * ROWB);
+      f = *(__attribute__((address_space(3))) const s16x8*)((lds_bytes_t)ka[ks] + u * 16 * ROWB);
     }
   };
-  auto load_second = [&](int j, const unsigned char* vb) __attribute__((always_inline)) {
+  auto load_second = [&](int j) __attribute__((always_inline)) {
     if (j >= NPV) return;
     s16x8& f = fr[j % (PD + 1)];
     const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) s16x4*)(vb + (32 * (j / MT) + 16) * ROWB + (v_a ^ ((j % MT) << 5))));
+        (__attribute__((address_space(3))) s16x4*)((lds_bytes_t)va[j % MT] + (32 * (j / MT) + 16) * ROWB));
     f = __builtin_shufflevector(f, __builtin_shufflevector(x, x, 0, 1, 2, 3, -1, -1, -1, -1), 0, 1, 2, 3, 8, 9, 10, 11);
   };
-  auto part_m = [&](auto first, auto end, const unsigned char* vb, const unsigned char* kb, auto&& dma) __attribute__((always_inline)) {
+  auto part_m = [&](auto first, auto end) __attribute__((always_inline)) {
     constexpr int J0 = decltype(first)::value, J1 = decltype(end)::value;
     __builtin_amdgcn_s_setprio(3);
 #pragma unroll
     for (int j = J0; j < J0 + PD; ++j) {
-      load_first(j, vb, kb);
-      load_second(j, vb);
+      load_first(j);
+      load_second(j);
     }
-    dma();   // behind the first fragment reads: issued while the wave would wait for them anyway
+    if (J0 == NPV) {     // (no PV half to send them from)
+#pragma unroll
+      for (int x = 0; x < 2 * INSTS; ++x) refill(x);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = J0; j < J1; ++j) {
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
-        if (j + PD < J1 && n == 0) load_first(j + PD, vb, kb);
-        if (j + PD < J1 && n == 1) load_second(j + PD, vb);
+        if (j + PD < J1 && n == 0) load_first(j + PD);
+        if (j + PD < J1 && n == 1) load_second(j + PD);
+        if (J0 == 0 && J1 > NPV && n == 1 && j % 4 == 0 && j / 4 < 2 * INSTS) {
+          refill(j / 4);
+          __builtin_amdgcn_sched_barrier(0);
+        }
         const bf16x8 f = *reinterpret_cast<const bf16x8*>(&fr[j % (PD + 1)]);
         if (j < NPV) {
           const int t = j / MT, m = j % MT;
@@ -338,6 +393,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
     __builtin_amdgcn_s_setprio(0);
+    if (J1 > NPV) next_addresses();
   };
 
   // ---- V part: causal mask, online softmax, P^T fragments, rescale of O^T -------------------------
@@ -427,42 +483,31 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // compiler would otherwise guard their first use inside the loop with vmcnt waits that also
   // wait for the look-ahead tile loads.
   __builtin_amdgcn_s_waitcnt(0x0f70);
-  issue_rows(a.k, k_lane_off, k_lo, k_lds_addr);                           // K(0)
-  issue_rows(a.k, k_lane_off, k_lo + BN, k_lds_addr + TILE_BYTES);         // K(1)
-  issue_rows(a.v, v_lane_off, k_lo, v_lds_addr);                           // V(0)
+  issue_rows(a.k, k_lane_off, k_lo, 0);                                    // K(0)
+  issue_rows(a.k, k_lane_off, k_lo + BN, TILE_BYTES);                      // K(1)
+  issue_rows(a.v, v_lane_off, k_lo, V_LDS);                                // V(0)
   __builtin_amdgcn_s_waitcnt(WAIT_OLDER);                                  // K(0) has landed
   __syncthreads();
   auto end_of_period = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(WAIT_OLDER);     // this wave's loads of the previous period have landed
     __syncthreads();                            // everybody's have; everybody is done with K(i), V(i-1)
   };
-  // Period i uses K(i) and V(i-1); its M parts fetch K(i+2) and V(i+1) into the stages of
-  // K(i-1) and V(i-2), which nobody reads any more.  Nothing but the place of the barrier differs
-  // between the two groups: both read the same tiles for the whole period.
-  // The look-ahead loads of period i (K(i+2), V(i+1)) are issued by each wave at the start of its
-  // M part, right behind the first fragment reads (at the start of the QK half instead: the same within 0.5 %).
-  auto refill = [&](int i, int st_im1, int st_ip1) __attribute__((always_inline)) {
-    issue_rows(a.k, k_lane_off, k_lo + (i + 2) * BN, k_lds_addr + st_im1 * TILE_BYTES);
-    issue_rows(a.v, v_lane_off, k_lo + (i + 1) * BN, v_lds_addr + st_ip1 * TILE_BYTES);
-  };
-  int st_i = 0;                                 // stage of tile i (i mod 3)
+  // Period i uses K(i) and V(i-1).  Nothing but the place of the barrier differs between the two groups: both read
+  // the same tiles for the whole period.
   using J0 = std::integral_constant<int, 0>;
   using JQK = std::integral_constant<int, NPV>;
   using JEND = std::integral_constant<int, NPV + NQK>;
-  part_m(JQK{}, JEND{}, v_lds, k_lds, [&]() __attribute__((always_inline)) { refill(0, 2, 1); });
+  part_m(JQK{}, JEND{});
   if (group_b) end_of_period();
   for (int i = 0; i + 1 < n_kt; ++i) {
-    const int st_ip1 = st_i == 2 ? 0 : st_i + 1, st_ip2 = st_ip1 == 2 ? 0 : st_ip1 + 1;
     part_v(k_lo + i * BN);
     if (!group_b) end_of_period();
-    part_m(J0{}, JEND{}, v_lds + st_i * TILE_BYTES, k_lds + st_ip1 * TILE_BYTES,
-           [&]() __attribute__((always_inline)) { refill(i + 1, st_i, st_ip2); });
+    part_m(J0{}, JEND{});
     if (group_b) end_of_period();
-    st_i = st_ip1;
   }
   part_v(k_lo + (n_kt - 1) * BN);
   if (!group_b) end_of_period();
-  part_m(J0{}, JQK{}, v_lds + st_i * TILE_BYTES, k_lds, []() __attribute__((always_inline)) {});
+  part_m(J0{}, JQK{});
   __builtin_amdgcn_s_waitcnt(0x0f70);           // drain the look-ahead loads before the LDS is released
 
   // ---- epilogue -------------------------------------------------------------------------------
