@@ -407,8 +407,8 @@ ct_status ct_validate_indices(const int32_t* host_idx, int32_t n_sel, int32_t n_
 void ct_set_profiling(int32_t on);
 void ct_profile_reset(void);
 /* Measurement aid: the matrix-core rate this device sustains.  Runs a kernel that does nothing
- * but dependent-free v_mfma_f32_32x32x16_bf16 (one workgroup of eight waves per compute unit,
- * `iters` x 64 MFMAs per wave) on `stream`, waits for it, and stores the achieved TFLOP/s in
+ * but dependent-free v_mfma_f32_16x16x32_bf16 (one workgroup of eight waves per compute unit,
+ * `iters` x 128 MFMAs per wave) on `stream`, waits for it, and stores the achieved TFLOP/s in
  * *tflops (host pointer).  `scratch` is device memory of at least 256 * 512 * 4 bytes that the
  * kernel writes its (meaningless) results to.  This is the ceiling the MFMA-bound kernels are
  * measured against besides the published peak; it is not part of the partial-prefill path. */

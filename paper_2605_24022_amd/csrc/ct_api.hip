@@ -226,8 +226,8 @@ static ct_status check_indices_host(const int32_t* idx, int32_t n_sel, int32_t n
   return CT_OK;
 }
 
-// Nothing but MFMAs on four independent accumulators per wave: the rate the matrix cores
-// sustain on this device (power-limited well below the published peak).
+// Nothing but MFMAs on eight independent accumulators per wave, of the shape that attention and GEMM use: the rate
+// the matrix cores sustain on this device (power-limited well below the published peak).
 __global__ __launch_bounds__(512) void mfma_rate_kernel(float* out, int iters) {
   bf16x8 a, b;
 #pragma unroll
@@ -239,17 +239,12 @@ __global__ __launch_bounds__(512) void mfma_rate_kernel(float* out, int iters) {
     a[i] = (__bf16)(((int)(h & 0xffff) - 32768) * (1.0f / 16384.0f));
     b[i] = (__bf16)(((int)(h >> 16) - 32768) * (1.0f / 16384.0f));
   }
-  f32x16 c0 = {0}, c1 = {0}, c2 = {0}, c3 = {0};
+  f32x4 c[8] = {};
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c1, 0, 0, 0);
-      c2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c2, 0, 0, 0);
-      c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c3, 0, 0, 0);
-    }
+    for (int r = 0; r < 128; ++r) c[r % 8] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c[r % 8], 0, 0, 0);
   }
-  out[blockIdx.x * 512 + threadIdx.x] = c0[0] + c1[1] + c2[2] + c3[3];
+  out[blockIdx.x * 512 + threadIdx.x] = ((c[0][0] + c[1][1]) + (c[2][2] + c[3][3])) + ((c[4][0] + c[5][1]) + (c[6][2] + c[7][3]));
 }
 
 // Device-visible address of pinned host memory, or nullptr when `p` is not mapped for the device
@@ -410,7 +405,7 @@ ct_status ct_measure_mfma_rate(void* scratch, int32_t iters, void* stream, doubl
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (e != hipSuccess) return hip_fail(e, "mfma rate measurement");
-  const double flops = (double)blocks * 8 * (double)iters * 64 * 2.0 * 32 * 32 * 16;
+  const double flops = (double)blocks * 8 * (double)iters * 128 * 2.0 * 16 * 16 * 32;
   *tflops = flops / ((double)ms * 1e-3) / 1e12;
   return CT_OK;
 }
