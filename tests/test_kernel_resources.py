@@ -22,5 +22,4 @@ def test_no_kernel_keeps_tiles_in_scratch_memory():
     with open(B.LIB_PATH, "rb") as f:
         kernels = _scratch_bytes(f.read())
     assert len(kernels) > 30 and len({n for n, _ in kernels}) == len(kernels), "kernel metadata not found"
-    # (the 128-wide attention kernel keeps two values from before its loop there; the smallest tile is 64 bytes per lane)
-    assert [k for k in kernels if k[1] > 16] == []
+    assert [k for k in kernels if k[1] > 0] == []
