@@ -151,7 +151,7 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
   return p;
 }
 
-// With few (tile, head) pairs a launch lasts as long as one workgroup takes to walk its keys, 1.4 us per 64 of
+// With few (tile, head) pairs a launch lasts as long as one workgroup takes to walk its keys, 1.2 to 1.4 us per 64 of
 // them.  Up to half a round of pairs is split further, into one round of workgroups over at least 256 keys
 // each, as far as the scratch goes; from there on a second round costs what the shorter walk gains.  (Layer calls with
 // at least 128 or 192 keys: tiny model, 2048 tokens, 102 rows 36.8 and 34.2 against 33.2 us with 256, 4096 tokens, 40
@@ -159,12 +159,13 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
 // ahead, with 16/16 heads 10 %.)  At most 32 parts:
 // the merge reads them one after the other (8/2 heads of 64, 16384 tokens, 100 rows: 64 parts 68 us, 32 49, 8 61).
 // The parts also go through memory, 133 KB each, which short walks do not win back: the keys that the last row
-// is expected to see (n_sel rows anywhere) have to reach 560 and 5 more per pair.  Attention and merge, whole / split:
-// 32/8 heads of 128, 100 rows (16 pairs) of 513 tokens 20.4 / 22.0 us, 768 25.3 / 23.2, 1024 30.4 / 24.7, 2048 49 / 30;
-// 400 rows (56 pairs) of 768 27.0 / 27.8, 1024 31.5 / 30.5; 800 rows (104) of 1024 32.2 / 33.6, 1536 42.2 / 38.6;
-// 8/2 heads of 64, 100 rows (4) of 513 16.7 / 17.1, 640 18.9 / 17.9.  Layer calls, split against
-// whole: tiny model, 1024 tokens, 153 rows 28.7 / 34.3 us, 2048 tokens, 102 rows 32 / 54 us; Llama-3-8B 2048 tokens,
-// 20 rows 62 / 89 us, 1024 rows (128 pairs) 92 / 100 us, 8192 tokens, 81 rows 88 / 103 us.
+// is expected to see (n_sel rows anywhere) have to reach 560 and 5 more per pair.  With an earlier form of the attention
+// kernel, attention and merge, whole / split: 32/8 heads of 128, 100 rows (16 pairs) of 513 tokens 20.4 / 22.0 us, 768 25.3 /
+// 23.2; 400 rows (56 pairs) of 768 27.0 / 27.8, 1024 31.5 / 30.5; 800 rows (104) of 1024 32.2 / 33.6, 1536 42.2 / 38.6;
+// 8/2 heads of 64, 100 rows (4) of 513 16.7 / 17.1, 640 18.9 / 17.9.  With the present one, layer calls, split against
+// whole: tiny model, 640 tokens, 100 rows 25.0 / 25.4 us, 1024 tokens, 153 rows 26.2 / 31.8, 2048 tokens, 102 rows 29 / 51;
+// Llama-3-8B 768 tokens, 100 rows 57.4 / 60.3, 1024 tokens, 400 rows 63.3 / 68.5, 1536 tokens, 800 rows 77.3 / 81.6,
+// 2048 tokens, 20 rows 60 / 85, 1024 rows (128 pairs) 89 / 98, 8192 tokens, 81 rows 80 / 100.
 // With a tuning knob set the plan is plan_attention's, which follows them.
 // For the layer and stack calls, whose workspace is taken up by their rows in any case.  The attention entry points keep
 // to plan_attention: what needs no scratch there leaves the workspace, and the array that all calls on a GPU share,

@@ -24,9 +24,9 @@
 // LDS holds three weight tiles and two (of 128 tokens: three) token tiles, and the loads of two K steps are in flight.
 // On 256 tokens the slot of a step's token tile becomes free in the middle of the step, behind a barrier of its
 // own, once all waves have its fragments in registers: with the token tile one step ahead instead (and no second
-// barrier) 8192 x 8192 x 8192 takes 737 us against 723, QKV of 4915 rows 184 against 179.  Each barrier has MFMAs of the
+// barrier) 8192 x 8192 x 8192 and QKV of 4915 rows take 2 to 3 % longer.  Each barrier has MFMAs of the
 // same wave ahead of it and behind it, so it passes while the matrix core is busy.  Fragment reads and tile loads
-// go out one by one behind the MFMAs (in bursts ahead of each group of 16: 737 us as well).
+// go out one by one behind the MFMAs (in bursts ahead of each group of 16: 2 % longer as well).
 // Before, with 32 x 32 x 16 MFMAs / now: QKV 1228 rows 57 / 53 us, 2458 rows 102 / 92, 4915 rows 200 / 183, 32768 rows
 // 1235 / 1145; gate/up of 4915 rows 909 / 856; down projection of 4915 rows (K = 14336) 471 / 433.
 // Not kept: on 128 tokens two wave groups that take one k-step each, with wave tiles of 128 x 64 and the halves added
@@ -609,7 +609,10 @@ static void fill_tiles(GemmArgs* a, bool swiglu, int nb) {
 
 // Token tile width for a launch: 256 tokens per workgroup unless the workgroups then fill the last
 // round over the 256 compute units so badly that 128-token tiles (about 0.56 of the time of a
-// 256-token tile each) finish earlier.
+// 256-token tile each) finish earlier.  Measured, a full round of 128-token tiles against one of 256: linear with residual
+// K = 512 0.59, 2048 and 4096 0.56, 14336 0.54, gate/up 0.54 to 0.56.  Whole launches at the chosen height / the other:
+// QKV 4096 -> 6144 614 rows 41 / 70 us, 1228 56 / 77, 1638 85 / 94, 2458 97 / 106, 3276 152 / 170, 4915 189 / 207;
+// gate/up 4096 -> 14336 819 rows 178 / 189, 1228 246 / 258, 1638 303 / 350, 4915 829 / 897.
 static int pick_nb(const GemmArgs& a, bool swiglu) {
   GemmArgs t = a;
   double cost[3] = {0, 0, 0};
@@ -653,14 +656,14 @@ static ct_status launch_qkv_variant(const GemmArgs& a, const RopeTable& rope, co
 }
 
 // The rotation beside the projection costs it some of its memory bandwidth, which pays as long as idle compute
-// units take most of the work.  Llama-3-8B layer, fused against a launch of its own before: 2048 tokens,
-// 307 rows 88 us against 99 us, 8192 tokens, 983 rows 154 / 163 us, 32768 tokens, 1638 rows 536 / 552 us; with
-// 240 tiles on 256 units 206 / 205 us (8192 tokens, 1228 rows) and 529 / 529 us (16384 tokens, 2457 rows).
+// units take most of the work.  Llama-3-8B layer, fused / in a launch of its own before: 2048 tokens,
+// 307 rows 67 / 77 us, 8192 tokens, 983 rows 146 / 159, 32768 tokens, 1638 rows 518 / 538, 131072 tokens, 1310 rows 2133 / 2193;
+// with 240 tiles on 256 units 200 / 199 (8192 tokens, 1228 rows) and 511 / 517 (16384 tokens, 2457 rows): within what runs differ by.
 // A unit holds one such workgroup (it claims the LDS of a tile).  With the loads of eight heads in flight that still
 // reads at speed, with two or with the loop over any number it does not, and what the idle units have not moved when the
-// projection ends takes longer than in a launch of its own: at most 3 MB for each.  Inputs from memory, fused / apart:
-// 16/16 heads of 64, 32768 tokens, 9830 rows (6.1 MB) 1093 / 1074 us, 1638 rows (2.7 MB) 381 / 384, 327 rows (1.2 MB)
-// 214 / 218; 32/2 heads of 128, 131072 tokens, 1310 rows (4.6 MB) 1844 / 1812; 32/8 of 128, 131072, 1310 (9.6 MB) 2133 / 2180.
+// projection ends takes longer than in a launch of its own: at most 3 MB for each.  Fused / apart: 16/16 heads of 64,
+// 32768 tokens, 9830 rows (6.1 MB) 1024 / 1021 us, 1638 rows (2.7 MB) 359 / 360, 327 rows (1.2 MB) 194 / 199; with inputs from memory
+// (earlier forms of the kernels) 1093 / 1074, 381 / 384, 214 / 218, and 32/2 heads of 128, 131072 tokens, 1310 rows (4.6 MB) 1844 / 1812.
 bool projection_leaves_units(const ct_layer_cfg* cfg, int32_t n_sel, int64_t move_tokens) {
   GemmArgs a;
   memset(&a, 0, sizeof(a));
@@ -738,7 +741,9 @@ static int split_plan(const GemmArgs& a256, size_t ws_bytes, double cost_unsplit
   if (ws_bytes < (size_t)rem * parts * 256 * BF * sizeof(float)) return 1;
   // in units of one round of 256-token tiles: the split round, plus the partial tiles' trip
   // through memory and the two extra launches (measured: 0.45 of a round for 256 partial tiles at
-  // K = 4096, where a round takes 100 us; in proportion less for longer reductions)
+  // K = 4096, where a round takes 100 us; in proportion less for longer reductions).  4096 features with residual, split /
+  // whole: K = 14336 153 rows 46 / 121 us, 614 85 / 121, 1228 125 / 141, 1638 167 / 157, 4915 434 / 503; K = 4096 153 rows
+  // 27 / 39, 300 38 / 39, 614 43 / 40, 1638 67 / 51: chosen right but for 300 rows, 4 % behind
   const double cost = (double)(*full_tiles / n_cu) + 1.05 / parts + 0.45 * (64.0 / nk) * (rem * parts / 256.0);
   return cost < cost_unsplit ? parts : 1;
 }
