@@ -131,6 +131,9 @@ AttnPlan plan_attention(const ct_layer_cfg* cfg, int n_ctx, int n_sel) {
   // Split the key range only when the (tile, kv head) pairs alone leave compute units idle:
   // measured on MI355X, an unsplit launch wins as soon as there are about 1.5 pairs per
   // compute unit (each split costs an fp32 partial (O, m, l) round trip and a merge kernel).
+  // Targets of 256 / 384 / 512 / 768 pairs, Llama-3-8B layer: 32768 tokens, 1638 rows 539 / 542 / 646 / 594 us, 3276 rows
+  // 1017 / 1018 / 1048 / 1044, 4915 rows 1348 / 1355 / 1350 / 1410; but 8192 tokens, 1228 rows 186 / 197 / 198 / 197,
+  // 16384 tokens, 2457 rows 495 / 511 / 511 / 450: how the parts fall into rounds decides, and no one target wins everywhere.
   const long pairs = (long)p.n_tiles * cfg->n_kv_heads;
   const long target = knob_split_target() > 0 ? knob_split_target() : 384;   // 1.5 x 256 compute units
   if (pairs > 0 && pairs < target && n_ctx > 2048) {
